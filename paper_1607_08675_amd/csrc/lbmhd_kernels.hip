@@ -1163,7 +1163,7 @@ __device__ void block_reduce(double (&v)[kNRed], double* __restrict__ out) {
 }
 
 // One pass over the lattice: a block of kDiagThreads threads owns as many
-// columns and walks strips of kDiagRows rows (tile t, strip r: unit
+// columns and walks strips of `rows` rows (tile t, strip r: unit
 // r * tiles_x + t; a block takes units blockIdx.x, + gridDim.x, ...).  Per row
 // it loads the populations of row y + 1 (no streaming: the moments of the
 // current state), forms rho, u, B in FP64 into a rolling 3-row LDS buffer with
@@ -1176,7 +1176,7 @@ __device__ void block_reduce(double (&v)[kNRed], double* __restrict__ out) {
 // (a correctly rounded square root is monotone, so the root of the largest
 // square is the largest root).
 constexpr int kDiagThreads = 256;
-constexpr int kDiagRows = 64;   // 8-11% faster than 16 rows (fewer halo rows)
+constexpr int kDiagRows = 64;   // the most rows of a strip
 
 constexpr int kDiagNC = kDiagThreads + 2;
 typedef double DiagRing[3][5][kDiagNC];   // rho, ux, uy, Bx, By of three rows
@@ -1272,7 +1272,7 @@ __device__ __forceinline__ void diag_partial(const double (&v)[kNRed], DiagRing&
 template <int ST>
 __global__ __launch_bounds__(kDiagThreads) void k_diag(const typename Codec<ST>::T* __restrict__ lat,
                                                        double* __restrict__ part, Geom geo,
-                                                       int tiles_x, int units) {
+                                                       int tiles_x, int units, int rows) {
   using C = Codec<ST>;
   using T = typename C::T;
   __shared__ DiagRing mac;
@@ -1282,8 +1282,8 @@ __global__ __launch_bounds__(kDiagThreads) void k_diag(const typename Codec<ST>:
   for (int q = 0; q < kNRed; ++q) v[q] = 0.0;
   for (int u = int(blockIdx.x); u < units; u += int(gridDim.x)) {
     const int xt = (u % tiles_x) * kDiagThreads;
-    const int y0 = (u / tiles_x) * kDiagRows;
-    const int y1 = min(y0 + kDiagRows, geo.ny);
+    const int y0 = (u / tiles_x) * rows;
+    const int y1 = min(y0 + rows, geo.ny);
     const int x = xt + tx;
     const bool active = x < geo.nx;
     const int xc = x % geo.nx;   // past the last column: its periodic images
@@ -1332,7 +1332,8 @@ template <bool LES>
 __global__ __launch_bounds__(kDiagThreads) void k_step_diag(const float* __restrict__ src,
                                                             float* __restrict__ dst,
                                                             double* __restrict__ part, Geom geo,
-                                                            Rates rt, int tiles_x, int units) {
+                                                            Rates rt, int tiles_x, int units,
+                                                            int rows) {
   __shared__ DiagRing mac;
   const int tx = int(threadIdx.x);
   const long long P = geo.plane;
@@ -1341,8 +1342,8 @@ __global__ __launch_bounds__(kDiagThreads) void k_step_diag(const float* __restr
   for (int q = 0; q < kNRed; ++q) v[q] = 0.0;
   for (int u = int(blockIdx.x); u < units; u += int(gridDim.x)) {
     const int xt = (u % tiles_x) * kDiagThreads;
-    const int y0 = (u / tiles_x) * kDiagRows;
-    const int y1 = min(y0 + kDiagRows, geo.ny);
+    const int y0 = (u / tiles_x) * rows;
+    const int y1 = min(y0 + rows, geo.ny);
     const int x = xt + tx;
     const bool active = x < geo.nx;
     const int xc = x % geo.nx;   // past the last column: its periodic images
@@ -1739,23 +1740,39 @@ hipError_t launch_copy(const void* src, void* dst, size_t bytes, hipStream_t s) 
   return hipGetLastError();
 }
 
+// Strip height of the diagnostics passes.  A block takes its rows one after
+// another (about 1.9 us a row, the latency of the loads and of the FP64
+// chain), so a strip is only as tall as leaves about 1024 of them.  64-row
+// strips on every lattice against this rule: k_step_diag 121 and 10.6 us at
+// 64^2 (one block and 64), 132 and 11.9 us at 256^2, k_diag 82 and 31 us at
+// 1024^2 (4 rows).  On the largest lattices 64 rows are 8-11% faster than 16
+// (two halo rows a strip).
+static int diag_rows(const Geom& g) {
+  const long long tiles_x = (g.nx + kDiagThreads - 1) / kDiagThreads;
+  return int(std::max<long long>(1, std::min<long long>(kDiagRows, tiles_x * g.ny / 1024)));
+}
+
+static long long diag_units(const Geom& g) {
+  const long long tiles_x = (g.nx + kDiagThreads - 1) / kDiagThreads;
+  const int rows = diag_rows(g);
+  return tiles_x * ((g.ny + rows - 1) / rows);
+}
+
 int diag_partials(const Geom& g) {
-  const int tiles_x = (g.nx + kDiagThreads - 1) / kDiagThreads;
-  const long long units = (long long)tiles_x * ((g.ny + kDiagRows - 1) / kDiagRows);
-  return int(std::min<long long>(kDiagBlocks, units));
+  return int(std::min<long long>(kDiagBlocks, diag_units(g)));
 }
 
 hipError_t launch_diag(int storage, const void* lat, double* part, double* out_dev,
                        const Geom& g, hipStream_t s) {
   const int tiles_x = (g.nx + kDiagThreads - 1) / kDiagThreads;
-  const long long units = (long long)tiles_x * ((g.ny + kDiagRows - 1) / kDiagRows);
-  const int nparts = diag_partials(g);
+  const long long units = diag_units(g);
+  const int nparts = diag_partials(g), rows = diag_rows(g);
   if (storage == LBMHD_FP32)
     hipLaunchKernelGGL(k_diag<LBMHD_FP32>, dim3(nparts), dim3(kDiagThreads), 0, s,
-                       static_cast<const float*>(lat), part, g, tiles_x, int(units));
+                       static_cast<const float*>(lat), part, g, tiles_x, int(units), rows);
   else
     hipLaunchKernelGGL(k_diag<LBMHD_FP16>, dim3(nparts), dim3(kDiagThreads), 0, s,
-                       static_cast<const _Float16*>(lat), part, g, tiles_x, int(units));
+                       static_cast<const _Float16*>(lat), part, g, tiles_x, int(units), rows);
   hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(256), 0, s, part, nparts, out_dev);
   return hipGetLastError();
 }
@@ -1763,16 +1780,16 @@ hipError_t launch_diag(int storage, const void* lat, double* part, double* out_d
 hipError_t launch_step_diag(bool les, const void* src, void* dst, double* part, double* out_dev,
                             const Geom& g, const Rates& r, hipStream_t s) {
   const int tiles_x = (g.nx + kDiagThreads - 1) / kDiagThreads;
-  const long long units = (long long)tiles_x * ((g.ny + kDiagRows - 1) / kDiagRows);
-  const int nparts = diag_partials(g);
+  const long long units = diag_units(g);
+  const int nparts = diag_partials(g), rows = diag_rows(g);
   auto* a = static_cast<const float*>(src);
   auto* b = static_cast<float*>(dst);
   if (les)
     hipLaunchKernelGGL(k_step_diag<true>, dim3(nparts), dim3(kDiagThreads), 0, s, a, b, part, g, r,
-                       tiles_x, int(units));
+                       tiles_x, int(units), rows);
   else
     hipLaunchKernelGGL(k_step_diag<false>, dim3(nparts), dim3(kDiagThreads), 0, s, a, b, part, g,
-                       r, tiles_x, int(units));
+                       r, tiles_x, int(units), rows);
   hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(256), 0, s, part, nparts, out_dev);
   return hipGetLastError();
 }
