@@ -54,9 +54,28 @@ int eddy_of(const lbmhd_t* h) {
 // cross-helicity closure's vorticity).
 bool reads_neighbours(const lbmhd_t* h) { return (h->p.les & 2) || eddy_of(h) == 2; }
 
+// The most steps of one launch of the tile kernel, 0 where it is not taken:
+// the automatic mode's kernel for small lattices (steps_per_pass asks for the
+// row-walking kernels by name).
+int tile_most(const lbmhd_t* h) {
+  if (h->p.inplace || h->p.steps_per_pass != 0) return 0;
+  return lbk::tile_steps(h->p.storage, reads_neighbours(h), h->geo);
+}
+
+// Whether launches of one to three steps go to the tile kernel as well.
+bool tile_short(const lbmhd_t* h) {
+  return tile_most(h) > 0 && lbk::tile_short_pays(reads_neighbours(h), h->geo);
+}
+
+hipError_t launch_tile_steps(const lbmhd_t* h, const void* src, void* dst, int k) {
+  return lbk::launch_tile(h->p.storage, eddy_of(h), (h->p.les & 2) != 0, src, dst, k, h->geo,
+                          h->rates, h->p.delta, h->stream);
+}
+
 // One step src -> dst with the handle's closure.
 hipError_t launch_one_step(const lbmhd_t* h, const void* src, void* dst) {
   const int eddy = eddy_of(h);
+  if (reads_neighbours(h) && tile_short(h)) return launch_tile_steps(h, src, dst, 1);
   if (reads_neighbours(h))
     return lbk::launch_step_nb(h->p.storage, eddy, (h->p.les & 2) != 0, src, dst, h->geo,
                                h->rates, h->p.delta, h->stream);
@@ -66,6 +85,7 @@ hipError_t launch_one_step(const lbmhd_t* h, const void* src, void* dst) {
 // Two steps src -> dst in one pass (mid: also the state between them).
 hipError_t launch_two_steps(const lbmhd_t* h, const void* src, void* dst, void* mid) {
   const int eddy = eddy_of(h);
+  if (!mid && tile_short(h)) return launch_tile_steps(h, src, dst, 2);
   if (reads_neighbours(h))
     return lbk::launch_step_nb2(h->p.storage, eddy, (h->p.les & 2) != 0, src, dst, mid, h->geo,
                                 h->rates, h->p.delta, h->stream);
@@ -490,6 +510,24 @@ int lbmhd_step(lbmhd_t* h, int64_t nsteps) {
   const bool les = (h->p.les & 1) && (h->p.cs > 0.0 || h->p.cs_b > 0.0);
   int64_t t = 0;
   const int ps = pass_steps(h);
+  if (const int most = tile_most(h)) {
+    // as even launches as the count allows (9 = 5 + 4); where short launches
+    // do not pay, whole ones only, the remainder going by rows
+    const int64_t launches = (nsteps + most - 1) / most;
+    const bool all = tile_short(h) || (launches > 0 && nsteps / launches >= most - 1);
+    const int64_t m = all ? launches : nsteps / most;
+    for (int64_t i = 0; i < m; ++i) {
+      const int64_t left = all ? nsteps - t : (m - i) * most;
+      const int k = int((left + (m - i) - 1) / (m - i));
+      if (k == 1) break;   // a lone step: the single-step kernels below
+      if (int rc = before_write(h, 1 - h->cur)) return rc;
+      hipError_t e = launch_tile_steps(h, h->lat[h->cur], h->lat[1 - h->cur], k);
+      if (e != hipSuccess) return hip_fail(h, e, "step launch");
+      h->cur = 1 - h->cur;
+      h->step += k;
+      t += k;
+    }
+  }
   if (ps == 3) {
     // a remainder of two steps is one pair, of one step a single step: a
     // triple and a single step took 5-8% less time than two pairs from 2048^2
@@ -729,7 +767,7 @@ int lbmhd_run(lbmhd_t* h, int64_t nsteps, int64_t every, double* dev, lbmhd_diag
   // its result in one pass on the bound stream
   const int ps = pass_steps(h);
   const bool fuse = !h->p.inplace && h->p.storage == LBMHD_FP32 && !reads_neighbours(h) &&
-                    (ps == 1 || every % ps == 1);
+                    (ps == 1 || every % ps == 1 || tile_most(h) > 0);
   if (!h->p.inplace && !fuse && !h->side) {
     hipError_t e = hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&h->ev_state, hipEventDisableTiming);

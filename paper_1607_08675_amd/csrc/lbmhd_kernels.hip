@@ -812,6 +812,121 @@ __global__ __launch_bounds__(kNb2Threads) __attribute__((amdgpu_waves_per_eu(4))
   }
 }
 
+// ------------------------------------------ several steps of a tile in LDS
+// dst = (C S)^k src on small lattices, k >= 1 a run-time argument: a block
+// owns a tile of the output and a region of RX x RY sites around it, takes
+// the first update of every site of the region from HBM (periodic images
+// where the region passes the lattice's edge or is larger than the lattice),
+// and the other k - 1 from LDS, on a region that shrinks by one site on each
+// side per step.  A thread owns the S sites (rx, ry + j RY / S).  It holds
+// the rest populations in registers; the 16 moving ones pass through one LDS
+// buffer (written, barrier, read at x - c, barrier).
+// The closures that read their neighbours' moments (NB) shrink by two sites
+// a step: each step's gathered moments go to a second LDS buffer, and the
+// update takes the sites whose eight neighbours were gathered.
+// The populations pass through the storage codec between the steps, so the
+// result equals k single steps bit for bit.  Plain stores: a tile's rows end
+// inside cache lines, which the L2 then completes (non-temporal stores
+// measured 5-15% slower from 512^2 on).
+template <int ST, int EDDY, bool KIN, int RX, int RY, int S>
+__global__ __launch_bounds__(RX* RY / S) void k_tile(
+    const typename Codec<ST>::T* __restrict__ src, typename Codec<ST>::T* __restrict__ dst,
+    Geom geo, Rates rt, float c12, int k, int tiles_x, int tile_w, int tile_h) {
+  using C = Codec<ST>;
+  using T = typename C::T;
+  constexpr bool NB = KIN || EDDY == 2;
+  constexpr int NF = KIN ? 5 : 3;     // moments of NB: rho - 1, j (, B)
+  constexpr int N = RX * RY, H = RY / S;
+  __shared__ T pl[16][N];             // moving planes (kTileRow)
+  __shared__ float mo[NB ? NF : 1][NB ? N : 1];
+  const int rx = int(threadIdx.x) % RX, ry0 = int(threadIdx.x) / RX;
+  const int halo = NB ? 2 * k - 1 : k - 1;
+  const int x0 = (int(blockIdx.x) % tiles_x) * tile_w, y0 = (int(blockIdx.x) / tiles_x) * tile_h;
+  const int wx = min(tile_w, geo.nx - x0), wy = min(tile_h, geo.ny - y0);
+  int x = (x0 - halo + rx) % geo.nx;
+  x = x < 0 ? x + geo.nx : x;
+  const int xl = x == 0 ? geo.nx - 1 : x - 1, xr = x == geo.nx - 1 ? 0 : x + 1;
+  float v[S][kNPop][1];
+#pragma unroll
+  for (int j = 0; j < S; ++j) {
+    int y = (y0 - halo + ry0 + j * H) % geo.ny;
+    y = y < 0 ? y + geo.ny : y;
+    unsigned row[3];
+    t2_rows(y, geo, row);
+    gather_row<ST, 1>(src, geo.plane, x, xl, xr, row, v[j]);
+  }
+  for (int s = 1;; ++s) {
+    // the update of step s takes the sites at least `in` sites inside the region
+    const int in = NB ? 2 * s - 1 : s - 1;
+    if constexpr (NB) {
+#pragma unroll
+      for (int j = 0; j < S; ++j) {
+        float p[kNPop], m[5];
+#pragma unroll
+        for (int q = 0; q < kNPop; ++q) p[q] = v[j][q][0];
+        site_moments(p, m);
+#pragma unroll
+        for (int i = 0; i < NF; ++i) mo[i][(ry0 + j * H) * RX + rx] = m[i];
+      }
+      __syncthreads();
+    }
+#pragma unroll
+    for (int j = 0; j < S; ++j) {
+      const int ry = ry0 + j * H;
+      if (rx >= in && rx < RX - in && ry >= in && ry < RY - in) {
+        if constexpr (NB) {
+          const NbTerms kc = nb_terms<EDDY, KIN>(&mo[0][(ry - 1) * RX], &mo[0][ry * RX],
+                                                 &mo[0][(ry + 1) * RX], N, rx, c12);
+          float f[9], g[10];
+#pragma unroll
+          for (int i = 0; i < 9; ++i) f[i] = v[j][i][0];
+#pragma unroll
+          for (int i = 0; i < 10; ++i) g[i] = v[j][9 + i][0];
+          collide<EDDY, KIN>(f, g, rt, kc);
+#pragma unroll
+          for (int i = 0; i < 9; ++i) v[j][i][0] = f[i];
+#pragma unroll
+          for (int i = 0; i < 10; ++i) v[j][9 + i][0] = g[i];
+        } else {
+          collide_sites<1, EDDY == 1, ST == kFP16S>(v[j], rt);
+        }
+        if (s < k) {
+#pragma unroll
+          for (int q = 0; q < kNPop; ++q) {
+            const T e = C::enc(v[j][q][0]);
+            if (kTileRow[q] >= 0)
+              pl[kTileRow[q] < 0 ? 0 : kTileRow[q]][ry * RX + rx] = e;
+            else
+              v[j][q][0] = C::dec(e);
+          }
+        }
+      }
+    }
+    if (s == k) break;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < S; ++j) {
+      const int ry = ry0 + j * H;
+      if (rx > in && rx < RX - 1 - in && ry > in && ry < RY - 1 - in) {
+#pragma unroll
+        for (int q = 0; q < kNPop; ++q)
+          if (kTileRow[q] >= 0)
+            v[j][q][0] = C::dec(pl[kTileRow[q] < 0 ? 0 : kTileRow[q]]
+                                  [(ry - kPlaneCy[q]) * RX + rx - kPlaneCx[q]]);
+      }
+    }
+    if constexpr (!NB) __syncthreads();   // NB: the moments' barrier follows every read
+  }
+  if (rx >= halo && rx < halo + wx) {
+#pragma unroll
+    for (int j = 0; j < S; ++j) {
+      const int oy = ry0 + j * H - halo;
+      if (oy >= 0 && oy < wy)
+        store_row<ST, 1, false>(dst, geo.plane, unsigned(y0 + oy) * geo.pitch + unsigned(x), v[j]);
+    }
+  }
+}
+
 // ------------------------------------------------------ in-place (AA) step
 // One lattice updated in place by two alternating steps.  Layout N (natural,
 // as for k_step): slot q at x holds the post-collision f*_q(x).  Layout R
@@ -1635,6 +1750,97 @@ hipError_t launch_step2(int storage, bool les, const void* src, void* dst, void*
     launch_step2_v<kFP16S, 1>(les, src, dst, mid, g, r, s);
   return hipGetLastError();
 }
+
+// Regions of the tile kernel.  The smallest lattices need blocks, so 16 x 16
+// sites and up to five steps (tiles of 8 x 8; closures with neighbour terms
+// three steps, 6 x 6); from 200^2 on 32 x 32 (32 x 28 with FP32 neighbour
+// terms), two sites a thread and five (three) steps, which leaves two blocks
+// per CU in 64-75 KB of LDS each: taller regions with one block per CU, four
+// sites a thread or fewer steps were 10-40% slower at 512^2 to 1024^2.
+// us per step, single-step kernel / 16 x 16 / 32 x 32, FP32:
+// 64^2 2.7 / 1.15 / 1.9, 256^2 4.6 / 2.5 / 2.4, 512^2 9.7 / 5.7 / 4.5,
+// 1024^2 30 / 18 / 12; kinetic closure: 64^2 25 / 2.0 / 2.6,
+// 256^2 26 / 5.1 / 4.5, 512^2 32 / 14 / 8.6.
+template <int ST, int EDDY, bool KIN>
+struct Tile {
+  static constexpr bool kNb = KIN || EDDY == 2;
+  static constexpr int kBigRows = kNb && ST == LBMHD_FP32 ? 28 : 32;
+};
+
+static bool tile_small(const Geom& g) { return (long long)g.nx * g.ny <= 40000; }
+
+template <int ST, int EDDY, bool KIN, int RX, int RY, int S>
+static void launch_tile_r(const void* src, void* dst, int k, const Geom& g, const Rates& r,
+                          float c12, hipStream_t s) {
+  using T = typename Codec<ST>::T;
+  const int halo = Tile<ST, EDDY, KIN>::kNb ? 2 * k - 1 : k - 1;
+  const int w = RX - 2 * halo, h = RY - 2 * halo;
+  const int tiles_x = (g.nx + w - 1) / w, tiles_y = (g.ny + h - 1) / h;
+  hipLaunchKernelGGL((k_tile<ST, EDDY, KIN, RX, RY, S>), dim3(tiles_x * tiles_y),
+                     dim3(RX * RY / S), 0, s, static_cast<const T*>(src), static_cast<T*>(dst), g,
+                     r, c12, k, tiles_x, w, h);
+}
+
+template <int ST, int EDDY, bool KIN>
+static void launch_tile_c(const void* src, void* dst, int k, const Geom& g, const Rates& r,
+                          float c12, hipStream_t s) {
+  if (tile_small(g))
+    launch_tile_r<ST, EDDY, KIN, 16, 16, 1>(src, dst, k, g, r, c12, s);
+  else
+    launch_tile_r<ST, EDDY, KIN, 32, Tile<ST, EDDY, KIN>::kBigRows, 2>(src, dst, k, g, r, c12, s);
+}
+
+template <int ST>
+static hipError_t launch_tile_s(int eddy, bool kin, const void* src, void* dst, int k,
+                                const Geom& g, const Rates& r, float c12, hipStream_t s) {
+  constexpr int SN = ST == kFP16S ? LBMHD_FP16 : ST;   // codec of the closures with neighbours
+  if (kin && eddy == 0)
+    launch_tile_c<SN, 0, true>(src, dst, k, g, r, c12, s);
+  else if (kin && eddy == 1)
+    launch_tile_c<SN, 1, true>(src, dst, k, g, r, c12, s);
+  else if (kin)
+    launch_tile_c<SN, 2, true>(src, dst, k, g, r, c12, s);
+  else if (eddy == 2)
+    launch_tile_c<SN, 2, false>(src, dst, k, g, r, c12, s);
+  else if (eddy == 1)
+    launch_tile_c<ST, 1, false>(src, dst, k, g, r, c12, s);
+  else
+    launch_tile_c<ST, 0, false>(src, dst, k, g, r, c12, s);
+  return hipGetLastError();
+}
+
+hipError_t launch_tile(int storage, int eddy, bool kin, const void* src, void* dst, int k,
+                       const Geom& g, const Rates& r, double delta, hipStream_t s) {
+  const int most = kin || eddy == 2 ? 3 : 5;
+  if (k < 1 || k > most) return hipErrorInvalidValue;
+  const float c12 = float(delta * delta / 12.0);
+  if (storage == LBMHD_FP32)
+    return launch_tile_s<LBMHD_FP32>(eddy, kin, src, dst, k, g, r, c12, s);
+  return launch_tile_s<kFP16S>(eddy, kin, src, dst, k, g, r, c12, s);
+}
+
+// The lattice's sites, weighted by the share of the row-walking kernels'
+// 256-column tiles that they fill.
+static double tile_size(const Geom& g) {
+  const double cols = double((g.nx + 255) / 256) * 256;
+  return double(g.nx) * g.ny * (g.nx / cols);
+}
+
+// Where tiles stop paying, us per step in tiles / by rows (k_step_t3, k_step2
+// with FP16, k_step_nb2 or k_step_nb): FP32 1024^2 12.2 / 14.2,
+// 2048 x 1024 22.5 / 26.2, 2048^2 45.1 / 45.2; FP16 1024^2 12.4 / 16.9,
+// 2048 x 1024 21.9 / 24.1, 2048^2 41.9 / 45.6; kinetic closure FP32
+// 724^2 14.8 / 22.0, 3000 x 300 23.1 / 23.7, 1024^2 25.6 / 23.8, FP16
+// 1448^2 41.6 / 59.1, 2048 x 1024 42.7 / 38.5.
+int tile_steps(int storage, bool nb, const Geom& g) {
+  const double limit = nb ? (storage == LBMHD_FP32 ? 1.0e6 : 2.0e6) : 4.0e6;
+  return tile_size(g) < limit ? (nb ? 3 : 5) : 0;
+}
+
+// One and two steps: kinetic closure 1024^2 45.7 / 45.1 for one; the plain
+// kernels' pairs 724^2 11.9 / 15.1 FP32 and 10.1 / 18.3 FP16, 1024^2
+// 22.5 / 18.1 and 18.3 / 18.7.
+bool tile_short_pays(bool nb, const Geom& g) { return tile_size(g) < (nb ? 1.0e6 : 7.5e5); }
 
 template <int ST, int V, int PHASE>
 void launch_step_aa_v(bool les, void* lat, const Geom& g, const Rates& r, hipStream_t s) {

@@ -103,6 +103,10 @@ __device__ __forceinline__ void st_plane_nt(T* __restrict__ base, unsigned off, 
   __builtin_nontemporal_store(
       v, reinterpret_cast<VT*>(reinterpret_cast<char*>(base) + off * unsigned(sizeof(T))));
 }
+template <typename VT, typename T>
+__device__ __forceinline__ void st_plane(T* __restrict__ base, unsigned off, VT v) {
+  *reinterpret_cast<VT*>(reinterpret_cast<char*>(base) + off * unsigned(sizeof(T))) = v;
+}
 
 // velocity (c_x, c_y) of the population held by each of the 19 planes
 __device__ constexpr int kPlaneCx[kNPop] = {0, 1, 0, -1, 0, 1, -1, -1, 1, 0,
@@ -342,7 +346,7 @@ __device__ __forceinline__ void collide_sites(float (&v)[kNPop][V], const Rates&
 }
 
 // Encode and store the V sites of v at element `off` of every plane.
-template <int ST, int V>
+template <int ST, int V, bool NT = true>
 __device__ __forceinline__ void store_row(typename Codec<ST>::T* __restrict__ dst, long long P,
                                           unsigned off, const float (&v)[kNPop][V]) {
   using C = Codec<ST>;
@@ -356,7 +360,10 @@ __device__ __forceinline__ void store_row(typename Codec<ST>::T* __restrict__ ds
 #pragma unroll
       for (int j = 0; j < V; ++j) w[j] = C::enc(v[q][j]);
     }
-    st_plane_nt<VT>(dst + q * P, off, w);
+    if constexpr (NT)
+      st_plane_nt<VT>(dst + q * P, off, w);
+    else
+      st_plane<VT>(dst + q * P, off, w);
   }
 }
 
@@ -374,6 +381,10 @@ __device__ constexpr int kT2Index[kNPop] = {0, 0, 0, 1, 0, 0, 1, 0, 1, 0,
 // {2, 11, 16} (c_y = +1), {4, 13, 18} (c_y = -1)
 __device__ constexpr int kT2Reg[kNPop] = {0, -1, 0, -1, 0, -1, -1, -1, -1, 1,
                                           -1, 1, -1, 1, 2, -1, 2, -1, 2};
+
+// index of a plane among the 16 that move (-1 for the three rest planes)
+__device__ constexpr int kTileRow[kNPop] = {-1, 0, 1,  2,  3,  4,  5, 6,  7, -1,
+                                            8,  9, 10, 11, -1, 12, 13, 14, 15};
 
 // Row offsets of the gather for row r (-ny <= r < 2 ny, wrapped once): the source
 // row of a plane with velocity c_y is r - c_y, indexed by c_y + 1.
