@@ -1763,6 +1763,20 @@ struct Tile {
 
 static bool tile_small(const Geom& g) { return (long long)g.nx * g.ny <= 40000; }
 
+// Steps per launch: without neighbour terms up to nine in the larger region
+// while the smaller tiles still leave a CU each (256^2: five steps 14.5 us, 121
+// blocks; nine steps 21.3 us, 256 blocks).
+static int tile_most(bool nb, const Geom& g) {
+  if (nb) return 3;
+  int k = 5;
+  if (!tile_small(g))
+    for (; k < 9; ++k) {
+      const int w = 32 - 2 * k;   // tile of k + 1 steps
+      if ((long long)((g.nx + w - 1) / w) * ((g.ny + w - 1) / w) > 256) break;
+    }
+  return k;
+}
+
 template <int ST, int EDDY, bool KIN, int RX, int RY, int S>
 static void launch_tile_r(const void* src, void* dst, int k, const Geom& g, const Rates& r,
                           float c12, hipStream_t s) {
@@ -1805,8 +1819,7 @@ static hipError_t launch_tile_s(int eddy, bool kin, const void* src, void* dst, 
 
 hipError_t launch_tile(int storage, int eddy, bool kin, const void* src, void* dst, int k,
                        const Geom& g, const Rates& r, double delta, hipStream_t s) {
-  const int most = kin || eddy == 2 ? 3 : 5;
-  if (k < 1 || k > most) return hipErrorInvalidValue;
+  if (k < 1 || k > tile_most(kin || eddy == 2, g)) return hipErrorInvalidValue;
   const float c12 = float(delta * delta / 12.0);
   if (storage == LBMHD_FP32)
     return launch_tile_s<LBMHD_FP32>(eddy, kin, src, dst, k, g, r, c12, s);
@@ -1828,7 +1841,7 @@ static double tile_size(const Geom& g) {
 // 1448^2 41.6 / 59.1, 2048 x 1024 42.7 / 38.5.
 int tile_steps(int storage, bool nb, const Geom& g) {
   const double limit = nb ? (storage == LBMHD_FP32 ? 1.0e6 : 2.0e6) : 4.0e6;
-  return tile_size(g) < limit ? (nb ? 3 : 5) : 0;
+  return tile_size(g) < limit ? tile_most(nb, g) : 0;
 }
 
 // One and two steps: kinetic closure 1024^2 45.7 / 45.1 for one; the plain

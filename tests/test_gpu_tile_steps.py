@@ -1,7 +1,7 @@
 """Several steps of a small lattice per launch (GPU), the automatic mode's tile kernel: equal
 to single steps bit for bit.
 
-A launch takes up to five steps (three with neighbour terms) of a tile in LDS from a region of
+A launch takes up to nine steps (three with neighbour terms) of a tile in LDS from a region of
 16 x 16, 32 x 32 or 32 x 28 sites.  The sizes take both regions and both sides of the line
 between them, one tile and several with ragged ends, lattices smaller than the region (whose
 sites are periodic images of each other) and the step counts every split (one launch, even and
@@ -39,7 +39,7 @@ def lattices(nx, ny, les, storage):
 @pytest.mark.parametrize("nx,ny", SIZES)
 def test_tiles_equal_single_steps(nx, ny, les, storage):
     one, tile = lattices(nx, ny, les, storage)
-    for n in (1, 2, 3, 4, 5, 6, 9, 11):
+    for n in (1, 2, 3, 4, 5, 6, 9, 11, 16):
         one.step(n)
         tile.step(n)
         assert one.step_count == tile.step_count
