@@ -791,7 +791,7 @@ template <int ST, bool LESF, bool LESA>
 __global__ __launch_bounds__(kT3Threads) void k_adj_step2(
     const typename Codec<ST>::T* __restrict__ st, const float* __restrict__ lam_next,
     float* __restrict__ lam_prev, double* __restrict__ acc, Geom geo, Geom ga, Rates rt,
-    AdjConsts ac, int tiles_x, int rows, int nslots) {
+    AdjConsts ac, int tiles_x, int rows, bool xcd_map, int nslots) {
   // the forward recompute runs on the stored values as the forward step
   // does (FP16: in units of 2^-10); the reverse steps see deviations
   constexpr int SF = ST == LBMHD_FP32 ? LBMHD_FP32 : kFP16S;
@@ -802,8 +802,17 @@ __global__ __launch_bounds__(kT3Threads) void k_adj_step2(
   __shared__ double red[2][kT3Threads];
   const int nx = geo.nx, ny = geo.ny;
   const long long P = geo.plane, PA = ga.plane;
-  const int tile = int(blockIdx.x) % tiles_x, strip = int(blockIdx.x) / tiles_x;
+  int tile, strip;
+  if (xcd_map) {   // whole strips per XCD, as in the forward kernels
+    const int k = int(blockIdx.x) >> 3;
+    strip = (int(blockIdx.x) & 7) + 8 * (k / tiles_x);
+    tile = k % tiles_x;
+  } else {
+    tile = int(blockIdx.x) % tiles_x;
+    strip = int(blockIdx.x) / tiles_x;
+  }
   const int x0 = tile * kT3Cols, y0 = strip * rows;
+  if (y0 >= ny) return;
   const int wt = min(kT3Cols, nx - x0), h = min(rows, ny - y0);
   // the thread's column: its own (threads 0 .. kT3Cols - 1) or a halo column
   // (lanes 0 .. 3 of the fifth wave: x0 - 2, x0 - 1, x0 + wt, x0 + wt + 1)
@@ -1016,8 +1025,9 @@ __global__ __launch_bounds__(kT3Threads) void k_adj_step2(
       __syncthreads();
     }
     if (tid == 0) {
-      acc[blockIdx.x] += red[0][0];
-      acc[nslots + blockIdx.x] += red[1][0];
+      const int slot = strip * tiles_x + tile;
+      acc[slot] += red[0][0];
+      acc[nslots + slot] += red[1][0];
     }
   }
 }
@@ -1058,23 +1068,20 @@ hipError_t launch_adj_step(int storage, bool les, const void* state, const float
 // Strip height of the two-reverse-step kernel (halo overhead 4 / rows): as
 // for the forward three-step kernel, about 512 blocks up to 128-row strips,
 // 32-row strips beyond.
-static int adj_step2_rows(const Geom& g) {
-  const long long tiles_x = (g.nx + kT3Cols - 1) / kT3Cols;
-  const long long rows = tiles_x * g.ny / 512;
-  return int(rows < 8 ? 8 : (rows > 128 ? 32 : rows));
+static Strips adj_step2_strips(const Geom& g) {
+  return split_rows((g.nx + kT3Cols - 1) / kT3Cols, g.ny, 512, 8, 128, 32);
 }
 
 template <int ST, bool LESF, bool LESA>
 void launch_adj_step2_t(const void* state, const float* lam_next, float* lam_prev, double* acc,
                         const Geom& g, const Geom& ga, const Rates& r, const AdjConsts& ac,
                         hipStream_t s) {
-  const int rows = adj_step2_rows(g);
+  const auto [rows, strips, xcd_map] = adj_step2_strips(g);
   const int tiles_x = (g.nx + kT3Cols - 1) / kT3Cols;
-  const int strips = (g.ny + rows - 1) / rows;
   const dim3 grid(unsigned(tiles_x) * unsigned(strips)), block(kT3Threads);
   hipLaunchKernelGGL((k_adj_step2<ST, LESF, LESA>), grid, block, 0, s,
                      static_cast<const typename Codec<ST>::T*>(state), lam_next, lam_prev, acc, g,
-                     ga, r, ac, tiles_x, rows, adj_step_blocks(g));
+                     ga, r, ac, tiles_x, rows, xcd_map, adj_step_blocks(g));
 }
 
 hipError_t launch_adj_step2(int storage, bool les_fwd, bool les, const void* state,

@@ -49,6 +49,39 @@ struct Rates {
   float qclip;    // q_b below which the root lies under max(sqrt(1/2), sqrt(tau_m0/3))
 };
 
+// The strips of rows of a row-walking kernel: `rows` rows each, `grid` strips
+// launched (with xcd the count rounded up to a multiple of eight, so that each
+// XCD gets whole strips; a block past the last strip returns at once).
+struct Strips {
+  int rows, grid;
+  bool xcd;
+};
+
+// The strips of `rows` rows each, in the order by XCDs (which lets neighbouring
+// tiles share their edge lines in one L2) where at most `idle` in 64 of the
+// launched ones lie past the lattice.
+inline Strips strips_of(int rows, int ny, int idle = 8) {
+  const int n = (ny + rows - 1) / rows, pad = (n + 7) / 8 * 8;
+  const bool xcd = (pad - n) * 64 <= idle * pad;
+  return Strips{rows, xcd ? pad : n, xcd};
+}
+
+// About `want` blocks, never more while strips of `lo` rows allow it: a few
+// blocks over an even round leave some CUs a round of their own.  Strips
+// taller than `hi` become `big` rows (many rounds; there idle strips cost more
+// than the order by XCDs gives, 2% at 5990 x 3900).  ms per step, rows rounded down and plain order /
+// this rule: k_step_t3 1448^2 0.0326 / 0.0272, 2500^2 0.089 / 0.070,
+// 5000 x 3000 0.186 / 0.156; k_step_nb2 0.064 / 0.044, 0.166 / 0.110,
+// 0.345 / 0.242; k_adj_step2 0.086 / 0.065, 0.251 / 0.175, 0.530 / 0.409;
+// 2048^2 and 4096^2, which split evenly, as before.
+inline Strips split_rows(long long tiles_x, int ny, int want, int lo, int hi, int big) {
+  long long n = want / tiles_x;
+  n = n >= 8 ? n / 8 * 8 : (n > 1 ? n : 1);
+  const long long rows = (ny + n - 1) / n;
+  if (rows > hi) return strips_of(big, ny, 0);
+  return strips_of(int(rows < lo ? lo : rows), ny);
+}
+
 constexpr int kNPop = 19;
 constexpr int kDiagSlots = 16;   // doubles per diagnostics partial
 constexpr int kDiagBlocks = 4096; // partials in the workspace (one per reducing block)

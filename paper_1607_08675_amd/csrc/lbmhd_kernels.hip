@@ -89,9 +89,10 @@ __global__ __launch_bounds__(kT2Threads) void k_step2(
   __shared__ T lds[kT2Slots][W + 2];   // LDS column s holds local column s - 1
   const int nx = geo.nx, ny = geo.ny;
   const long long P = geo.plane;
-  // blocks go round-robin to the eight XCDs: with xcd_map (strips % 8 == 0)
-  // each XCD gets whole strips, so that the halo lines that neighbouring
-  // tiles share meet in one L2
+  // blocks go round-robin to the eight XCDs: with xcd_map (a multiple of eight
+  // strips launched, the last ones possibly past the lattice) each XCD gets
+  // whole strips, so that the halo lines that neighbouring tiles share meet in
+  // one L2
   int tile, strip;
   if (xcd_map) {
     const int k = int(blockIdx.x) >> 3;
@@ -103,6 +104,7 @@ __global__ __launch_bounds__(kT2Threads) void k_step2(
   }
   const int x0 = tile * W;
   const int y0 = strip * rows;
+  if (y0 >= ny) return;
   const int wt = min(W, nx - x0);          // columns of this tile
   const int h = min(rows, ny - y0);        // output rows of this strip
   const int lc = int(threadIdx.x) * V;     // first local column of the thread
@@ -256,6 +258,7 @@ __global__ __launch_bounds__(kT3Threads) void k_step_t3(const float* __restrict_
     strip = int(blockIdx.x) / tiles_x;
   }
   const int x0 = tile * kT3Cols, y0 = strip * rows;
+  if (y0 >= ny) return;
   const int wt = min(kT3Cols, nx - x0), h = min(rows, ny - y0);
   // the thread's column: its own (threads 0 .. kT3Cols - 1) or a halo column
   // (lanes 0 .. 3 of the fifth wave: x0 - 2, x0 - 1, x0 + wt, x0 + wt + 1)
@@ -640,6 +643,7 @@ __global__ __launch_bounds__(kNb2Threads) __attribute__((amdgpu_waves_per_eu(4))
     strip = int(blockIdx.x) / tiles_x;
   }
   const int x0 = tile * W, y0 = strip * rows;
+  if (y0 >= ny) return;
   const int wt = min(W, nx - x0), h = min(rows, ny - y0);
   // the thread's column: its own (threads 0 .. W - 1) or a halo column
   // (lanes 0 .. 5 of the fifth wave: x0 - 3 .. x0 - 1, x0 + wt .. x0 + wt + 2)
@@ -1550,26 +1554,23 @@ void launch_step_v(bool les, const void* src, void* dst, const Geom& g, const Ra
     hipLaunchKernelGGL((k_step<ST, V, false>), grid, block, 0, s, a, b, g, r, tiles_x);
 }
 
-// Strip height of the two-step kernel, measured on MI355X: FP32 runs best
-// with about 512 blocks (2048^2: 32 rows, 4096^2: 128), FP16 with about 4096
-// (8192^2: 32 rows, 4096^2 and 2048^2: 8); halo overhead 2 / rows.
-static int step2_rows(const Geom& g, int storage, int V) {
+// Strips of the two-step kernel, measured on MI355X: FP32 runs best with about
+// 512 blocks (2048^2: 32 rows, 4096^2: 128), FP16 with about 4096 (8192^2: 32
+// rows, 4096^2 and 2048^2: 8); halo overhead 2 / rows.
+static Strips step2_strips(const Geom& g, int storage, int V) {
   const bool fp16 = storage != LBMHD_FP32;   // LBMHD_FP16 or its scaled tag
   const long long tiles_x = (g.nx + kT2Threads * V - 1) / (kT2Threads * V);
-  const long long rows = tiles_x * g.ny / (fp16 ? 4096 : 512);
-  const long long hi = fp16 ? 32 : 128;
-  return int(rows < 8 ? 8 : (rows > hi ? hi : rows));
+  const int hi = fp16 ? 32 : 128;
+  return split_rows(tiles_x, g.ny, fp16 ? 4096 : 512, 8, hi, hi);
 }
 
 template <int ST, int V>
 void launch_step2_v(bool les, const void* src, void* dst, void* mid, const Geom& g,
                     const Rates& r, hipStream_t s) {
   using T = typename Codec<ST>::T;
-  const int rows = step2_rows(g, ST, V);
+  const auto [rows, strips, xcd_map] = step2_strips(g, ST, V);
   const int tiles_x = (g.nx + kT2Threads * V - 1) / (kT2Threads * V);
-  const int strips = (g.ny + rows - 1) / rows;
   const dim3 grid(unsigned(tiles_x) * unsigned(strips)), block(kT2Threads);
-  const bool xcd_map = strips % 8 == 0;
   auto* a = static_cast<const T*>(src);
   auto* b = static_cast<T*>(dst);
   auto* m = static_cast<T*>(mid);
@@ -1617,21 +1618,17 @@ hipError_t launch_step_nb_s(int eddy, bool kin, const void* src, void* dst, cons
 // Strip height of the two-step kernel with lattice gradients (halo overhead
 // 6 / rows): as for the three-step kernel, about 512 blocks up to 128-row
 // strips, 32-row strips beyond.
-static int step_nb2_rows(const Geom& g) {
-  const long long tiles_x = (g.nx + kNb2Cols - 1) / kNb2Cols;
-  const long long rows = tiles_x * g.ny / 512;
-  return int(rows < 8 ? 8 : (rows > 128 ? 32 : rows));
+static Strips step_nb2_strips(const Geom& g) {
+  return split_rows((g.nx + kNb2Cols - 1) / kNb2Cols, g.ny, 512, 8, 128, 32);
 }
 
 template <int ST, int EDDY, bool KIN>
 void launch_step_nb2_t(const void* src, void* dst, void* mid, const Geom& g, const Rates& r,
                        float c12, hipStream_t s) {
   using T = typename Codec<ST>::T;
-  const int rows = step_nb2_rows(g);
+  const auto [rows, strips, xcd_map] = step_nb2_strips(g);
   const int tiles_x = (g.nx + kNb2Cols - 1) / kNb2Cols;
-  const int strips = (g.ny + rows - 1) / rows;
   const dim3 grid(unsigned(tiles_x) * unsigned(strips)), block(kNb2Threads);
-  const bool xcd_map = strips % 8 == 0;
   auto* a = static_cast<const T*>(src);
   auto* b = static_cast<T*>(dst);
   auto* m = static_cast<T*>(mid);
@@ -1702,19 +1699,15 @@ bool step2_pays(int storage, const Geom& g) {
 // to 128-row strips (2048^2: 32 rows, 4096^2: 128; 64-row strips there, 1024
 // blocks, were slower); on larger lattices 32-row strips (8192^2: 16-row
 // strips as fast, 64 and 8 rows 3% and 8% slower).
-static int step_t3_rows(const Geom& g) {
-  const long long tiles_x = (g.nx + kT3Cols - 1) / kT3Cols;
-  const long long rows = tiles_x * g.ny / 512;
-  return int(rows < 8 ? 8 : (rows > 128 ? 32 : rows));
+static Strips step_t3_strips(const Geom& g) {
+  return split_rows((g.nx + kT3Cols - 1) / kT3Cols, g.ny, 512, 8, 128, 32);
 }
 
 hipError_t launch_step_t3(bool les, const void* src, void* dst, void* mid1, void* mid2,
                           const Geom& g, const Rates& r, hipStream_t s) {
-  const int rows = step_t3_rows(g);
+  const auto [rows, strips, xcd_map] = step_t3_strips(g);
   const int tiles_x = (g.nx + kT3Cols - 1) / kT3Cols;
-  const int strips = (g.ny + rows - 1) / rows;
   const dim3 grid(unsigned(tiles_x) * unsigned(strips)), block(kT3Threads);
-  const bool xcd_map = strips % 8 == 0;
   auto* a = static_cast<const float*>(src);
   auto* b = static_cast<float*>(dst);
   auto* m1 = static_cast<float*>(mid1);
