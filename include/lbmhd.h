@@ -119,7 +119,12 @@ typedef struct {
                              (those read the neighbours' populations).  Calls
                              that read the state, or take a state argument
                              that is the bound lattice itself, first return
-                             a reversed lattice to the natural layout. */
+                             a reversed lattice to the natural layout.  With
+                             FP32 storage, steps_per_pass = 0 and three million
+                             sites or more, two and three steps go in one pass
+                             on the natural layout, with copies of the rows
+                             and columns around its tiles and strips in the
+                             workspace (8% of the lattice at 4096^2). */
   int32_t steps_per_pass; /* How many steps lbmhd_step takes per pass over
                              the lattice when two lattices are bound, the
                              intermediate states staying on chip.  Closures
@@ -184,7 +189,8 @@ int lbmhd_destroy(lbmhd_t* h);
 /* Byte sizes the caller must allocate in device memory:
  *   lattice    -- one encoded population lattice (two are bound, one in place);
  *   workspace  -- scratch used by diagnostics, energy and reductions (block
- *                 partials and results, the same at any lattice size);
+ *                 partials and results, the same at any lattice size; in
+ *                 place also the copies named above);
  *   adj_lattice -- one FP32 adjoint lattice (lambda), for the adjoint calls;
  *   adj_acc    -- the FP64 accumulator array of lbmhd_adj_step.
  * Any output pointer may be NULL. */

@@ -24,6 +24,7 @@ struct lbmhd {
   size_t lattice_bytes = 0, workspace_bytes = 0, adj_lattice_bytes = 0, adj_acc_bytes = 0;
   void* lat[2] = {nullptr, nullptr};
   double* ws = nullptr;
+  size_t halo_bytes = 0;   // in place: the halo copies at the workspace's end
   hipStream_t stream = nullptr;
   bool bound = false;
   int cur = 0;  // index of the lattice holding the current state
@@ -408,7 +409,9 @@ int lbmhd_create(const lbmhd_params* p, lbmhd_t** out) {
   r.qclip = float(ts * ts * ts - taum0 * ts);
   h->lattice_bytes = size_t(lbk::kNPop) * size_t(g.plane) * esize;
   h->adj_lattice_bytes = size_t(lbk::kNPop) * size_t(ga.plane) * 4;
-  h->workspace_bytes = round_up(workspace_doubles() * sizeof(double), kAlign);
+  if (p->inplace && p->steps_per_pass == 0 && p->storage == LBMHD_FP32)
+    h->halo_bytes = lbk::inplace_halo_bytes(g);
+  h->workspace_bytes = round_up(workspace_doubles() * sizeof(double), kAlign) + h->halo_bytes;
   h->adj_acc_bytes = round_up(2 * size_t(lbk::adj_step_blocks(g)) * sizeof(double), kAlign);
   *out = h;
   return LBMHD_OK;
@@ -504,9 +507,40 @@ int before_write(lbmhd_t* h, int i) {
   return e == hipSuccess ? LBMHD_OK : hip_fail(h, e, "diagnostics wait");
 }
 
+// One AA step of an in-place lattice.
+int inplace_one(lbmhd_t* h) {
+  hipError_t e = lbk::launch_step_aa(h->p.storage, eddy_of(h) == 1, h->reversed ? 1 : 0, h->lat[0],
+                                     h->geo, h->rates, h->stream);
+  if (e != hipSuccess) return hip_fail(h, e, "step launch");
+  h->reversed = !h->reversed;
+  ++h->step;
+  return LBMHD_OK;
+}
+
+// Steps of an in-place lattice by rows: an AA step first where the lattice is
+// reversed, then triples and pairs on the natural layout; a remainder of one
+// goes with the last triple as two pairs, a lone step is an AA step.
+int inplace_steps(lbmhd_t* h, int64_t n) {
+  if (n > 0 && h->reversed) {
+    if (int rc = inplace_one(h)) return rc;
+    --n;
+  }
+  void* halo = reinterpret_cast<char*>(h->ws) + (h->workspace_bytes - h->halo_bytes);
+  while (n > 1) {
+    const int k = n != 2 && n != 4 ? 3 : 2;
+    hipError_t e = lbk::launch_inplace_steps(eddy_of(h) == 1, k, h->lat[0], halo, h->geo, h->rates,
+                                             h->stream);
+    if (e != hipSuccess) return hip_fail(h, e, "step launch");
+    h->step += k;
+    n -= k;
+  }
+  return n == 1 ? inplace_one(h) : LBMHD_OK;
+}
+
 int lbmhd_step(lbmhd_t* h, int64_t nsteps) {
   if (int rc = need_bound(h)) return rc;
   if (nsteps < 0) return fail(h, LBMHD_ERR_INVALID_ARG, "negative step count");
+  if (h->halo_bytes > 0) return inplace_steps(h, nsteps);
   const bool les = (h->p.les & 1) && (h->p.cs > 0.0 || h->p.cs_b > 0.0);
   int64_t t = 0;
   const int ps = pass_steps(h);
@@ -551,17 +585,14 @@ int lbmhd_step(lbmhd_t* h, int64_t nsteps) {
     }
   }
   for (; t < nsteps; ++t) {
-    if (int rc = before_write(h, h->p.inplace ? 0 : 1 - h->cur)) return rc;
-    hipError_t e;
     if (h->p.inplace) {
-      e = lbk::launch_step_aa(h->p.storage, les, h->reversed ? 1 : 0, h->lat[0], h->geo,
-                              h->rates, h->stream);
-      h->reversed = !h->reversed;
-    } else {
-      e = launch_one_step(h, h->lat[h->cur], h->lat[1 - h->cur]);
-      h->cur = 1 - h->cur;
+      if (int rc = inplace_one(h)) return rc;
+      continue;
     }
+    if (int rc = before_write(h, 1 - h->cur)) return rc;
+    hipError_t e = launch_one_step(h, h->lat[h->cur], h->lat[1 - h->cur]);
     if (e != hipSuccess) return hip_fail(h, e, "step launch");
+    h->cur = 1 - h->cur;
     ++h->step;
   }
   return LBMHD_OK;

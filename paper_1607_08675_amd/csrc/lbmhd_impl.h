@@ -108,6 +108,15 @@ bool step2_pays(int storage, const Geom& g);
 hipError_t launch_step_aa(int storage, bool les, int phase, void* lat, const Geom& g,
                           const Rates& r, hipStream_t s);
 hipError_t launch_unswap_aa(int storage, void* lat, const Geom& g, hipStream_t s);
+// k = 3 or 2 steps on one FP32 lattice in its natural layout, in one pass over
+// it after the strips' and tiles' halos are copied to `halo`
+// (inplace_halo_bytes, 256-byte aligned); equal to k launch_step calls.
+hipError_t launch_inplace_steps(bool les, int k, void* lat, void* halo, const Geom& g,
+                                const Rates& r, hipStream_t s);
+// Whether launch_inplace_steps beats the AA steps on this lattice, and the
+// bytes of its halo copies (0 where it does not).
+bool inplace_rows_pay(const Geom& g);
+size_t inplace_halo_bytes(const Geom& g);
 // Forward step that needs the neighbours' rho, j, B (lattice gradients):
 // the kinetic closure (kin: filtered equilibria, filter width delta) and/or
 // the eddy closure `eddy` (0 none, 1 Smagorinsky, 2 cross-helicity).

@@ -50,6 +50,173 @@ __global__ __launch_bounds__(kStepThreads) void k_step(
   store_row<ST, V>(dst, geo.plane, row[1] + unsigned(x0), v);
 }
 
+// ---------------------------- several steps in place (FP32): saved halos
+// A row-walking block of the kernels below reads its own tile and strip and D
+// rows and columns around them (D: 3 for three steps, 2 for two).  When src
+// and dst are one lattice the blocks around it may already have written those,
+// so k_halo_save first copies, for every strip boundary, the D rows on either
+// side (rows: [boundary][plane][2 D][pitch]) and, for every tile boundary, the
+// D columns (cols: [boundary][ny][plane][8], column x0 - D + j at j), boundary
+// b being the lower or left edge of strip or tile b.  A block then takes what
+// lies outside its tile from the copies.  Inside, it walks upward and stores
+// row r only after the last pass that reads it.
+struct Halos {
+  const float* rows;
+  const float* cols;
+  int strips;   // strip boundaries
+};
+
+template <typename T, bool INP>
+struct Ptrs {
+  using Src = const T* __restrict__;
+  using Dst = T* __restrict__;
+};
+template <typename T>
+struct Ptrs<T, true> {   // one lattice: its loads and stores alias
+  using Src = const T*;
+  using Dst = T*;
+};
+template <typename T, bool INP>
+using SrcPtr = typename Ptrs<T, INP>::Src;
+template <typename T, bool INP>
+using DstPtr = typename Ptrs<T, INP>::Dst;
+
+// The source rows y = r - c_y of one gather of row r, indexed by c_y + 1: the
+// element offset in a plane of the lattice where the row lies in the strip
+// (bit c_y + 1 of `in`), else its place in the copied rows.
+struct HaloRows {
+  unsigned in;
+  unsigned off[3];
+  int row[3];   // rows of the copy before it, for plane 0
+  int y[3];
+};
+
+template <int D>
+__device__ __forceinline__ HaloRows halo_rows(int r, int y0, int h, int strip, int strips,
+                                              int pitch) {
+  HaloRows o;
+  o.in = 0;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const int y = r - (c - 1), k = y - y0;
+    o.in |= k >= 0 && k < h ? 1u << c : 0u;
+    o.y[c] = y;
+    o.off[c] = unsigned(y) * pitch;
+    const int b = k < 0 ? strip : (strip + 1 == strips ? 0 : strip + 1);
+    o.row[c] = b * kNPop * (2 * D) + (k < 0 ? D + k : D + k - h);
+  }
+  return o;
+}
+
+// Element of the copied columns at boundary b, row y, column j of plane 0 (the
+// planes follow eight elements apart).
+__device__ __forceinline__ unsigned halo_col(int b, int ny, int y, int j) {
+  return (unsigned(b) * unsigned(ny) + unsigned(y)) * unsigned(kNPop * 8) + unsigned(j);
+}
+
+// pre_q at column x of the tile, as gather_row, of the row in `hr`; lc: the
+// local column of wt, tile and next the tile's boundaries.
+template <int D>
+__device__ __forceinline__ void gather_tile(const float* lat, long long P, const Halos& hs,
+                                            const HaloRows& hr, int pitch, int ny, int tile,
+                                            int next, int lc, int wt, int x, int xl, int xr,
+                                            float (&v)[kNPop][1]) {
+  if (hr.in == 7u) {   // all three rows in the strip: nearly every pass
+    gather_row<LBMHD_FP32, 1>(lat, P, x, xl, xr, hr.off, v);
+  } else {
+    // (the empty asm keeps the addresses of these few passes out of the
+    // registers of the others)
+    long long p = P;
+    int step = 2 * D * pitch;
+    asm("" : "+s"(p), "+s"(step));
+#pragma unroll
+    for (int q = 0; q < kNPop; ++q) {
+      const int c = kPlaneCy[q] + 1;
+      const bool in = hr.in >> c & 1u;
+      const float* base =
+          in ? lat + q * p : hs.rows + ((long long)hr.row[c] * pitch + (long long)q * step);
+      const int xs = kPlaneCx[q] == 0 ? x : (kPlaneCx[q] == 1 ? xl : xr);
+      v[q][0] = ld_plane<float>(base, (in ? hr.off[c] : 0u) + unsigned(xs));
+    }
+  }
+  // the elements beyond the tile's edge columns, from the copied columns
+  // (a thread may be at both edges of a narrow last tile)
+  auto edge = [&](int cx, int b, int j) {
+    unsigned o[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) o[c] = halo_col(b, ny, hr.y[c], j);
+#pragma unroll
+    for (int q = 0; q < kNPop; ++q) {
+      const int c = kPlaneCy[q] + 1;
+      if (kPlaneCx[q] == cx && (hr.in >> c & 1u))
+        v[q][0] = ld_plane<float>(hs.cols, o[c] + unsigned(8 * q));
+    }
+  };
+  if (lc == 0) edge(1, tile, D - 1);
+  if (lc + 1 == wt) edge(-1, next, D);
+}
+
+// The same at a halo column: local column lc < 0 or >= wt, wrapped to x; b: the
+// tile boundary it lies at.
+template <int D>
+__device__ __forceinline__ void gather_halo(const Halos& hs, const HaloRows& hr, int pitch, int ny,
+                                            int b, int lc, int wt, int x, int xl, int xr,
+                                            float (&v)[kNPop][1]) {
+  unsigned o[3];
+#pragma unroll
+  for (int c = 0; c < 3; ++c)
+    o[c] = halo_col(b, ny, hr.y[c], D + (lc < 0 ? lc : lc - wt));
+  if (hr.in == 7u) {
+#pragma unroll
+    for (int q = 0; q < kNPop; ++q)
+      v[q][0] = ld_plane<float>(hs.cols, o[kPlaneCy[q] + 1] + unsigned(8 * q - kPlaneCx[q]));
+    return;
+  }
+  int step = 2 * D * pitch;
+  asm("" : "+s"(step));
+#pragma unroll
+  for (int q = 0; q < kNPop; ++q) {
+    const int c = kPlaneCy[q] + 1;
+    const int xs = kPlaneCx[q] == 0 ? x : (kPlaneCx[q] == 1 ? xl : xr);
+    if (hr.in >> c & 1u)
+      v[q][0] = ld_plane<float>(hs.cols, o[c] + unsigned(8 * q - kPlaneCx[q]));
+    else
+      v[q][0] = ld_plane<float>(hs.rows + ((long long)hr.row[c] * pitch + (long long)q * step),
+                                unsigned(xs));
+  }
+}
+
+// Copies the halos (see above): first the rows, one block a row of a plane,
+// then the columns, one block 32 rows at a tile boundary.
+__global__ __launch_bounds__(256) void k_halo_save(const float* __restrict__ lat,
+                                                   float* __restrict__ rows,
+                                                   float* __restrict__ cols, Geom g, int D,
+                                                   int strip_h, int strips, int tile_w,
+                                                   int col_blocks) {
+  const int nrow = strips * kNPop * 2 * D, tid = int(threadIdx.x);
+  int b = int(blockIdx.x);
+  if (b < nrow) {
+    const int k = b % (2 * D), q = (b / (2 * D)) % kNPop, s = b / (2 * D * kNPop);
+    int y = (s * strip_h - D + k) % g.ny;
+    y = y < 0 ? y + g.ny : y;
+    const uint4* a = reinterpret_cast<const uint4*>(lat + q * g.plane + (long long)y * g.pitch);
+    uint4* o = reinterpret_cast<uint4*>(rows + (long long)b * g.pitch);
+    for (int i = tid; i < g.pitch / 4; i += 256) o[i] = a[i];
+    return;
+  }
+  b -= nrow;
+  const int t = b / col_blocks, j = tid & 7, y = (b % col_blocks) * 32 + (tid >> 3);
+  int x = (t * tile_w - D + j) % g.nx;
+  x = x < 0 ? x + g.nx : x;
+  if (y >= g.ny || j >= 2 * D) return;
+  const unsigned a = unsigned(y) * unsigned(g.pitch) + unsigned(x), o = halo_col(t, g.ny, y, j);
+  float v[kNPop];
+#pragma unroll
+  for (int q = 0; q < kNPop; ++q) v[q] = ld_plane<float>(lat + q * g.plane, a);
+#pragma unroll
+  for (int q = 0; q < kNPop; ++q) cols[o + unsigned(8 * q)] = v[q];
+}
+
 // ------------------------------------------- two steps in one pass over HBM
 // dst = C(S(C(S(src)))) for the closures that read no neighbours (plain and
 // Smagorinsky-MHD): temporal blocking.  A block of kT2Threads threads owns a
@@ -78,11 +245,13 @@ constexpr int kT2Slots = 2 * kT2SlotsA + 6 * kT2SlotsB + 2 * kT2SlotsC;
 constexpr int kT2BaseB = 2 * kT2SlotsA, kT2BaseC = kT2BaseB + 6 * kT2SlotsB;
 // MID: also store the intermediate state (after the first update) to mid;
 // each block writes the rows and columns it owns, so every site once.
-template <int ST, int V, bool LES, bool MID>
+// INP: src and dst are one lattice, the halos as k_halo_save left them.
+template <int ST, int V, bool LES, bool MID, bool INP>
 __global__ __launch_bounds__(kT2Threads) void k_step2(
-    const typename Codec<ST>::T* __restrict__ src, typename Codec<ST>::T* __restrict__ dst,
+    SrcPtr<typename Codec<ST>::T, INP> src, DstPtr<typename Codec<ST>::T, INP> dst,
     typename Codec<ST>::T* __restrict__ mid, Geom geo, Rates rt, int tiles_x, int rows,
-    bool xcd_map) {
+    bool xcd_map, Halos halos) {
+  static_assert(!INP || (ST == LBMHD_FP32 && V == 1), "in place: FP32");
   using C = Codec<ST>;
   using T = typename C::T;
   constexpr int W = kT2Threads * V;
@@ -107,6 +276,7 @@ __global__ __launch_bounds__(kT2Threads) void k_step2(
   if (y0 >= ny) return;
   const int wt = min(W, nx - x0);          // columns of this tile
   const int h = min(rows, ny - y0);        // output rows of this strip
+  const int next = tile + 1 == tiles_x ? 0 : tile + 1;
   const int lc = int(threadIdx.x) * V;     // first local column of the thread
   const bool active = lc < wt;
   const int x = x0 + lc;
@@ -132,10 +302,17 @@ __global__ __launch_bounds__(kT2Threads) void k_step2(
     // first update of row y0 - 1 + t; c_x = 0 planes kept by c_y (nc: 0, nu: +1, nd: -1)
     float nc[3][V], nu[3][V], nd[3][V];
     unsigned row[3];
-    t2_rows(y0 - 1 + t, geo, row);
+    HaloRows hr;
+    if (INP)
+      hr = halo_rows<2>(y0 - 1 + t, y0, h, strip, halos.strips, geo.pitch);
+    else
+      t2_rows(y0 - 1 + t, geo, row);
     if (active) {
       float v[kNPop][V];
-      gather_row<ST, V>(src, P, x, xl, xr, row, v);
+      if constexpr (INP)
+        gather_tile<2>(src, P, halos, hr, geo.pitch, ny, tile, next, lc, wt, x, xl, xr, v);
+      else
+        gather_row<ST, V>(src, P, x, xl, xr, row, v);
       collide_sites<V, LES, ST == kFP16S>(v, rt);
       if (MID && t >= 1 && t <= h) store_row<ST, V>(mid, P, row[1] + unsigned(x), v);
 #pragma unroll
@@ -161,7 +338,11 @@ __global__ __launch_bounds__(kT2Threads) void k_step2(
     }
     if (halo) {
       float v[kNPop][1];
-      gather_row<ST, 1>(src, P, hx, hxl, hxr, row, v);
+      if constexpr (INP)
+        gather_halo<2>(halos, hr, geo.pitch, ny, threadIdx.x == 0 ? tile : next,
+                           threadIdx.x == 0 ? -1 : wt, wt, hx, hxl, hxr, v);
+      else
+        gather_row<ST, 1>(src, P, hx, hxl, hxr, row, v);
       collide_sites<1, LES, ST == kFP16S>(v, rt);
 #pragma unroll
       for (int q = 0; q < kNPop; ++q) {
@@ -237,13 +418,14 @@ __global__ __launch_bounds__(kT2Threads) void k_step2(
 // 4 / rows of the rows and 8 / kT3Cols of the columns.
 // MID: also store the states after the first and the second update to mid1
 // and mid2 (each block the rows and columns it owns, so every site once).
-template <bool LES, bool MID>
-__global__ __launch_bounds__(kT3Threads) void k_step_t3(const float* __restrict__ src,
-                                                        float* __restrict__ dst,
+// INP: as for k_step2.
+template <bool LES, bool MID, bool INP>
+__global__ __launch_bounds__(kT3Threads) void k_step_t3(SrcPtr<float, INP> src,
+                                                        DstPtr<float, INP> dst,
                                                         float* __restrict__ mid1,
                                                         float* __restrict__ mid2, Geom geo,
                                                         Rates rt, int tiles_x, int rows,
-                                                        bool xcd_map) {
+                                                        bool xcd_map, Halos hs) {
   __shared__ float l1[kT3Rows][kT3Cols + 4];   // first update: column lc + 2
   __shared__ float l2[kT3Rows][kT3Cols + 2];   // second update: column lc + 1
   const int nx = geo.nx, ny = geo.ny;
@@ -260,6 +442,7 @@ __global__ __launch_bounds__(kT3Threads) void k_step_t3(const float* __restrict_
   const int x0 = tile * kT3Cols, y0 = strip * rows;
   if (y0 >= ny) return;
   const int wt = min(kT3Cols, nx - x0), h = min(rows, ny - y0);
+  const int next = tile + 1 == tiles_x ? 0 : tile + 1;
   // the thread's column: its own (threads 0 .. kT3Cols - 1) or a halo column
   // (lanes 0 .. 3 of the fifth wave: x0 - 2, x0 - 1, x0 + wt, x0 + wt + 1)
   const int tid = int(threadIdx.x);
@@ -299,9 +482,19 @@ __global__ __launch_bounds__(kT3Threads) void k_step_t3(const float* __restrict_
     float n1c[3], n1u[3], n1d[3];
     if (has) {
       unsigned row[3];
-      t2_rows(y0 - 2 + t, geo, row);
       float v[kNPop][1];
-      gather_row<LBMHD_FP32, 1>(src, P, xc, xl, xr, row, v);
+      if constexpr (INP) {
+        const HaloRows hr = halo_rows<3>(y0 - 2 + t, y0, h, strip, hs.strips, geo.pitch);
+        if (tid < kT3Cols)
+          gather_tile<3>(src, P, hs, hr, geo.pitch, ny, tile, next, lc, wt, xc, xl, xr,
+                                        v);
+        else
+          gather_halo<3>(hs, hr, geo.pitch, ny, lc < 0 ? tile : next, lc, wt, xc, xl, xr,
+                                     v);
+      } else {
+        t2_rows(y0 - 2 + t, geo, row);
+        gather_row<LBMHD_FP32, 1>(src, P, xc, xl, xr, row, v);
+      }
       collide_sites<1, LES>(v, rt);
       if (MID && up3 && t >= 2 && t <= h + 1)
         store_row<LBMHD_FP32, 1>(mid1, P, row[1] + unsigned(xc), v);
@@ -1574,18 +1767,19 @@ void launch_step2_v(bool les, const void* src, void* dst, void* mid, const Geom&
   auto* a = static_cast<const T*>(src);
   auto* b = static_cast<T*>(dst);
   auto* m = static_cast<T*>(mid);
+  const Halos none{nullptr, nullptr, 0};
   if (les && m)
-    hipLaunchKernelGGL((k_step2<ST, V, true, true>), grid, block, 0, s, a, b, m, g, r, tiles_x,
-                       rows, xcd_map);
+    hipLaunchKernelGGL((k_step2<ST, V, true, true, false>), grid, block, 0, s, a, b, m, g, r,
+                       tiles_x, rows, xcd_map, none);
   else if (les)
-    hipLaunchKernelGGL((k_step2<ST, V, true, false>), grid, block, 0, s, a, b, m, g, r, tiles_x,
-                       rows, xcd_map);
+    hipLaunchKernelGGL((k_step2<ST, V, true, false, false>), grid, block, 0, s, a, b, m, g, r,
+                       tiles_x, rows, xcd_map, none);
   else if (m)
-    hipLaunchKernelGGL((k_step2<ST, V, false, true>), grid, block, 0, s, a, b, m, g, r, tiles_x,
-                       rows, xcd_map);
+    hipLaunchKernelGGL((k_step2<ST, V, false, true, false>), grid, block, 0, s, a, b, m, g, r,
+                       tiles_x, rows, xcd_map, none);
   else
-    hipLaunchKernelGGL((k_step2<ST, V, false, false>), grid, block, 0, s, a, b, m, g, r,
-                       tiles_x, rows, xcd_map);
+    hipLaunchKernelGGL((k_step2<ST, V, false, false, false>), grid, block, 0, s, a, b, m, g, r,
+                       tiles_x, rows, xcd_map, none);
 }
 
 template <int ST, int EDDY, bool KIN>
@@ -1712,18 +1906,19 @@ hipError_t launch_step_t3(bool les, const void* src, void* dst, void* mid1, void
   auto* b = static_cast<float*>(dst);
   auto* m1 = static_cast<float*>(mid1);
   auto* m2 = static_cast<float*>(mid2);
+  const Halos none{nullptr, nullptr, 0};
   if (m1 && les)
-    hipLaunchKernelGGL((k_step_t3<true, true>), grid, block, 0, s, a, b, m1, m2, g, r, tiles_x,
-                       rows, xcd_map);
+    hipLaunchKernelGGL((k_step_t3<true, true, false>), grid, block, 0, s, a, b, m1, m2, g, r,
+                       tiles_x, rows, xcd_map, none);
   else if (m1)
-    hipLaunchKernelGGL((k_step_t3<false, true>), grid, block, 0, s, a, b, m1, m2, g, r, tiles_x,
-                       rows, xcd_map);
+    hipLaunchKernelGGL((k_step_t3<false, true, false>), grid, block, 0, s, a, b, m1, m2, g, r,
+                       tiles_x, rows, xcd_map, none);
   else if (les)
-    hipLaunchKernelGGL((k_step_t3<true, false>), grid, block, 0, s, a, b, m1, m2, g, r, tiles_x,
-                       rows, xcd_map);
+    hipLaunchKernelGGL((k_step_t3<true, false, false>), grid, block, 0, s, a, b, m1, m2, g, r,
+                       tiles_x, rows, xcd_map, none);
   else
-    hipLaunchKernelGGL((k_step_t3<false, false>), grid, block, 0, s, a, b, m1, m2, g, r,
-                       tiles_x, rows, xcd_map);
+    hipLaunchKernelGGL((k_step_t3<false, false, false>), grid, block, 0, s, a, b, m1, m2, g, r,
+                       tiles_x, rows, xcd_map, none);
   return hipGetLastError();
 }
 
@@ -1841,6 +2036,67 @@ int tile_steps(int storage, bool nb, const Geom& g) {
 // kernels' pairs 724^2 11.9 / 15.1 FP32 and 10.1 / 18.3 FP16, 1024^2
 // 22.5 / 18.1 and 18.3 / 18.7.
 bool tile_short_pays(bool nb, const Geom& g) { return tile_size(g) < (nb ? 1.0e6 : 7.5e5); }
+
+// ------------------------------------------ several steps in place
+// Strips of 32 to 128 rows and tiles of 256 columns: the copies are
+// 6 / rows + 8 / 256 of the lattice (8% at 4096^2).
+static Strips halo_strips(const Geom& g) {
+  return split_rows((g.nx + kT2Threads - 1) / kT2Threads, g.ny, 512, 32, 128, 128);
+}
+
+// Against the AA steps, us per step: 2048 x 1024 46.3 / 46.3 by rows, 2048^2
+// 66.6 / 108.6, 4096^2 232 / 494 (k_step_t3 0.59 ms a launch, 0.50 on two
+// lattices, where no lane takes other addresses than its neighbours; the
+// copies 0.10), 8192 x 4096 576 / 1001.  FP16 pairs measured slower than the AA
+// steps (276 / 252 us at 4096^2: 32-row strips of two sites a thread, whose
+// halo sites wait for the copies, against 8-row strips on two lattices).  256
+// columns keep the copies' offsets within 32 bits on every lattice that
+// create accepts.
+bool inplace_rows_pay(const Geom& g) {
+  return g.nx >= kT2Threads && (long long)g.nx * g.ny >= 3000000;
+}
+
+// Elements of the saved rows (three a side, of which the pairs use two).
+static size_t halo_row_elems(const Geom& g) {
+  const int rows = halo_strips(g).rows;
+  return size_t((g.ny + rows - 1) / rows) * kNPop * 6 * g.pitch;
+}
+
+size_t inplace_halo_bytes(const Geom& g) {
+  if (!inplace_rows_pay(g)) return 0;
+  const size_t cols = size_t((g.nx + kT2Threads - 1) / kT2Threads) * kNPop * g.ny * 8;
+  return (halo_row_elems(g) + cols) * sizeof(float) / 256 * 256 + 256;
+}
+
+template <bool LES>
+static void launch_inplace_l(int k, float* lat, float* halo, const Geom& g, const Rates& r,
+                             hipStream_t s) {
+  const auto [rows, strips, xcd_map] = halo_strips(g);
+  const int tiles_x = (g.nx + kT2Threads - 1) / kT2Threads, n = (g.ny + rows - 1) / rows;
+  const int col_blocks = (g.ny + 31) / 32;
+  float* cols = halo + halo_row_elems(g);
+  hipLaunchKernelGGL(k_halo_save, dim3(n * kNPop * 2 * k + tiles_x * col_blocks), dim3(256), 0, s,
+                     lat, halo, cols, g, k, rows, n, kT2Threads, col_blocks);
+  const Halos hs{halo, cols, n};
+  const dim3 grid(unsigned(tiles_x) * unsigned(strips));
+  float* none = nullptr;
+  if (k == 3)
+    hipLaunchKernelGGL((k_step_t3<LES, false, true>), grid, dim3(kT3Threads), 0, s, lat, lat, none,
+                       none, g, r, tiles_x, rows, xcd_map, hs);
+  else
+    hipLaunchKernelGGL((k_step2<LBMHD_FP32, 1, LES, false, true>), grid, dim3(kT2Threads), 0, s,
+                       lat, lat, none, g, r, tiles_x, rows, xcd_map, hs);
+}
+
+hipError_t launch_inplace_steps(bool les, int k, void* lat, void* halo, const Geom& g,
+                                const Rates& r, hipStream_t s) {
+  if (k != 2 && k != 3) return hipErrorInvalidValue;
+  if (les)
+    launch_inplace_l<true>(k, static_cast<float*>(lat), static_cast<float*>(halo), g, r, s);
+  else
+    launch_inplace_l<false>(k, static_cast<float*>(lat), static_cast<float*>(halo), g, r, s);
+  return hipGetLastError();
+}
 
 template <int ST, int V, int PHASE>
 void launch_step_aa_v(bool les, void* lat, const Geom& g, const Rates& r, hipStream_t s) {

@@ -31,7 +31,8 @@ class LBMHDConfig:
     viscosity; cs_b: constant C_Sb of the eddy resistivity (None: same as cs);
     delta: filter width.
     storage: "fp32" or "fp16" (deviation from the rest state, FP16 scaled by 2^10).
-    inplace: one lattice updated in place (AA pattern) instead of two; not with
+    inplace: one lattice updated in place (AA pattern, or several steps per pass on
+    large FP32 lattices) instead of two; not with
     the closures that read neighbours (les = 2, 3, 4, 6).
     steps_per_pass: with two lattices, step() can advance several steps per
     pass over the lattice with the intermediate states kept on chip, equal to
