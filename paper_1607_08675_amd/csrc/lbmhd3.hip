@@ -178,10 +178,13 @@ template <typename T>
 __device__ __forceinline__ T ld(const T* __restrict__ base, unsigned off) {
   return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + off * unsigned(sizeof(T)));
 }
-template <typename T>
-__device__ __forceinline__ void st_nt(T* __restrict__ base, unsigned off, T v) {
-  __builtin_nontemporal_store(
-      v, reinterpret_cast<T*>(reinterpret_cast<char*>(base) + off * unsigned(sizeof(T))));
+template <bool NT, typename T>
+__device__ __forceinline__ void st(T* __restrict__ base, unsigned off, T v) {
+  T* p = reinterpret_cast<T*>(reinterpret_cast<char*>(base) + off * unsigned(sizeof(T)));
+  if (NT)
+    __builtin_nontemporal_store(v, p);
+  else
+    *p = v;
 }
 
 // One collision at one site.  d[27] = f - w (deviations), g[18] (x, y, z
@@ -306,16 +309,34 @@ __device__ __forceinline__ void collide3(float (&d)[kQ], float (&g)[18], const R
 }
 
 // Thread t of block b updates site x = (b mod tiles_x) * 256 + t of row
-// (y, z), b / tiles_x = z * ny + y.
-template <int ST, bool LES, bool MRT>
+// (y, z), b / tiles_x = z * ny + y; with LIN site b * 256 + t in the order
+// x, y, z, so that rows shorter than a block leave no lane idle.  NT:
+// non-temporal stores.  step3_order chooses.
+template <int ST, bool LES, bool MRT, bool LIN, bool NT>
 __global__ __launch_bounds__(kThreads) void k_step3(const typename Codec3<ST>::T* __restrict__ src,
                                                     typename Codec3<ST>::T* __restrict__ dst,
                                                     Geom3 g, Rates3 r, int tiles_x) {
   using C = Codec3<ST>;
-  const int x = (int(blockIdx.x) % tiles_x) * kThreads + int(threadIdx.x);
-  const int row = int(blockIdx.x) / tiles_x;
-  const int y = row % g.ny, z = row / g.ny;
-  if (x >= g.nx) return;
+  int x, y, z;
+  if constexpr (LIN) {
+    const unsigned s0 = blockIdx.x * unsigned(kThreads);
+    const unsigned row = s0 / unsigned(g.nx);
+    x = int(s0 - row * unsigned(g.nx)) + int(threadIdx.x);
+    z = int(row / unsigned(g.ny));
+    y = int(row) - z * g.ny;
+    for (; x >= g.nx; x -= g.nx)
+      if (++y == g.ny) {
+        y = 0;
+        ++z;
+      }
+    if (z >= g.nz) return;
+  } else {
+    x = (int(blockIdx.x) % tiles_x) * kThreads + int(threadIdx.x);
+    const int row = int(blockIdx.x) / tiles_x;
+    y = row % g.ny;
+    z = row / g.ny;
+    if (x >= g.nx) return;
+  }
   const int xs[3] = {x == g.nx - 1 ? 0 : x + 1, x, x == 0 ? g.nx - 1 : x - 1};   // x - c, c = -1, 0, 1
   const int ys[3] = {y == g.ny - 1 ? 0 : y + 1, y, y == 0 ? g.ny - 1 : y - 1};
   const int zs[3] = {z == g.nz - 1 ? 0 : z + 1, z, z == 0 ? g.nz - 1 : z - 1};
@@ -334,9 +355,9 @@ __global__ __launch_bounds__(kThreads) void k_step3(const typename Codec3<ST>::T
   collide3<LES, MRT>(d, gg, r);
   const unsigned o = (unsigned(z) * unsigned(g.ny) + unsigned(y)) * g.pitch + unsigned(x);
 #pragma unroll
-  for (int i = 0; i < kQ; ++i) st_nt(dst + i * g.plane, o, C::enc(d[i]));
+  for (int i = 0; i < kQ; ++i) st<NT>(dst + i * g.plane, o, C::enc(d[i]));
 #pragma unroll
-  for (int k = 0; k < 18; ++k) st_nt(dst + (kQ + k) * g.plane, o, C::enc(gg[k]));
+  for (int k = 0; k < 18; ++k) st<NT>(dst + (kQ + k) * g.plane, o, C::enc(gg[k]));
 }
 
 __device__ __forceinline__ long long site_index(const Geom3& g, long long s, unsigned* off) {
@@ -700,6 +721,26 @@ long long sites3(const lbmhd3_t* h) {
 unsigned blocks3(long long n) { return unsigned((n + 255) / 256); }
 // workspace: reduction partials, 16 results
 size_t ws_doubles3() { return size_t(lbk3::kReduceBlocks) * lbk3::kRed + 16; }
+// How the step kernel takes its sites and stores, by the bytes of the two
+// lattices.  Where they stay in the 256 MB last-level cache from step to step,
+// plain stores: they end there in whole lines, which the next step reads (us a
+// step, non-temporal / plain: 256 x 64 x 40 FP32 45 / 35, 90 x 60 x 70 29 / 24,
+// 96^3 FP16 47 / 41; 128^3 FP32 141 / 146, and 48 x 40 x 36 6.8 / 7.8, which the
+// L2s hold).  Sites in linear order where a row is no multiple of a block and
+// its rows end on cache lines (192^3 FP16 moment-space 290 / 263, 64 x 256 x 256
+// 196 / 158), and with FP16, bound by its arithmetic, wherever plain stores
+// are taken (96^3 57 / 39, 80 x 90 x 100 56 / 34); elsewhere its unaligned
+// stores cost more than the idle lanes (130^3 FP32 206 / 282).
+struct Order3 {
+  bool lin, nt;
+};
+Order3 step3_order(const lbk3::Geom3& g, int esize) {
+  const double bytes = 2.0 * lbk3::kNPop * esize * g.nx * g.ny * g.nz;
+  const bool plain = bytes >= 50e6 && bytes <= (esize == 4 ? 320e6 : 200e6);
+  const bool lin = g.nx % lbk3::kThreads != 0 && bytes >= 50e6 &&
+                   (g.nx * esize % 128 == 0 || (esize == 2 && plain));
+  return Order3{lin, !plain};
+}
 // rho, u (3 fields), B (3 fields) of the current state, FP64 device fields
 void launch_macro3(lbmhd3_t* h, double* rho, double* u, double* B) {
   const dim3 grid(blocks3(sites3(h)));
@@ -818,23 +859,34 @@ int lbmhd3_step(lbmhd3_t* h, int64_t nsteps) {
   if (int rc = need3(h)) return rc;
   if (nsteps < 0) return fail3(h, LBMHD_ERR_INVALID_ARG, "negative step count");
   const bool les = h->p.les && (h->p.cs > 0.0 || h->p.cs_b > 0.0);
+  const bool fp32 = h->p.storage == LBMHD_FP32, mrt = h->p.mrt != 0;
+  const Order3 order = step3_order(h->geo, fp32 ? 4 : 2);
   const int tiles_x = (h->geo.nx + lbk3::kThreads - 1) / lbk3::kThreads;
-  const dim3 grid(unsigned(tiles_x) * unsigned(h->geo.ny) * unsigned(h->geo.nz));
+  const dim3 grid(order.lin ? unsigned((sites3(h) + lbk3::kThreads - 1) / lbk3::kThreads)
+                      : unsigned(tiles_x) * unsigned(h->geo.ny) * unsigned(h->geo.nz));
   for (int64_t t = 0; t < nsteps; ++t) {
     const void* src = h->lat[h->cur];
     void* dst = h->lat[1 - h->cur];
     auto go = [&](auto st_tag, auto les_tag, auto mrt_tag) {
       constexpr int ST = decltype(st_tag)::value;
+      constexpr bool L = decltype(les_tag)::value, M = decltype(mrt_tag)::value;
       using T = typename lbk3::Codec3<ST>::T;
-      hipLaunchKernelGGL((lbk3::k_step3<ST, decltype(les_tag)::value, decltype(mrt_tag)::value>),
-                         grid, dim3(lbk3::kThreads), 0, h->stream, static_cast<const T*>(src),
-                         static_cast<T*>(dst), h->geo, h->rates, tiles_x);
+      auto launch = [&](auto lin_tag, auto nt_tag) {
+        hipLaunchKernelGGL((lbk3::k_step3<ST, L, M, decltype(lin_tag)::value,
+                                          decltype(nt_tag)::value>), grid, dim3(lbk3::kThreads), 0, h->stream, static_cast<const T*>(src),
+                           static_cast<T*>(dst), h->geo, h->rates, tiles_x);
+      };
+      using Y = std::true_type;
+      using N = std::false_type;
+      if (order.lin && order.nt) launch(Y{}, Y{});
+      else if (order.lin) launch(Y{}, N{});
+      else if (order.nt) launch(N{}, Y{});
+      else launch(N{}, N{});
     };
     using F32 = std::integral_constant<int, LBMHD_FP32>;
     using F16 = std::integral_constant<int, LBMHD_FP16>;
     using Y = std::true_type;
     using N = std::false_type;
-    const bool fp32 = h->p.storage == LBMHD_FP32, mrt = h->p.mrt != 0;
     if (fp32 && les && mrt) go(F32{}, Y{}, Y{});
     else if (fp32 && les) go(F32{}, Y{}, N{});
     else if (fp32 && mrt) go(F32{}, N{}, Y{});
