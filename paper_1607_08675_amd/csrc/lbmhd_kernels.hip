@@ -20,6 +20,9 @@
 // order (a remap giving each XCD a contiguous band of tiles measured slower).
 #include <math.h>
 
+#include <tuple>
+#include <type_traits>
+
 #include "lbmhd_impl.h"
 #include "lbmhd_step_dev.h"
 
@@ -30,7 +33,7 @@ namespace {
 // streaming written as a gather).  Thread t of block b updates sites
 // x0 .. x0 + V - 1 of row y, x0 = (b mod tiles_x) * 256 V + t V, y = b / tiles_x.
 // V > 1 requires nx % V == 0.
-template <int ST, int V, bool LES>
+template <int ST, int V, bool LES, bool NT>
 __global__ __launch_bounds__(kStepThreads) void k_step(
     const typename Codec<ST>::T* __restrict__ src, typename Codec<ST>::T* __restrict__ dst,
     Geom geo, Rates rt, int tiles_x) {
@@ -47,7 +50,7 @@ __global__ __launch_bounds__(kStepThreads) void k_step(
   float v[kNPop][V];
   gather_row<ST, V>(src, geo.plane, x0, xl, xr, row, v);
   collide_sites<V, LES, ST == kFP16S>(v, rt);
-  store_row<ST, V>(dst, geo.plane, row[1] + unsigned(x0), v);
+  store_row<ST, V, NT>(dst, geo.plane, row[1] + unsigned(x0), v);
 }
 
 // ---------------------------- several steps in place (FP32): saved halos
@@ -246,7 +249,7 @@ constexpr int kT2BaseB = 2 * kT2SlotsA, kT2BaseC = kT2BaseB + 6 * kT2SlotsB;
 // MID: also store the intermediate state (after the first update) to mid;
 // each block writes the rows and columns it owns, so every site once.
 // INP: src and dst are one lattice, the halos as k_halo_save left them.
-template <int ST, int V, bool LES, bool MID, bool INP>
+template <int ST, int V, bool LES, bool MID, bool INP, bool NT>
 __global__ __launch_bounds__(kT2Threads) void k_step2(
     SrcPtr<typename Codec<ST>::T, INP> src, DstPtr<typename Codec<ST>::T, INP> dst,
     typename Codec<ST>::T* __restrict__ mid, Geom geo, Rates rt, int tiles_x, int rows,
@@ -314,7 +317,7 @@ __global__ __launch_bounds__(kT2Threads) void k_step2(
       else
         gather_row<ST, V>(src, P, x, xl, xr, row, v);
       collide_sites<V, LES, ST == kFP16S>(v, rt);
-      if (MID && t >= 1 && t <= h) store_row<ST, V>(mid, P, row[1] + unsigned(x), v);
+      if (MID && t >= 1 && t <= h) store_row<ST, V, NT>(mid, P, row[1] + unsigned(x), v);
 #pragma unroll
       for (int q = 0; q < kNPop; ++q) {
 #pragma unroll
@@ -383,7 +386,7 @@ __global__ __launch_bounds__(kT2Threads) void k_step2(
         }
       }
       collide_sites<V, LES, ST == kFP16S>(v, rt);
-      store_row<ST, V>(dst, P, unsigned(y0 + t - 2) * geo.pitch + unsigned(x), v);
+      store_row<ST, V, NT>(dst, P, unsigned(y0 + t - 2) * geo.pitch + unsigned(x), v);
     }
 #pragma unroll
     for (int k = 0; k < 3; ++k)
@@ -419,7 +422,7 @@ __global__ __launch_bounds__(kT2Threads) void k_step2(
 // MID: also store the states after the first and the second update to mid1
 // and mid2 (each block the rows and columns it owns, so every site once).
 // INP: as for k_step2.
-template <bool LES, bool MID, bool INP>
+template <bool LES, bool MID, bool INP, bool NT>
 __global__ __launch_bounds__(kT3Threads) void k_step_t3(SrcPtr<float, INP> src,
                                                         DstPtr<float, INP> dst,
                                                         float* __restrict__ mid1,
@@ -497,7 +500,7 @@ __global__ __launch_bounds__(kT3Threads) void k_step_t3(SrcPtr<float, INP> src,
       }
       collide_sites<1, LES>(v, rt);
       if (MID && up3 && t >= 2 && t <= h + 1)
-        store_row<LBMHD_FP32, 1>(mid1, P, row[1] + unsigned(xc), v);
+        store_row<LBMHD_FP32, 1, NT>(mid1, P, row[1] + unsigned(xc), v);
 #pragma unroll
       for (int q = 0; q < kNPop; ++q) {
         const int k = kT2Reg[q];
@@ -540,7 +543,7 @@ __global__ __launch_bounds__(kT3Threads) void k_step_t3(SrcPtr<float, INP> src,
       if (do2) {
         collide_sites<1, LES>(v, rt);
         if (MID && up3 && t >= 3 && t <= h + 2)
-          store_row<LBMHD_FP32, 1>(mid2, P, unsigned(y0 - 3 + t) * geo.pitch + unsigned(xc), v);
+          store_row<LBMHD_FP32, 1, NT>(mid2, P, unsigned(y0 - 3 + t) * geo.pitch + unsigned(xc), v);
 #pragma unroll
         for (int q = 0; q < kNPop; ++q) {
           const int k = kT2Reg[q];
@@ -574,7 +577,7 @@ __global__ __launch_bounds__(kT3Threads) void k_step_t3(SrcPtr<float, INP> src,
             v[q][0] = kPlaneCy[q] == 0 ? z2c[k] : (kPlaneCy[q] == 1 ? z2u2[k] : n2d[k]);
         }
         collide_sites<1, LES>(v, rt);
-        store_row<LBMHD_FP32, 1>(dst, P, unsigned(y0 - 4 + t) * geo.pitch + unsigned(xc), v);
+        store_row<LBMHD_FP32, 1, NT>(dst, P, unsigned(y0 - 4 + t) * geo.pitch + unsigned(xc), v);
       }
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
@@ -812,7 +815,7 @@ constexpr int kNb2Threads = kNb2Cols + 64;
 // compiler's own choice the pass measured 1.2x slower for the kinetic and the
 // cross-helicity closure and 1.5x slower for both together (135 VGPRs), at
 // 4096^2, with bit-identical results.
-template <int ST, int EDDY, bool KIN, bool MID>
+template <int ST, int EDDY, bool KIN, bool MID, bool NT>
 __global__ __launch_bounds__(kNb2Threads) __attribute__((amdgpu_waves_per_eu(4))) void k_step_nb2(
     const typename Codec<ST>::T* __restrict__ src, typename Codec<ST>::T* __restrict__ dst,
     typename Codec<ST>::T* __restrict__ mid, Geom geo, Rates rt, float c12, int tiles_x,
@@ -930,7 +933,7 @@ __global__ __launch_bounds__(kNb2Threads) __attribute__((amdgpu_waves_per_eu(4))
       if (MID && lc >= 0 && lc < wt && r1 >= y0 && r1 < y0 + h) {
         const unsigned od = unsigned(r1) * geo.pitch + unsigned(xc);
 #pragma unroll
-        for (int q = 0; q < kNPop; ++q) st_plane_nt<T>(mid + q * P, od, C::enc(v[q]));
+        for (int q = 0; q < kNPop; ++q) st_plane_as<NT, T>(mid + q * P, od, C::enc(v[q]));
       }
 #pragma unroll
       for (int q = 0; q < kNPop; ++q) {
@@ -991,9 +994,9 @@ __global__ __launch_bounds__(kNb2Threads) __attribute__((amdgpu_waves_per_eu(4))
       collide<EDDY, KIN>(f, g, rt, kc);
       const unsigned od = unsigned(y0 - 6 + t) * geo.pitch + unsigned(xc);
 #pragma unroll
-      for (int i = 0; i < 9; ++i) st_plane_nt<T>(dst + i * P, od, C::enc(f[i]));
+      for (int i = 0; i < 9; ++i) st_plane_as<NT, T>(dst + i * P, od, C::enc(f[i]));
 #pragma unroll
-      for (int k = 0; k < 10; ++k) st_plane_nt<T>(dst + (9 + k) * P, od, C::enc(g[k]));
+      for (int k = 0; k < 10; ++k) st_plane_as<NT, T>(dst + (9 + k) * P, od, C::enc(g[k]));
     }
 #pragma unroll
     for (int q = 0; q < kNPop; ++q) {
@@ -1733,6 +1736,35 @@ inline unsigned blocks_for(long long n, int bs) { return unsigned((n + bs - 1) /
 }  // namespace
 
 // ----------------------------------------------------------------- launchers
+// f(std::bool_constant<b>...) of run-time booleans.
+template <class F, class... Done>
+void with_bools(F&& f, std::tuple<Done...>) {
+  std::apply(f, std::tuple<Done...>{});
+}
+template <class F, class... Done, class... More>
+void with_bools(F&& f, std::tuple<Done...>, bool b, More... more) {
+  if (b)
+    with_bools(f, std::tuple<Done..., std::true_type>{}, more...);
+  else
+    with_bools(f, std::tuple<Done..., std::false_type>{}, more...);
+}
+template <class F, class... More>
+void with_bools(F&& f, bool b, More... more) {
+  with_bools(f, std::tuple<>{}, b, more...);
+}
+
+// Non-temporal stores, except where this lattice and the one it was read from
+// stay in the 256 MB last-level cache until the next pass: there plain stores
+// end as whole lines in it.  us per step, non-temporal / plain: k_step 1024^2
+// FP32 31 / 22, 2048 x 1024 FP16 34 / 22, k_step_t3 1280 x 1024 17.7 / 14.3, k_step2
+// 1024^2 18.2 / 14.1, k_step_nb2 23.7 / 21.8; beyond it (1448^2 FP32, 318 MB)
+// k_step_t3 26.8 / 27.8 and k_step_nb2 44.6 / 46.4, and in the L2s (512^2 FP16,
+// 20 MB) k_step 6.2 / 6.8.
+static bool stores_bypass(const Geom& g, size_t esize) {
+  const double bytes = 2.0 * kNPop * double(esize) * g.nx * g.ny;
+  return bytes < 30e6 || bytes > 240e6;
+}
+
 template <int ST, int V>
 void launch_step_v(bool les, const void* src, void* dst, const Geom& g, const Rates& r,
                    hipStream_t s) {
@@ -1741,10 +1773,9 @@ void launch_step_v(bool les, const void* src, void* dst, const Geom& g, const Ra
   const dim3 grid(unsigned(tiles_x) * unsigned(g.ny)), block(kStepThreads);
   auto* a = static_cast<const T*>(src);
   auto* b = static_cast<T*>(dst);
-  if (les)
-    hipLaunchKernelGGL((k_step<ST, V, true>), grid, block, 0, s, a, b, g, r, tiles_x);
-  else
-    hipLaunchKernelGGL((k_step<ST, V, false>), grid, block, 0, s, a, b, g, r, tiles_x);
+  with_bools([&](auto l, auto nt) {
+    hipLaunchKernelGGL((k_step<ST, V, l(), nt()>), grid, block, 0, s, a, b, g, r, tiles_x);
+  }, les, stores_bypass(g, sizeof(T)));
 }
 
 // Strips of the two-step kernel, measured on MI355X: FP32 runs best with about
@@ -1768,18 +1799,12 @@ void launch_step2_v(bool les, const void* src, void* dst, void* mid, const Geom&
   auto* b = static_cast<T*>(dst);
   auto* m = static_cast<T*>(mid);
   const Halos none{nullptr, nullptr, 0};
-  if (les && m)
-    hipLaunchKernelGGL((k_step2<ST, V, true, true, false>), grid, block, 0, s, a, b, m, g, r,
-                       tiles_x, rows, xcd_map, none);
-  else if (les)
-    hipLaunchKernelGGL((k_step2<ST, V, true, false, false>), grid, block, 0, s, a, b, m, g, r,
-                       tiles_x, rows, xcd_map, none);
-  else if (m)
-    hipLaunchKernelGGL((k_step2<ST, V, false, true, false>), grid, block, 0, s, a, b, m, g, r,
-                       tiles_x, rows, xcd_map, none);
-  else
-    hipLaunchKernelGGL((k_step2<ST, V, false, false, false>), grid, block, 0, s, a, b, m, g, r,
-                       tiles_x, rows, xcd_map, none);
+  const int h = rows;
+  const bool xcd = xcd_map;
+  with_bools([&](auto l, auto md, auto nt) {
+    hipLaunchKernelGGL((k_step2<ST, V, l(), md(), false, nt()>), grid, block, 0, s, a, b, m, g, r,
+                       tiles_x, h, xcd, none);
+  }, les, m != nullptr, stores_bypass(g, sizeof(T)));
 }
 
 template <int ST, int EDDY, bool KIN>
@@ -1826,12 +1851,12 @@ void launch_step_nb2_t(const void* src, void* dst, void* mid, const Geom& g, con
   auto* a = static_cast<const T*>(src);
   auto* b = static_cast<T*>(dst);
   auto* m = static_cast<T*>(mid);
-  if (m)
-    hipLaunchKernelGGL((k_step_nb2<ST, EDDY, KIN, true>), grid, block, 0, s, a, b, m, g, r, c12,
-                       tiles_x, rows, xcd_map);
-  else
-    hipLaunchKernelGGL((k_step_nb2<ST, EDDY, KIN, false>), grid, block, 0, s, a, b, m, g, r, c12,
-                       tiles_x, rows, xcd_map);
+  const int h = rows;
+  const bool xcd = xcd_map;
+  with_bools([&](auto md, auto nt) {
+    hipLaunchKernelGGL((k_step_nb2<ST, EDDY, KIN, md(), nt()>), grid, block, 0, s, a, b, m, g, r,
+                       c12, tiles_x, h, xcd);
+  }, m != nullptr, stores_bypass(g, sizeof(T)));
 }
 
 template <int ST>
@@ -1907,18 +1932,12 @@ hipError_t launch_step_t3(bool les, const void* src, void* dst, void* mid1, void
   auto* m1 = static_cast<float*>(mid1);
   auto* m2 = static_cast<float*>(mid2);
   const Halos none{nullptr, nullptr, 0};
-  if (m1 && les)
-    hipLaunchKernelGGL((k_step_t3<true, true, false>), grid, block, 0, s, a, b, m1, m2, g, r,
-                       tiles_x, rows, xcd_map, none);
-  else if (m1)
-    hipLaunchKernelGGL((k_step_t3<false, true, false>), grid, block, 0, s, a, b, m1, m2, g, r,
-                       tiles_x, rows, xcd_map, none);
-  else if (les)
-    hipLaunchKernelGGL((k_step_t3<true, false, false>), grid, block, 0, s, a, b, m1, m2, g, r,
-                       tiles_x, rows, xcd_map, none);
-  else
-    hipLaunchKernelGGL((k_step_t3<false, false, false>), grid, block, 0, s, a, b, m1, m2, g, r,
-                       tiles_x, rows, xcd_map, none);
+  const int h = rows;
+  const bool xcd = xcd_map;
+  with_bools([&](auto l, auto md, auto nt) {
+    hipLaunchKernelGGL((k_step_t3<l(), md(), false, nt()>), grid, block, 0, s, a, b, m1, m2, g, r,
+                       tiles_x, h, xcd, none);
+  }, les, m1 != nullptr, stores_bypass(g, 4));
   return hipGetLastError();
 }
 
@@ -2081,10 +2100,10 @@ static void launch_inplace_l(int k, float* lat, float* halo, const Geom& g, cons
   const dim3 grid(unsigned(tiles_x) * unsigned(strips));
   float* none = nullptr;
   if (k == 3)
-    hipLaunchKernelGGL((k_step_t3<LES, false, true>), grid, dim3(kT3Threads), 0, s, lat, lat, none,
+    hipLaunchKernelGGL((k_step_t3<LES, false, true, true>), grid, dim3(kT3Threads), 0, s, lat, lat, none,
                        none, g, r, tiles_x, rows, xcd_map, hs);
   else
-    hipLaunchKernelGGL((k_step2<LBMHD_FP32, 1, LES, false, true>), grid, dim3(kT2Threads), 0, s,
+    hipLaunchKernelGGL((k_step2<LBMHD_FP32, 1, LES, false, true, true>), grid, dim3(kT2Threads), 0, s,
                        lat, lat, none, g, r, tiles_x, rows, xcd_map, hs);
 }
 

@@ -107,6 +107,13 @@ template <typename VT, typename T>
 __device__ __forceinline__ void st_plane(T* __restrict__ base, unsigned off, VT v) {
   *reinterpret_cast<VT*>(reinterpret_cast<char*>(base) + off * unsigned(sizeof(T))) = v;
 }
+template <bool NT, typename VT, typename T>
+__device__ __forceinline__ void st_plane_as(T* __restrict__ base, unsigned off, VT v) {
+  if constexpr (NT)
+    st_plane_nt<VT>(base, off, v);
+  else
+    st_plane<VT>(base, off, v);
+}
 
 // velocity (c_x, c_y) of the population held by each of the 19 planes
 __device__ constexpr int kPlaneCx[kNPop] = {0, 1, 0, -1, 0, 1, -1, -1, 1, 0,
@@ -360,10 +367,7 @@ __device__ __forceinline__ void store_row(typename Codec<ST>::T* __restrict__ ds
 #pragma unroll
       for (int j = 0; j < V; ++j) w[j] = C::enc(v[q][j]);
     }
-    if constexpr (NT)
-      st_plane_nt<VT>(dst + q * P, off, w);
-    else
-      st_plane<VT>(dst + q * P, off, w);
+    st_plane_as<NT, VT>(dst + q * P, off, w);
   }
 }
 
