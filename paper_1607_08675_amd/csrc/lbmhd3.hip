@@ -719,8 +719,11 @@ long long sites3(const lbmhd3_t* h) {
   return (long long)h->geo.nx * h->geo.ny * h->geo.nz;
 }
 unsigned blocks3(long long n) { return unsigned((n + 255) / 256); }
-// workspace: reduction partials, 16 results
-size_t ws_doubles3() { return size_t(lbk3::kReduceBlocks) * lbk3::kRed + 16; }
+// workspace: reduction partials, 16 results; its size stays that of seven fields
+// of n doubles more, which callers may count on
+size_t ws_doubles3(long long n) {
+  return 7 * size_t(n) + size_t(lbk3::kReduceBlocks) * lbk3::kRed + 16;
+}
 // How the step kernel takes its sites and stores, by the bytes of the two
 // lattices.  Where they stay in the 256 MB last-level cache from step to step,
 // plain stores: they end there in whole lines, which the next step reads (us a
@@ -793,7 +796,9 @@ int lbmhd3_create(const lbmhd3_params* p, lbmhd3_t** out) {
                           float(36.0 * p->cs_b * d2), float(p->s5), float(p->s7),
                           float(p->s8), float(p->sg), float(p->szz)};
   h->lattice_bytes = size_t(lbk3::kNPop) * size_t(g.plane) * esize;
-  h->workspace_bytes = (ws_doubles3() * sizeof(double) + kAlign3 - 1) / kAlign3 * kAlign3;
+  h->workspace_bytes =
+      (ws_doubles3((long long)p->nx * p->ny * p->nz) * sizeof(double) + kAlign3 - 1) / kAlign3 *
+      kAlign3;
   *out = h;
   return LBMHD_OK;
 }
