@@ -233,18 +233,17 @@ int lbmhd_init_fields(lbmhd_t* h, const double* rho, const double* ux, const dou
  * the two bound lattices (or updating the one lattice in place).  Each kernel
  * launch fuses streaming and collision of one, two or three steps as
  * steps_per_pass selects (the same result, bit for bit); steps_per_pass = 0
- * takes up to nine (three for closures that read the neighbours' moments) in
- * tiles of the lattice held on chip, where the lattice is small enough for
- * that to be faster (below about 4 million sites, 1 million with neighbour
- * terms and FP32 storage, 2 million with FP16).  Asynchronous. */
+ * takes five (up to nine on small lattices; three or two for closures that
+ * read the neighbours' moments, below about 1.6 million sites with FP32
+ * storage) in tiles of the lattice held on chip, and a remainder that tiles
+ * do not speed up with those kernels.  Asynchronous. */
 int lbmhd_step(lbmhd_t* h, int64_t nsteps);
 
 /* Steps that one pass over the lattice covers when lbmhd_step advances a
  * multiple of that many steps on this handle: 3 or 2 where steps_per_pass
  * (and, for 0, the lattice size) selects the three- or two-step kernel for
- * this storage, closure and layout, else 1; the launches of up to nine steps
- * that 0 takes on smaller lattices (lbmhd_step) are not counted here.  Host
- * only.  Errors:
+ * this storage, closure and layout, else 1; the launches in tiles that 0 takes
+ * instead where they are faster (lbmhd_step) are not counted here.  Host only.  Errors:
  * LBMHD_ERR_INVALID_ARG for NULL arguments. */
 int lbmhd_steps_per_pass(const lbmhd_t* h, int32_t* out);
 

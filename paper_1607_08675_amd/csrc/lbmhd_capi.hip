@@ -55,17 +55,18 @@ int eddy_of(const lbmhd_t* h) {
 // cross-helicity closure's vorticity).
 bool reads_neighbours(const lbmhd_t* h) { return (h->p.les & 2) || eddy_of(h) == 2; }
 
-// The most steps of one launch of the tile kernel, 0 where it is not taken:
-// the automatic mode's kernel for small lattices (steps_per_pass asks for the
-// row-walking kernels by name).
+// The steps of one launch of the tile kernel, 0 where it is not taken: the
+// automatic mode's kernel (steps_per_pass asks for the row-walking kernels by
+// name).
 int tile_most(const lbmhd_t* h) {
   if (h->p.inplace || h->p.steps_per_pass != 0) return 0;
   return lbk::tile_steps(h->p.storage, reads_neighbours(h), h->geo);
 }
 
-// Whether launches of one to three steps go to the tile kernel as well.
-bool tile_short(const lbmhd_t* h) {
-  return tile_most(h) > 0 && lbk::tile_short_pays(reads_neighbours(h), h->geo);
+// Whether a launch of only k steps goes to the tile kernel as well.
+bool tile_short(const lbmhd_t* h, int k) {
+  return tile_most(h) > 0 &&
+         lbk::tile_short_pays(h->p.storage, reads_neighbours(h), k, h->geo);
 }
 
 hipError_t launch_tile_steps(const lbmhd_t* h, const void* src, void* dst, int k) {
@@ -76,7 +77,7 @@ hipError_t launch_tile_steps(const lbmhd_t* h, const void* src, void* dst, int k
 // One step src -> dst with the handle's closure.
 hipError_t launch_one_step(const lbmhd_t* h, const void* src, void* dst) {
   const int eddy = eddy_of(h);
-  if (reads_neighbours(h) && tile_short(h)) return launch_tile_steps(h, src, dst, 1);
+  if (reads_neighbours(h) && tile_short(h, 1)) return launch_tile_steps(h, src, dst, 1);
   if (reads_neighbours(h))
     return lbk::launch_step_nb(h->p.storage, eddy, (h->p.les & 2) != 0, src, dst, h->geo,
                                h->rates, h->p.delta, h->stream);
@@ -86,7 +87,7 @@ hipError_t launch_one_step(const lbmhd_t* h, const void* src, void* dst) {
 // Two steps src -> dst in one pass (mid: also the state between them).
 hipError_t launch_two_steps(const lbmhd_t* h, const void* src, void* dst, void* mid) {
   const int eddy = eddy_of(h);
-  if (!mid && tile_short(h)) return launch_tile_steps(h, src, dst, 2);
+  if (!mid && tile_short(h, 2)) return launch_tile_steps(h, src, dst, 2);
   if (reads_neighbours(h))
     return lbk::launch_step_nb2(h->p.storage, eddy, (h->p.les & 2) != 0, src, dst, mid, h->geo,
                                 h->rates, h->p.delta, h->stream);
@@ -545,15 +546,15 @@ int lbmhd_step(lbmhd_t* h, int64_t nsteps) {
   int64_t t = 0;
   const int ps = pass_steps(h);
   if (const int most = tile_most(h)) {
-    // as even launches as the count allows (9 = 5 + 4); where short launches
-    // do not pay, whole ones only, the remainder going by rows
-    const int64_t launches = (nsteps + most - 1) / most;
-    const bool all = tile_short(h) || (launches > 0 && nsteps / launches >= most - 1);
-    const int64_t m = all ? launches : nsteps / most;
-    for (int64_t i = 0; i < m; ++i) {
-      const int64_t left = all ? nsteps - t : (m - i) * most;
-      const int k = int((left + (m - i) - 1) / (m - i));
-      if (k == 1) break;   // a lone step: the single-step kernels below
+    // where launches of any count pay, as even ones as the count allows
+    // (9 = 5 + 4); else whole ones and then what still pays in tiles, the rest
+    // by rows (six plain steps are faster as two triples or as 4 + 2)
+    const bool even = tile_short(h, 2) && (most < 5 || tile_short(h, 3));
+    for (int64_t left = nsteps; left > 0; left = nsteps - t) {
+      const int64_t launches = (left + most - 1) / most;
+      int k = even ? int((left + launches - 1) / launches) : int(std::min<int64_t>(left, most));
+      if (!even && left == 6 && most == 5) k = h->p.storage == LBMHD_FP32 ? 3 : 4;
+      if (k < most && !tile_short(h, k)) break;
       if (int rc = before_write(h, 1 - h->cur)) return rc;
       hipError_t e = launch_tile_steps(h, h->lat[h->cur], h->lat[1 - h->cur], k);
       if (e != hipSuccess) return hip_fail(h, e, "step launch");
@@ -795,10 +796,12 @@ int lbmhd_run(lbmhd_t* h, int64_t nsteps, int64_t every, double* dev, lbmhd_diag
     return fail(h, LBMHD_ERR_INVALID_ARG, "diagnostics buffer overlaps the workspace");
   // an interval that lbmhd_step ends with a single step (FP32 storage, a
   // closure without neighbour terms) takes that step and the diagnostics of
-  // its result in one pass on the bound stream
-  const int ps = pass_steps(h);
+  // its result in one pass on the bound stream; so does every interval of a
+  // lattice so small that the launch saved counts for more than the step
+  const int ps = pass_steps(h), most = tile_most(h);
+  const bool tiny = (long long)h->p.nx * h->p.ny < 300000;
   const bool fuse = !h->p.inplace && h->p.storage == LBMHD_FP32 && !reads_neighbours(h) &&
-                    (ps == 1 || every % ps == 1 || tile_most(h) > 0);
+                    (most > 0 ? tiny || every % most == 1 : ps == 1 || every % ps == 1);
   if (!h->p.inplace && !fuse && !h->side) {
     hipError_t e = hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&h->ev_state, hipEventDisableTiming);

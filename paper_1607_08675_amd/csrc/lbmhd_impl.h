@@ -129,18 +129,18 @@ hipError_t launch_step_nb2(int storage, int eddy, bool kin, const void* src, voi
                            void* mid, const Geom& g, const Rates& r, double delta, hipStream_t s);
 // Whether launch_step_nb2 beats two launch_step_nb calls on this lattice.
 bool step_nb2_pays(const Geom& g);
-// k steps of a small lattice in one launch, tile by tile in LDS: dst = (C S)^k
-// src for any closure (eddy, kin as launch_step_nb; eddy 0 or 1 without kin
-// the plain and the Smagorinsky-MHD update), equal to k single steps bit for
-// bit.  1 <= k <= tile_steps.  src and dst do not overlap.
+// k steps in one launch, tile by tile in LDS: dst = (C S)^k src for any closure
+// (eddy, kin as launch_step_nb; eddy 0 or 1 without kin the plain and the
+// Smagorinsky-MHD update), equal to k single steps bit for bit.  k is at least
+// one and at most 5 (3 with neighbour terms), or what tile_steps gives.  src
+// and dst do not overlap.
 hipError_t launch_tile(int storage, int eddy, bool kin, const void* src, void* dst, int k,
                        const Geom& g, const Rates& r, double delta, hipStream_t s);
-// The most steps launch_tile takes (nb: closures with neighbour terms), or 0
-// where the lattice is large enough for the row-walking kernels.
+// The steps of one launch where tiles are the faster way (nb: closures with
+// neighbour terms), or 0 where the row-walking kernels are.
 int tile_steps(int storage, bool nb, const Geom& g);
-// Whether launch_tile is also the faster way to take only two or three steps
-// (one, with neighbour terms).
-bool tile_short_pays(bool nb, const Geom& g);
+// Where tile_steps is not 0: whether tiles are also faster for only k steps.
+bool tile_short_pays(int storage, bool nb, int k, const Geom& g);
 // Equilibrium initialisation from FP64 fields.
 hipError_t launch_init(int storage, const double* rho, const double* ux, const double* uy,
                        const double* bx, const double* by, void* lat, const Geom& g,

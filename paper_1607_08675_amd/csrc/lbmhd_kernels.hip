@@ -1028,10 +1028,11 @@ __global__ __launch_bounds__(kNb2Threads) __attribute__((amdgpu_waves_per_eu(4))
 // result equals k single steps bit for bit.  Plain stores: a tile's rows end
 // inside cache lines, which the L2 then completes (non-temporal stores
 // measured 5-15% slower from 512^2 on).
-template <int ST, int EDDY, bool KIN, int RX, int RY, int S>
+template <int ST, int EDDY, bool KIN, int RX, int RY, int S, int K>
 __global__ __launch_bounds__(RX* RY / S) void k_tile(
     const typename Codec<ST>::T* __restrict__ src, typename Codec<ST>::T* __restrict__ dst,
-    Geom geo, Rates rt, float c12, int k, int tiles_x, int tile_w, int tile_h) {
+    Geom geo, Rates rt, float c12, int steps, int tiles_x, int tile_w, int tile_h) {
+  const int k = K > 0 ? K : steps;
   using C = Codec<ST>;
   using T = typename C::T;
   constexpr bool NB = KIN || EDDY == 2;
@@ -1041,7 +1042,12 @@ __global__ __launch_bounds__(RX* RY / S) void k_tile(
   __shared__ float mo[NB ? NF : 1][NB ? N : 1];
   const int rx = int(threadIdx.x) % RX, ry0 = int(threadIdx.x) / RX;
   const int halo = NB ? 2 * k - 1 : k - 1;
-  const int x0 = (int(blockIdx.x) % tiles_x) * tile_w, y0 = (int(blockIdx.x) / tiles_x) * tile_h;
+  // blocks go round-robin to the eight XCDs: each takes a contiguous band of
+  // tiles, so that neighbours share halo lines and complete each other's store
+  // lines in one L2
+  const int tile = (int(blockIdx.x) & 7) * int(gridDim.x >> 3) + (int(blockIdx.x) >> 3);
+  const int x0 = (tile % tiles_x) * tile_w, y0 = (tile / tiles_x) * tile_h;
+  if (y0 >= geo.ny) return;
   const int wx = min(tile_w, geo.nx - x0), wy = min(tile_h, geo.ny - y0);
   int x = (x0 - halo + rx) % geo.nx;
   x = x < 0 ? x + geo.nx : x;
@@ -1055,7 +1061,7 @@ __global__ __launch_bounds__(RX* RY / S) void k_tile(
     t2_rows(y, geo, row);
     gather_row<ST, 1>(src, geo.plane, x, xl, xr, row, v[j]);
   }
-  for (int s = 1;; ++s) {
+  auto step = [&](int s) {
     // the update of step s takes the sites at least `in` sites inside the region
     const int in = NB ? 2 * s - 1 : s - 1;
     if constexpr (NB) {
@@ -1102,7 +1108,7 @@ __global__ __launch_bounds__(RX* RY / S) void k_tile(
         }
       }
     }
-    if (s == k) break;
+    if (s == k) return;
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < S; ++j) {
@@ -1116,6 +1122,12 @@ __global__ __launch_bounds__(RX* RY / S) void k_tile(
       }
     }
     if constexpr (!NB) __syncthreads();   // NB: the moments' barrier follows every read
+  };
+  if constexpr (K > 0) {
+#pragma unroll
+    for (int s = 1; s <= K; ++s) step(s);
+  } else {
+    for (int s = 1; s <= k; ++s) step(s);
   }
   if (rx >= halo && rx < halo + wx) {
 #pragma unroll
@@ -1955,13 +1967,11 @@ hipError_t launch_step2(int storage, bool les, const void* src, void* dst, void*
 // Regions of the tile kernel.  The smallest lattices need blocks, so 16 x 16
 // sites and up to five steps (tiles of 8 x 8; closures with neighbour terms
 // three steps, 6 x 6); from 200^2 on 32 x 32 (32 x 28 with FP32 neighbour
-// terms), two sites a thread and five (three) steps, which leaves two blocks
-// per CU in 64-75 KB of LDS each: taller regions with one block per CU, four
-// sites a thread or fewer steps were 10-40% slower at 512^2 to 1024^2.
-// us per step, single-step kernel / 16 x 16 / 32 x 32, FP32:
-// 64^2 2.7 / 1.15 / 1.9, 256^2 4.6 / 2.5 / 2.4, 512^2 9.7 / 5.7 / 4.5,
-// 1024^2 30 / 18 / 12; kinetic closure: 64^2 25 / 2.0 / 2.6,
-// 256^2 26 / 5.1 / 4.5, 512^2 32 / 14 / 8.6.
+// terms), two sites a thread: eight waves, two on each SIMD, and two blocks
+// per CU in 64-75 KB of LDS each.  Regions whose waves do not divide evenly
+// over the SIMDs (40 x 32, 32 x 36, 48 x 24) ran at 75k MLUPS at 4096^2 FP32
+// against 119k, one block per CU (64 x 32) at 89k, four sites a thread at 109k,
+// and blocks that stay for several tiles and gather the next one ahead at 85k.
 template <int ST, int EDDY, bool KIN>
 struct Tile {
   static constexpr bool kNb = KIN || EDDY == 2;
@@ -1976,7 +1986,7 @@ static bool tile_small(const Geom& g) { return (long long)g.nx * g.ny <= 40000; 
 static int tile_most(bool nb, const Geom& g) {
   if (nb) return 3;
   int k = 5;
-  if (!tile_small(g))
+  if (!tile_small(g) && (long long)g.nx * g.ny < 100000)
     for (; k < 9; ++k) {
       const int w = 32 - 2 * k;   // tile of k + 1 steps
       if ((long long)((g.nx + w - 1) / w) * ((g.ny + w - 1) / w) > 256) break;
@@ -1991,9 +2001,18 @@ static void launch_tile_r(const void* src, void* dst, int k, const Geom& g, cons
   const int halo = Tile<ST, EDDY, KIN>::kNb ? 2 * k - 1 : k - 1;
   const int w = RX - 2 * halo, h = RY - 2 * halo;
   const int tiles_x = (g.nx + w - 1) / w, tiles_y = (g.ny + h - 1) / h;
-  hipLaunchKernelGGL((k_tile<ST, EDDY, KIN, RX, RY, S>), dim3(tiles_x * tiles_y),
-                     dim3(RX * RY / S), 0, s, static_cast<const T*>(src), static_cast<T*>(dst), g,
-                     r, c12, k, tiles_x, w, h);
+  const dim3 grid((tiles_x * tiles_y + 7) / 8 * 8), block(RX * RY / S);
+  auto* a = static_cast<const T*>(src);
+  auto* b = static_cast<T*>(dst);
+  // the usual count of each kind is compiled for itself: unrolled, no value is
+  // moved between registers from step to step (FP16 10-17% faster)
+  constexpr int kFull = !Tile<ST, EDDY, KIN>::kNb ? 5 : (ST == LBMHD_FP32 || S == 1 ? 3 : 2);
+  if (k == kFull)
+    hipLaunchKernelGGL((k_tile<ST, EDDY, KIN, RX, RY, S, kFull>), grid, block, 0, s, a, b, g, r,
+                       c12, k, tiles_x, w, h);
+  else
+    hipLaunchKernelGGL((k_tile<ST, EDDY, KIN, RX, RY, S, 0>), grid, block, 0, s, a, b, g, r, c12,
+                       k, tiles_x, w, h);
 }
 
 template <int ST, int EDDY, bool KIN>
@@ -2040,21 +2059,29 @@ static double tile_size(const Geom& g) {
   return double(g.nx) * g.ny * (g.nx / cols);
 }
 
-// Where tiles stop paying, us per step in tiles / by rows (k_step_t3, k_step2
-// with FP16, k_step_nb2 or k_step_nb): FP32 1024^2 12.2 / 14.2,
-// 2048 x 1024 22.5 / 26.2, 2048^2 45.1 / 45.2; FP16 1024^2 12.4 / 16.9,
-// 2048 x 1024 21.9 / 24.1, 2048^2 41.9 / 45.6; kinetic closure FP32
-// 724^2 14.8 / 22.0, 3000 x 300 23.1 / 23.7, 1024^2 25.6 / 23.8, FP16
-// 1448^2 41.6 / 59.1, 2048 x 1024 42.7 / 38.5.
+// Which launches go to tiles, us per step in tiles / by rows.  Five steps
+// always: FP32 1024^2 10.2 / 11.7 (k_step_t3), 2048^2 38 / 45, 4096^2 147 / 167,
+// 8192 x 4096 298 / 373; FP16 1024^2 9.2 / 12.9 (k_step), 4096^2 124 / 151
+// (k_step2), 8192 x 4096 247 / 289.  Neighbour terms, FP32: three steps 724^2
+// 11.4 / 20.2 (k_step_nb2), 1300^2 34 / 40, 1448^2 45.1 / 44.5, 2048^2 89 / 73;
+// FP16: two steps 1024^2 17.9 / 35 (k_step_nb; three 19.3), 4096^2 237 / 268
+// (three 278).
 int tile_steps(int storage, bool nb, const Geom& g) {
-  const double limit = nb ? (storage == LBMHD_FP32 ? 1.0e6 : 2.0e6) : 4.0e6;
-  return tile_size(g) < limit ? tile_most(nb, g) : 0;
+  if (!nb) return tile_most(nb, g);
+  if (storage == LBMHD_FP16) return tile_size(g) < 4e5 ? 3 : 2;
+  return tile_size(g) < 1.6e6 ? 3 : 0;
 }
 
-// One and two steps: kinetic closure 1024^2 45.7 / 45.1 for one; the plain
-// kernels' pairs 724^2 11.9 / 15.1 FP32 and 10.1 / 18.3 FP16, 1024^2
-// 22.5 / 18.1 and 18.3 / 18.7.
-bool tile_short_pays(bool nb, const Geom& g) { return tile_size(g) < (nb ? 1.0e6 : 7.5e5); }
+// Fewer steps.  FP32: four 4096^2 171 / 234 (a triple and a single step), three
+// 1448^2 29.1 / 27.0 (k_step_t3), 4096^2 218 / 167, two 724^2 8.5 / 11.3 (k_step2),
+// 1024^2 14.3 / 14.2; FP16: three 4096^2 132 / 175, two 1448^2 16.6 / 25.3,
+// 2048^2 44.6 / 45.5, 4096^2 180 / 152; one with neighbour terms 1448^2
+// 79 / 95 FP32 and 36 / 60 FP16, 2048^2 170 / 132 and 94 / 78.
+bool tile_short_pays(int storage, bool nb, int k, const Geom& g) {
+  if (nb) return k > 1 || tile_size(g) < 2.2e6;
+  if (k >= (storage == LBMHD_FP32 ? 4 : 3)) return true;
+  return k > 1 && tile_size(g) < (storage == LBMHD_FP32 ? 1.04e6 : 4.0e6);
+}
 
 // ------------------------------------------ several steps in place
 // Strips of 32 to 128 rows and tiles of 256 columns: the copies are

@@ -40,8 +40,8 @@ class LBMHDConfig:
     takes three per pass with FP32 storage and two with FP16 where the lattice
     is large enough for it to pay; 3: three with FP32, two with FP16; 2: two.
     les = 2, 3, 4, 6: 0 takes two with FP32 storage where the lattice is large
-    enough, 2 and 3 two.  1: one.  0 also takes up to nine steps per launch
-    (three for les = 2, 3, 4, 6) in tiles held on chip on smaller lattices.
+    enough, 2 and 3 two.  1: one.  With 0 most steps go five to a launch
+    (nine to two, by size and closure) in tiles held on chip instead.
     """
     nx: int
     ny: int

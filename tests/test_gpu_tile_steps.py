@@ -47,11 +47,12 @@ def test_tiles_equal_single_steps(nx, ny, les, storage):
 
 
 @pytest.mark.parametrize("nx,ny,les,storage", [
-    (1000, 1100, 1, "fp32"), (1400, 1300, 0, "fp16"), (900, 1000, 2, "fp32"),
+    (1000, 1100, 1, "fp32"), (2100, 1900, 1, "fp32"), (1400, 1300, 0, "fp16"),
+    (2100, 2000, 1, "fp16"), (900, 1000, 2, "fp32"), (2050, 1100, 2, "fp16"),
     (1100, 1200, 4, "fp16")])
 def test_tiles_equal_single_steps_mid_sizes(nx, ny, les, storage):
     one, tile = lattices(nx, ny, les, storage)
-    for n in (4, 7, 8):
+    for n in (1, 2, 3, 4, 6, 7, 13):
         one.step(n)
         tile.step(n)
         assert torch.equal(stored_words(one), stored_words(tile)), n
