@@ -551,6 +551,42 @@ __device__ __forceinline__ void add_moment_adjoints(const float (&m)[5], float (
   }
 }
 
+// (rho - 1, j_x, j_y, B_x, B_y) of gathered populations.
+__device__ __forceinline__ void kin_moments(const float (&p)[19], float (&m)[5]) {
+  m[0] = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7])) + p[8];
+  m[1] = (p[1] - p[3]) + (p[5] - p[7]) - (p[6] - p[8]);
+  m[2] = (p[2] - p[4]) + (p[5] - p[7]) + (p[6] - p[8]);
+  m[3] = (p[9] + p[10]) + (p[11] + p[12]) + p[13];
+  m[4] = (p[14] + p[15]) + (p[16] + p[17]) + p[18];
+}
+
+// Gradients of the moments, m(k, dx, dy) being moment k at offset (dx, dy).
+template <class M>
+__device__ __forceinline__ void kin_gradients(M&& m, float (&gx)[5], float (&gy)[5],
+                                              float (&v)[5]) {
+#pragma unroll
+  for (int k = 0; k < 5; ++k) {
+    const float e = m(k, 1, 0), w = m(k, -1, 0), nn = m(k, 0, 1), ss = m(k, 0, -1);
+    const float ne = m(k, 1, 1), nw = m(k, -1, 1), se = m(k, 1, -1), sw = m(k, -1, -1);
+    gx[k] = (1.0f / 3.0f) * (e - w) + (1.0f / 12.0f) * ((ne - nw) + (se - sw));
+    gy[k] = (1.0f / 3.0f) * (nn - ss) + (1.0f / 12.0f) * ((ne + nw) - (se + sw));
+    v[k] = m(k, 0, 0);
+  }
+}
+
+// Their transpose: the moments' adjoints from those of the gradients, b(k, dx,
+// dy) of d_x X_k and b(5 + k, dx, dy) of d_y X_k at offset (dx, dy).
+template <class B>
+__device__ __forceinline__ void kin_gradients_adjoint(B&& b, float (&eta)[5]) {
+#pragma unroll
+  for (int k = 0; k < 5; ++k)
+    eta[k] = (1.0f / 3.0f) * ((b(k, -1, 0) - b(k, 1, 0)) + (b(5 + k, 0, -1) - b(5 + k, 0, 1))) +
+             (1.0f / 12.0f) * ((b(k, -1, -1) + b(5 + k, -1, -1)) +
+                               (b(5 + k, 1, -1) - b(k, 1, -1)) +
+                               (b(k, -1, 1) - b(5 + k, -1, 1)) -
+                               (b(k, 1, 1) + b(5 + k, 1, 1)));
+}
+
 // Both parts in one walk.  A block owns a tile of kT3Cols columns and a strip
 // of `rows` rows: pass t gathers row y0 + t (its moments go to a 3-row LDS
 // ring with two halo columns on each side), applies part A to row
@@ -611,11 +647,10 @@ __global__ __launch_bounds__(kT3Threads) void k_adj_kin(
     }
   };
   auto moments = [&](const float (&p)[19], int slot) {
-    mac[slot][0][mc] = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7])) + p[8];
-    mac[slot][1][mc] = (p[1] - p[3]) + (p[5] - p[7]) - (p[6] - p[8]);
-    mac[slot][2][mc] = (p[2] - p[4]) + (p[5] - p[7]) + (p[6] - p[8]);
-    mac[slot][3][mc] = (p[9] + p[10]) + (p[11] + p[12]) + p[13];
-    mac[slot][4][mc] = (p[14] + p[15]) + (p[16] + p[17]) + p[18];
+    float m[5];
+    kin_moments(p, m);
+#pragma unroll
+    for (int k = 0; k < 5; ++k) mac[slot][k][mc] = m[k];
   };
   CsGrad dcs{0.0f, 0.0f};
   // With FP32 states the next pass's gather is issued right after the first
@@ -648,18 +683,10 @@ __global__ __launch_bounds__(kT3Threads) void k_adj_kin(
     // part A at row a
     float lf[9], lg[10];
     if (hasa) {
-      const int c = mc;
       float gx[5], gy[5], v[5];
-#pragma unroll
-      for (int k = 0; k < 5; ++k) {
-        const float e = mac[s0][k][c + 1], w = mac[s0][k][c - 1];
-        const float nn = mac[sp][k][c], ss = mac[sm][k][c];
-        const float ne = mac[sp][k][c + 1], nw = mac[sp][k][c - 1];
-        const float se = mac[sm][k][c + 1], sw = mac[sm][k][c - 1];
-        gx[k] = (1.0f / 3.0f) * (e - w) + (1.0f / 12.0f) * ((ne - nw) + (se - sw));
-        gy[k] = (1.0f / 3.0f) * (nn - ss) + (1.0f / 12.0f) * ((ne + nw) - (se + sw));
-        v[k] = mac[s0][k][c];
-      }
+      kin_gradients([&](int k, int dx, int dy) {
+        return mac[dy == 0 ? s0 : (dy > 0 ? sp : sm)][k][mc + dx];
+      }, gx, gy, v);
       const KinTerms kc = kin_terms(gx, gy, v, c12);
       // lam_{n+1} of this site's populations, kept at x + c_i
       int ya = a % ny;
@@ -701,18 +728,10 @@ __global__ __launch_bounds__(kT3Threads) void k_adj_kin(
     // in the slots of passes t - 2, t - 1, t
     if (own && t >= 2) {
       const int rm = (t - 2) % 3, r0 = (t - 1) % 3, rp = t % 3;
-      const int c = gc;
       float eta[5];
-#pragma unroll
-      for (int k = 0; k < 5; ++k) {
-        // d/d(d_x X_k) in plane k, d/d(d_y X_k) in plane 5 + k
-        eta[k] = (1.0f / 3.0f) * ((gbr[r0][k][c - 1] - gbr[r0][k][c + 1]) +
-                                  (gbr[rm][5 + k][c] - gbr[rp][5 + k][c])) +
-                 (1.0f / 12.0f) * ((gbr[rm][k][c - 1] + gbr[rm][5 + k][c - 1]) +
-                                   (gbr[rm][5 + k][c + 1] - gbr[rm][k][c + 1]) +
-                                   (gbr[rp][k][c - 1] - gbr[rp][5 + k][c - 1]) -
-                                   (gbr[rp][k][c + 1] + gbr[rp][5 + k][c + 1]));
-      }
+      kin_gradients_adjoint([&](int k, int dx, int dy) {
+        return gbr[dy == 0 ? r0 : (dy > 0 ? rp : rm)][k][gc + dx];
+      }, eta);
       add_moment_adjoints(eta, clf, clg);
       int yb = (a - 1) % ny;
       if (yb < 0) yb += ny;
@@ -751,6 +770,122 @@ __global__ __launch_bounds__(kT3Threads) void k_adj_kin(
       }
       acc[blockIdx.x] += sv;
       acc[nslots + blockIdx.x] += sb;
+    }
+  }
+}
+
+// The same reverse step on lattices whose strips are 8 rows high, by tiles: a
+// block owns (RX - 4) x 8 sites and takes a region two sites wider on each
+// side, one site a thread, so that its chain is one gather, two barriers and
+// one store where the walk above has twelve passes.  A strip's sums of the
+// closure-constant derivatives run down each column in FP32, as above (the
+// strips are the same), then over the columns in FP64; slot: the tile.
+template <int ST, bool LES, int RX>
+__global__ __launch_bounds__(RX * 12) void k_adj_kin_tile(
+    const typename Dec<ST>::T* __restrict__ st, const float* __restrict__ lam_next,
+    float* __restrict__ lam_prev, double* __restrict__ acc, Geom geo, Geom ga, Rates rt,
+    AdjConsts ac, float c12, int tiles_x, int nslots) {
+  using D = Dec<ST>;
+  constexpr int N = RX * 12, W = RX - 4, H = 8;
+  static_assert(W <= 64, "one wave adds the columns");
+  __shared__ float mac[5][N];    // moments, then the derivatives
+  __shared__ float gbr[10][N];   // gradient adjoints
+  const int nx = geo.nx, ny = geo.ny;
+  const long long P = geo.plane, PA = ga.plane;
+  const int tile = (int(blockIdx.x) & 7) * int(gridDim.x >> 3) + (int(blockIdx.x) >> 3);
+  const int x0 = (tile % tiles_x) * W, y0 = (tile / tiles_x) * H;
+  if (y0 >= ny) return;
+  const int wx = min(W, nx - x0), wy = min(H, ny - y0);
+  const int tid = int(threadIdx.x), rx = tid % RX, ry = tid / RX;
+  const bool a_on = rx >= 1 && rx < RX - 1 && ry >= 1 && ry < 11;
+  const bool own = rx >= 2 && rx < 2 + wx && ry >= 2 && ry < 2 + wy;
+  int x = (x0 - 2 + rx) % nx, y = (y0 - 2 + ry) % ny;
+  x = x < 0 ? x + nx : x;
+  y = y < 0 ? y + ny : y;
+  const int xm = x == 0 ? nx - 1 : x - 1, xp = x == nx - 1 ? 0 : x + 1;
+  unsigned row[3], ra[3];   // rows y + 1, y, y - 1
+  t2_rows(y, geo, row);
+  t2_rows(y, ga, ra);
+  float p[kNPop], lam[kNPop];
+#pragma unroll
+  for (int q = 0; q < kNPop; ++q) {
+    const int cx = kPlaneCx[q];
+    p[q] = D::dec(ld_elem(st + q * P, row[kPlaneCy[q] + 1] +
+                                          unsigned(cx == 0 ? x : (cx == 1 ? xm : xp))));
+  }
+  if (a_on) {
+#pragma unroll
+    for (int q = 0; q < kNPop; ++q) {
+      const int cx = kPlaneCx[q];
+      lam[q] = ld_elem(lam_next + q * PA, ra[1 - kPlaneCy[q]] +
+                                              unsigned(cx == 0 ? x : (cx == 1 ? xp : xm)));
+    }
+  }
+  float m[5];
+  kin_moments(p, m);
+#pragma unroll
+  for (int k = 0; k < 5; ++k) mac[k][tid] = m[k];
+  __syncthreads();
+  float lf[9], lg[10];
+  CsGrad d{0.0f, 0.0f};
+  if (a_on) {
+    float gx[5], gy[5], v[5];
+    kin_gradients([&](int k, int dx, int dy) { return mac[k][tid + dy * RX + dx]; }, gx, gy, v);
+    const KinTerms kc = kin_terms(gx, gy, v, c12);
+    float f[9], g[10];
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+      f[i] = p[i];
+      lf[i] = lam[i];
+    }
+#pragma unroll
+    for (int q = 0; q < 10; ++q) {
+      g[q] = p[9 + q];
+      lg[q] = lam[9 + q];
+    }
+    KinTerms kcb;
+    d = collide_adjoint<LES, true>(f, g, lf, lg, rt, ac, kc, &kcb);
+    float gxb[5], gyb[5], vb[5];
+    kin_terms_adjoint(gx, gy, v, c12, kcb, gxb, gyb, vb);
+    add_moment_adjoints(vb, lf, lg);
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+      gbr[k][tid] = gxb[k];
+      gbr[5 + k][tid] = gyb[k];
+    }
+  }
+  __syncthreads();
+  if (own) {
+    float eta[5];
+    kin_gradients_adjoint([&](int k, int dx, int dy) { return gbr[k][tid + dy * RX + dx]; }, eta);
+    add_moment_adjoints(eta, lf, lg);
+    const unsigned oc = unsigned(y) * ga.pitch + unsigned(x);
+#pragma unroll
+    for (int i = 0; i < 9; ++i) st_plane<float>(lam_prev + i * PA, oc, lf[i]);
+#pragma unroll
+    for (int q = 0; q < 10; ++q) st_plane<float>(lam_prev + (9 + q) * PA, oc, lg[q]);
+  }
+  if (LES) {
+    mac[0][tid] = d.v;   // the moments were last read before the second barrier
+    mac[1][tid] = d.b;
+    __syncthreads();
+    if (tid < 64) {
+      float sv = 0.0f, sb = 0.0f;
+      if (tid < wx)
+        for (int r = 0; r < wy; ++r) {
+          sv += mac[0][(r + 2) * RX + tid + 2];
+          sb += mac[1][(r + 2) * RX + tid + 2];
+        }
+      double dv = double(sv), db = double(sb);
+#pragma unroll
+      for (int w = 32; w > 0; w >>= 1) {
+        dv += __shfl_xor(dv, w);
+        db += __shfl_xor(db, w);
+      }
+      if (tid == 0) {
+        acc[tile] += dv;
+        acc[nslots + tile] += db;
+      }
     }
   }
 }
@@ -1032,6 +1167,159 @@ __global__ __launch_bounds__(kT3Threads) void k_adj_step2(
   }
 }
 
+// ------------------------------------- two reverse steps of a tile in LDS
+// The same pair of reverse steps, tile by tile: a block owns a tile of the
+// output and a region of RX x RY sites around it (two more on each side), one
+// site a thread.  A thread gathers x_t once and keeps it for the second
+// reverse step, where the row-walking kernel gathers it again.
+//   A. every site of the region: the forward collision of the gathered x_t, the
+//      post-collision values to the neighbours through LDS;
+//   B. one site in: reverse step t + 1 at the x_{t+1} read from LDS, with
+//      lam_{t+2} at x + c_i from HBM (loaded together with x_t), its result to
+//      the neighbours through the same LDS;
+//   C. two sites in, the tile: reverse step t, stored.
+// A walk's chain is a strip's passes, each a gather, a store and two barriers
+// apart from the next, 40 us a launch however small the lattice; a tile's is one
+// gather, three barriers and one store.  Blocks in bands per XCD, as in k_tile,
+// so that halo lines and the lines two tiles share are met in one L2; plain
+// stores (lam_t is read by the next launch: 29 us per step at 1024^2 FP32
+// against 37 non-temporal).  Bound at 1024^2 by the 19 x (2 + 1.5) gathers a
+// site (halo sites included), beyond by HBM, where the walk reads less.  The
+// closure-constant derivatives are summed in FP64 per block over the tile
+// (slot: the tile).
+template <int ST, bool LESF, bool LESA, int RX, int RY>
+__global__ __launch_bounds__(RX* RY) void k_adj_tile(
+    const typename Codec<ST>::T* __restrict__ st, const float* __restrict__ lam_next,
+    float* __restrict__ lam_prev, double* __restrict__ acc, Geom geo, Geom ga, Rates rt,
+    AdjConsts ac, int tiles_x, int nslots) {
+  constexpr int SF = ST == LBMHD_FP32 ? LBMHD_FP32 : kFP16S;   // as in k_adj_step2
+  using CF = Codec<SF>;
+  using CA = Codec<ST>;
+  constexpr int N = RX * RY, W = RX - 4, H = RY - 4;
+  __shared__ float l[16][N];   // moving planes: x_{t+1}, then lam_{t+1}
+  const int nx = geo.nx, ny = geo.ny;
+  const long long P = geo.plane, PA = ga.plane;
+  const int tile = (int(blockIdx.x) & 7) * int(gridDim.x >> 3) + (int(blockIdx.x) >> 3);
+  const int x0 = (tile % tiles_x) * W, y0 = (tile / tiles_x) * H;
+  if (y0 >= ny) return;
+  const int wx = min(W, nx - x0), wy = min(H, ny - y0);
+  const int tid = int(threadIdx.x), rx = tid % RX, ry = tid / RX;
+  const bool b_on = rx >= 1 && rx < RX - 1 && ry >= 1 && ry < RY - 1;
+  const bool own = rx >= 2 && rx < 2 + wx && ry >= 2 && ry < 2 + wy;
+  int x = (x0 - 2 + rx) % nx, y = (y0 - 2 + ry) % ny;
+  x = x < 0 ? x + nx : x;
+  y = y < 0 ? y + ny : y;
+  const int xl = x == 0 ? nx - 1 : x - 1, xr = x == nx - 1 ? 0 : x + 1;
+  unsigned row[3], ra[3];
+  t2_rows(y, geo, row);
+  t2_rows(y, ga, ra);
+  float p[kNPop][1], lam[kNPop];
+  gather_row<SF, 1>(st, P, x, xl, xr, row, p);
+  if (b_on) {
+    // lam_{t+2} at x + c_i: row y + c_y is ra[1 - c_y]
+#pragma unroll
+    for (int q = 0; q < kNPop; ++q) {
+      const int cx = kPlaneCx[q];
+      lam[q] = ld_plane<float>(lam_next + q * PA,
+                               ra[1 - kPlaneCy[q]] + unsigned(cx == 0 ? x : (cx == 1 ? xr : xl)));
+    }
+  }
+  float f[9], g[10], lf[9], lg[10];
+  {   // A
+    float v[kNPop][1];
+#pragma unroll
+    for (int q = 0; q < kNPop; ++q) v[q][0] = p[q][0];
+    collide_sites<1, LESF, SF == kFP16S>(v, rt);
+#pragma unroll
+    for (int q = 0; q < kNPop; ++q) {
+      const float e = CA::dec(CF::enc(v[q][0]));
+      if (kTileRow[q] >= 0)
+        l[kTileRow[q] < 0 ? 0 : kTileRow[q]][tid] = e;
+      else if (q < 9)
+        f[0] = e;
+      else
+        g[q - 9] = e;   // the rest planes of g: 0 and 5
+    }
+  }
+  __syncthreads();
+  double dv = 0.0, db = 0.0;
+  if (b_on) {   // B
+#pragma unroll
+    for (int q = 0; q < kNPop; ++q)
+      if (kTileRow[q] >= 0) {
+        const float e = l[kTileRow[q] < 0 ? 0 : kTileRow[q]][tid - kPlaneCy[q] * RX - kPlaneCx[q]];
+        if (q < 9)
+          f[q < 9 ? q : 0] = e;
+        else
+          g[q < 9 ? 0 : q - 9] = e;
+      }
+#pragma unroll
+    for (int i = 0; i < 9; ++i) lf[i] = lam[i];
+#pragma unroll
+    for (int k = 0; k < 10; ++k) lg[k] = lam[9 + k];
+    const CsGrad d = collide_adjoint<LESA>(f, g, lf, lg, rt, ac);
+    if (LESA && own) {
+      dv = double(d.v);
+      db = double(d.b);
+    }
+  }
+  __syncthreads();
+  if (b_on) {
+#pragma unroll
+    for (int q = 0; q < kNPop; ++q)
+      if (kTileRow[q] >= 0)
+        l[kTileRow[q] < 0 ? 0 : kTileRow[q]][tid] = q < 9 ? lf[q < 9 ? q : 0] : lg[q < 9 ? 0 : q - 9];
+  }
+  __syncthreads();
+  if (own) {   // C
+#pragma unroll
+    for (int q = 0; q < kNPop; ++q) {
+      if (kTileRow[q] >= 0) {
+        const float e = l[kTileRow[q] < 0 ? 0 : kTileRow[q]][tid + kPlaneCy[q] * RX + kPlaneCx[q]];
+        if (q < 9)
+          lf[q < 9 ? q : 0] = e;
+        else
+          lg[q < 9 ? 0 : q - 9] = e;
+      }
+      // deviations of x_t (FP16: exact, a power of two)
+      const float e = SF == kFP16S ? p[q][0] * 0x1p-10f : p[q][0];
+      if (q < 9)
+        f[q < 9 ? q : 0] = e;
+      else
+        g[q < 9 ? 0 : q - 9] = e;
+    }
+    const CsGrad d = collide_adjoint<LESA>(f, g, lf, lg, rt, ac);
+    if (LESA) {
+      dv += double(d.v);
+      db += double(d.b);
+    }
+    const unsigned oc = unsigned(y) * ga.pitch + unsigned(x);
+#pragma unroll
+    for (int i = 0; i < 9; ++i) st_plane<float>(lam_prev + i * PA, oc, lf[i]);
+#pragma unroll
+    for (int q = 0; q < 10; ++q) st_plane<float>(lam_prev + (9 + q) * PA, oc, lg[q]);
+  }
+  if (LESA) {
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) {
+      dv += __shfl_xor(dv, w);
+      db += __shfl_xor(db, w);
+    }
+    __syncthreads();   // the reads of lam_{t+1} are done: l holds the waves' sums
+    double* red = reinterpret_cast<double*>(&l[0][0]);
+    if ((tid & 63) == 0) {
+      red[2 * (tid >> 6)] = dv;
+      red[2 * (tid >> 6) + 1] = db;
+    }
+    __syncthreads();
+    if (tid < 2) {
+      double s = 0.0;
+      for (int w = 0; w < (N + 63) / 64; ++w) s += red[2 * w + tid];
+      acc[tid * nslots + tile] += s;
+    }
+  }
+}
+
 }  // namespace
 
 int adj_step_blocks(const Geom& g) {
@@ -1084,24 +1372,67 @@ void launch_adj_step2_t(const void* state, const float* lam_next, float* lam_pre
                      ga, r, ac, tiles_x, rows, xcd_map, adj_step_blocks(g));
 }
 
+// Tiles of a lattice with output tiles of w x h sites, and whether each has a
+// slot of its own in the derivatives' accumulator (adj_step_blocks slots).
+static int adj_tiles(const Geom& g, int w, int h) {
+  return ((g.nx + w - 1) / w) * ((g.ny + h - 1) / h);
+}
+static bool adj_slots_hold(const Geom& g, int w, int h) {
+  return adj_tiles(g, w, h) <= adj_step_blocks(g);
+}
+
+// Two reverse steps by tiles of 28 x 12 sites, us per step by rows / by tiles
+// (les = 1, states from HBM): FP32 128^2 20.7 / 4.5, 512^2 22.9 / 10.8, 1024^2
+// 35 / 29, 1800^2 98 / 94, 2048^2 115 / 121; FP16 1024^2 34 / 26, 2048^2 107 /
+// 105, 2500^2 169 / 160, 4096^2 414 / 424.
+static bool adj_tile_pays(int storage, const Geom& g) {
+  const double sites = double(g.nx) * g.ny;
+  return sites < (storage == LBMHD_FP32 ? 3.5e6 : 8e6) && adj_slots_hold(g, 28, 12);
+}
+// ... and of 12 x 12 sites, more and shorter blocks: 64^2 3.3 us per step
+// against 3.8, 128^2 3.3 against 3.9, 200^2 4.2 against 4.4.
+static bool adj_tile_small(const Geom& g) {
+  return double(g.nx) * g.ny <= 40000 && adj_slots_hold(g, 12, 12);
+}
+
+template <int ST, bool LESF, bool LESA, int RX, int RY>
+void launch_adj_tile_t(const void* state, const float* lam_next, float* lam_prev, double* acc,
+                       const Geom& g, const Geom& ga, const Rates& r, const AdjConsts& ac,
+                       hipStream_t s) {
+  const int grid = (adj_tiles(g, RX - 4, RY - 4) + 7) / 8 * 8;   // 8 equal bands
+  hipLaunchKernelGGL((k_adj_tile<ST, LESF, LESA, RX, RY>), dim3(grid), dim3(RX * RY), 0, s,
+                     static_cast<const typename Codec<ST>::T*>(state), lam_next, lam_prev, acc, g,
+                     ga, r, ac, (g.nx + RX - 5) / (RX - 4), adj_step_blocks(g));
+}
+
 hipError_t launch_adj_step2(int storage, bool les_fwd, bool les, const void* state,
                             const float* lam_next, float* lam_prev, double* acc, const Geom& g,
                             const Geom& ga, const Rates& r, double delta2, hipStream_t s) {
   if (les_fwd && !les) return hipErrorInvalidValue;
   const AdjConsts ac{float(18.0 * delta2), float(36.0 * delta2)};
-  auto go = [&](auto fp32) {
+  const bool small = adj_tile_small(g), tiles = small || adj_tile_pays(storage, g);
+  auto go = [&](auto fp32, auto fwd, auto rev) {
     constexpr int ST = decltype(fp32)::value ? LBMHD_FP32 : LBMHD_FP16;
-    if (les_fwd)
-      launch_adj_step2_t<ST, true, true>(state, lam_next, lam_prev, acc, g, ga, r, ac, s);
-    else if (les)
-      launch_adj_step2_t<ST, false, true>(state, lam_next, lam_prev, acc, g, ga, r, ac, s);
+    constexpr bool F = decltype(fwd)::value, R = decltype(rev)::value;
+    if (small)
+      launch_adj_tile_t<ST, F, R, 16, 16>(state, lam_next, lam_prev, acc, g, ga, r, ac, s);
+    else if (tiles)
+      launch_adj_tile_t<ST, F, R, 32, 16>(state, lam_next, lam_prev, acc, g, ga, r, ac, s);
     else
-      launch_adj_step2_t<ST, false, false>(state, lam_next, lam_prev, acc, g, ga, r, ac, s);
+      launch_adj_step2_t<ST, F, R>(state, lam_next, lam_prev, acc, g, ga, r, ac, s);
+  };
+  auto closure = [&](auto fp32) {
+    if (les_fwd)
+      go(fp32, std::true_type{}, std::true_type{});
+    else if (les)
+      go(fp32, std::false_type{}, std::true_type{});
+    else
+      go(fp32, std::false_type{}, std::false_type{});
   };
   if (storage == LBMHD_FP32)
-    go(std::true_type{});
+    closure(std::true_type{});
   else
-    go(std::false_type{});
+    closure(std::false_type{});
   return hipGetLastError();
 }
 
@@ -1120,6 +1451,28 @@ static int adj_kin_rows(const Geom& g) {
   return int(rows < 8 ? 8 : (rows > 256 ? 256 : rows));
 }
 
+// Region width of the tile form (0: by rows): where the strips are 8 rows high
+// (256-column tiles times ny up to 4096, so 1024^2), 64 columns, and on up to
+// 40000 sites 32, as far as the tiles have slots.  us per step by rows / 64 / 32
+// columns, les = 3: FP32 64^2 41 / 10.2 / 8.1, 200^2 43 / 11.1 / 9.0, 300^2 44 /
+// 12.2 / 12.7, 512^2 46 / 27 / 24, 1024^2 95 / 80 / 71; FP16 200^2 63 / 9.9 /
+// 8.3, 512^2 68 / 21 / 21, 1024^2 86 / 58 / 64.
+static int adj_kin_tile(const Geom& g, int rows) {
+  if (rows != 8) return 0;
+  if (double(g.nx) * g.ny <= 40000 && adj_slots_hold(g, 28, 8)) return 32;
+  return adj_slots_hold(g, 60, 8) ? 64 : 0;
+}
+
+template <int ST, bool LES, int RX>
+void launch_adj_kin_tile(const void* state, const float* lam_next, float* lam_prev, double* acc,
+                         const Geom& g, const Geom& ga, const Rates& r, const AdjConsts& ac,
+                         float c12, hipStream_t s) {
+  const int grid = (adj_tiles(g, RX - 4, 8) + 7) / 8 * 8;   // 8 equal bands
+  hipLaunchKernelGGL((k_adj_kin_tile<ST, LES, RX>), dim3(grid), dim3(RX * 12), 0, s,
+                     static_cast<const typename Dec<ST>::T*>(state), lam_next, lam_prev, acc, g,
+                     ga, r, ac, c12, (g.nx + RX - 5) / (RX - 4), adj_step_blocks(g));
+}
+
 hipError_t launch_adj_step_kin(int storage, bool les, const void* state, const float* lam_next,
                                float* lam_prev, double* acc, const Geom& g, const Geom& ga,
                                const Rates& r, double delta2, hipStream_t s) {
@@ -1127,23 +1480,32 @@ hipError_t launch_adj_step_kin(int storage, bool les, const void* state, const f
   const int rows = adj_kin_rows(g);
   const int strips = (g.ny + rows - 1) / rows;
   const dim3 grid(unsigned(tiles_x) * unsigned(strips)), block(kT3Threads);
+  const int tile = adj_kin_tile(g, rows);
   const AdjConsts ac{float(18.0 * delta2), float(36.0 * delta2)};
   const float c12 = float(delta2 / 12.0);
   const int nslots = adj_step_blocks(g);
-  auto go = [&](auto fp32) {
+  auto go = [&](auto fp32, auto smag) {
     constexpr int ST = decltype(fp32)::value ? LBMHD_FP32 : LBMHD_FP16;
-    auto* st = static_cast<const typename Dec<ST>::T*>(state);
-    if (les)
-      hipLaunchKernelGGL((k_adj_kin<ST, true>), grid, block, 0, s, st, lam_next, lam_prev, acc,
-                         g, ga, r, ac, c12, tiles_x, rows, nslots);
+    constexpr bool LES = decltype(smag)::value;
+    if (tile == 32)
+      launch_adj_kin_tile<ST, LES, 32>(state, lam_next, lam_prev, acc, g, ga, r, ac, c12, s);
+    else if (tile == 64)
+      launch_adj_kin_tile<ST, LES, 64>(state, lam_next, lam_prev, acc, g, ga, r, ac, c12, s);
     else
-      hipLaunchKernelGGL((k_adj_kin<ST, false>), grid, block, 0, s, st, lam_next, lam_prev, acc,
+      hipLaunchKernelGGL((k_adj_kin<ST, LES>), grid, block, 0, s,
+                         static_cast<const typename Dec<ST>::T*>(state), lam_next, lam_prev, acc,
                          g, ga, r, ac, c12, tiles_x, rows, nslots);
   };
+  auto closure = [&](auto fp32) {
+    if (les)
+      go(fp32, std::true_type{});
+    else
+      go(fp32, std::false_type{});
+  };
   if (storage == LBMHD_FP32)
-    go(std::true_type{});
+    closure(std::true_type{});
   else
-    go(std::false_type{});
+    closure(std::false_type{});
   return hipGetLastError();
 }
 

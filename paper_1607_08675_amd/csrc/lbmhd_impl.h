@@ -194,7 +194,9 @@ int adj_step_blocks(const Geom& g);
 hipError_t launch_adj_step2(int storage, bool les_fwd, bool les, const void* state,
                             const float* lam_next, float* lam_prev, double* acc, const Geom& g,
                             const Geom& ga, const Rates& r, double delta2, hipStream_t s);
-// Whether launch_adj_step2 fills the chip on this lattice.
+// Whether a sweep over every state takes its steps in pairs: from 512 blocks of
+// 8-row strips on (below, acc gains each step's block sums in the slots and
+// order of single steps).
 bool adj_step2_pays(const Geom& g);
 // The same reverse step for the kinetic closure (les = 2, or 3 with the
 // Smagorinsky-MHD closure): one walk over strips of rows, the gradient
