@@ -270,9 +270,9 @@ int lbmhd_step_store(lbmhd_t* h, const void* src, void* store, size_t stride, in
 /* npairs >= 0 pairs of steps from the encoded lattice src, keeping every
  * other state: state 2k (k = 1 .. npairs) is written to store + (k - 1) *
  * stride bytes (device; stride a multiple of 256 and >= `lattice` bytes), the
- * odd states are never written.  Each pair is one pass over the lattice (the
- * two-step kernels of lbmhd_step), so the result equals 2 npairs single
- * steps bit for bit.  The handle's current state and step count are
+ * odd states are never written.  Each pair, with automatic steps_per_pass on
+ * small and middling lattices each two pairs, is one pass over the lattice, and
+ * the result equals 2 npairs single steps bit for bit.  The handle's current state and step count are
  * untouched; the store range overlaps neither src nor the bound buffers.
  * Used to recompute a checkpoint segment for lbmhd_adj_sweep_pairs, which
  * needs only these states.  Asynchronous.  Errors as lbmhd_step_store. */

@@ -69,9 +69,20 @@ bool tile_short(const lbmhd_t* h, int k) {
          lbk::tile_short_pays(h->p.storage, reads_neighbours(h), k, h->geo);
 }
 
-hipError_t launch_tile_steps(const lbmhd_t* h, const void* src, void* dst, int k) {
+hipError_t launch_tile_steps(const lbmhd_t* h, const void* src, void* dst, int k,
+                             size_t keep = 0) {
   return lbk::launch_tile(h->p.storage, eddy_of(h), (h->p.les & 2) != 0, src, dst, k, h->geo,
-                          h->rates, h->p.delta, h->stream);
+                          h->rates, h->p.delta, h->stream, keep);
+}
+
+// The steps of one tile launch that keeps the states on its way (every second
+// one, every one with neighbour terms), 0 where it is not taken.
+int tile_keep(const lbmhd_t* h) {
+  const bool nb = reads_neighbours(h);
+  if (h->p.inplace || h->p.steps_per_pass != 0 ||
+      !lbk::tile_keep_pays(h->p.storage, nb, h->geo))
+    return 0;
+  return lbk::tile_keep(nb, h->geo);
 }
 
 // One step src -> dst with the handle's closure.
@@ -634,6 +645,13 @@ int lbmhd_step_store(lbmhd_t* h, const void* src, void* store, size_t stride, in
   const char* prev = static_cast<const char*>(src);
   char* out = static_cast<char*>(store);
   int64_t t = 0;
+  if (const int k = reads_neighbours(h) ? tile_keep(h) : 0)
+    for (; t + k <= n; t += k) {
+      hipError_t e = launch_tile_steps(h, prev, out, k, stride);
+      if (e != hipSuccess) return hip_fail(h, e, "step launch");
+      prev = out + (k - 1) * stride;
+      out += k * stride;
+    }
   const bool les = (h->p.les & 1) && (h->p.cs > 0.0 || h->p.cs_b > 0.0);
   // triples (FP32) that also store both intermediate states; a remainder of
   // one step goes with the last triple as two pairs
@@ -688,7 +706,15 @@ int lbmhd_step_store_pairs(lbmhd_t* h, const void* src, void* store, size_t stri
   if (int rc = natural(h, src)) return rc;
   const char* prev = static_cast<const char*>(src);
   char* out = static_cast<char*>(store);
-  for (int64_t k = 0; k < npairs; ++k) {
+  const int kp = (reads_neighbours(h) ? 0 : tile_keep(h)) / 2;   // pairs of a tile launch
+  int64_t left = npairs;
+  for (; kp > 0 && left >= kp; left -= kp) {
+    hipError_t e = launch_tile_steps(h, prev, out, 2 * kp, stride);
+    if (e != hipSuccess) return hip_fail(h, e, "step launch");
+    prev = out + (kp - 1) * stride;
+    out += kp * stride;
+  }
+  for (; left > 0; --left) {
     hipError_t e = launch_two_steps(h, prev, out, nullptr);
     if (e != hipSuccess) return hip_fail(h, e, "step launch");
     prev = out;

@@ -133,9 +133,16 @@ bool step_nb2_pays(const Geom& g);
 // (eddy, kin as launch_step_nb; eddy 0 or 1 without kin the plain and the
 // Smagorinsky-MHD update), equal to k single steps bit for bit.  k is at least
 // one and at most 5 (3 with neighbour terms), or what tile_steps gives.  src
-// and dst do not overlap.
+// and dst do not overlap.  keep > 0 (k then what tile_keep gives): dst takes
+// every second state instead of the last, every state with neighbour terms,
+// keep bytes apart (at least a lattice).
 hipError_t launch_tile(int storage, int eddy, bool kin, const void* src, void* dst, int k,
-                       const Geom& g, const Rates& r, double delta, hipStream_t s);
+                       const Geom& g, const Rates& r, double delta, hipStream_t s,
+                       size_t keep = 0);
+// The steps of a launch that keeps states, and whether that beats launches
+// that keep one each.
+int tile_keep(bool nb, const Geom& g);
+bool tile_keep_pays(int storage, bool nb, const Geom& g);
 // The steps of one launch where tiles are the faster way (nb: closures with
 // neighbour terms), or 0 where the row-walking kernels are.
 int tile_steps(int storage, bool nb, const Geom& g);

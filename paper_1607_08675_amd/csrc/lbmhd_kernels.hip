@@ -1028,10 +1028,13 @@ __global__ __launch_bounds__(kNb2Threads) __attribute__((amdgpu_waves_per_eu(4))
 // result equals k single steps bit for bit.  Plain stores: a tile's rows end
 // inside cache lines, which the L2 then completes (non-temporal stores
 // measured 5-15% slower from 512^2 on).
-template <int ST, int EDDY, bool KIN, int RX, int RY, int S, int K>
+// KEEP > 0 stores the state after every KEEP steps (k a multiple of it), `stride`
+// elements apart from dst on, instead of the last one only.
+template <int ST, int EDDY, bool KIN, int RX, int RY, int S, int K, int KEEP = 0>
 __global__ __launch_bounds__(RX* RY / S) void k_tile(
     const typename Codec<ST>::T* __restrict__ src, typename Codec<ST>::T* __restrict__ dst,
-    Geom geo, Rates rt, float c12, int steps, int tiles_x, int tile_w, int tile_h) {
+    Geom geo, Rates rt, float c12, int steps, int tiles_x, int tile_w, int tile_h,
+    long long stride) {
   const int k = K > 0 ? K : steps;
   using C = Codec<ST>;
   using T = typename C::T;
@@ -1096,6 +1099,12 @@ __global__ __launch_bounds__(RX* RY / S) void k_tile(
         } else {
           collide_sites<1, EDDY == 1, ST == kFP16S>(v[j], rt);
         }
+        if constexpr (KEEP > 0) {
+          const int oy = ry - halo;
+          if (s % KEEP == 0 && s < k && rx >= halo && rx < halo + wx && oy >= 0 && oy < wy)
+            store_row<ST, 1, false>(dst + (s / KEEP - 1) * stride, geo.plane,
+                                    unsigned(y0 + oy) * geo.pitch + unsigned(x), v[j]);
+        }
         if (s < k) {
 #pragma unroll
           for (int q = 0; q < kNPop; ++q) {
@@ -1129,6 +1138,7 @@ __global__ __launch_bounds__(RX* RY / S) void k_tile(
   } else {
     for (int s = 1; s <= k; ++s) step(s);
   }
+  if constexpr (KEEP > 0) dst += (k / KEEP - 1) * stride;
   if (rx >= halo && rx < halo + wx) {
 #pragma unroll
     for (int j = 0; j < S; ++j) {
@@ -1994,11 +2004,16 @@ static int tile_most(bool nb, const Geom& g) {
   return k;
 }
 
+// Steps of the launches that keep every state (NB) or every second one.
+template <bool NB, int S>
+constexpr int kTileKeep = !NB ? 4 : (S == 1 ? 3 : 2);
+
 template <int ST, int EDDY, bool KIN, int RX, int RY, int S>
-static void launch_tile_r(const void* src, void* dst, int k, const Geom& g, const Rates& r,
-                          float c12, hipStream_t s) {
+static void launch_tile_r(const void* src, void* dst, int k, size_t keep, const Geom& g,
+                          const Rates& r, float c12, hipStream_t s) {
   using T = typename Codec<ST>::T;
-  const int halo = Tile<ST, EDDY, KIN>::kNb ? 2 * k - 1 : k - 1;
+  constexpr bool kNb = Tile<ST, EDDY, KIN>::kNb;
+  const int halo = kNb ? 2 * k - 1 : k - 1;
   const int w = RX - 2 * halo, h = RY - 2 * halo;
   const int tiles_x = (g.nx + w - 1) / w, tiles_y = (g.ny + h - 1) / h;
   const dim3 grid((tiles_x * tiles_y + 7) / 8 * 8), block(RX * RY / S);
@@ -2006,50 +2021,62 @@ static void launch_tile_r(const void* src, void* dst, int k, const Geom& g, cons
   auto* b = static_cast<T*>(dst);
   // the usual count of each kind is compiled for itself: unrolled, no value is
   // moved between registers from step to step (FP16 10-17% faster)
-  constexpr int kFull = !Tile<ST, EDDY, KIN>::kNb ? 5 : (ST == LBMHD_FP32 || S == 1 ? 3 : 2);
-  if (k == kFull)
+  constexpr int kFull = !kNb ? 5 : (ST == LBMHD_FP32 || S == 1 ? 3 : 2);
+  const long long stride = (long long)(keep / sizeof(T));
+  if (keep)
+    hipLaunchKernelGGL((k_tile<ST, EDDY, KIN, RX, RY, S, kTileKeep<kNb, S>, kNb ? 1 : 2>), grid,
+                       block, 0, s, a, b, g, r, c12, k, tiles_x, w, h, stride);
+  else if (k == kFull)
     hipLaunchKernelGGL((k_tile<ST, EDDY, KIN, RX, RY, S, kFull>), grid, block, 0, s, a, b, g, r,
-                       c12, k, tiles_x, w, h);
+                       c12, k, tiles_x, w, h, stride);
   else
     hipLaunchKernelGGL((k_tile<ST, EDDY, KIN, RX, RY, S, 0>), grid, block, 0, s, a, b, g, r, c12,
-                       k, tiles_x, w, h);
+                       k, tiles_x, w, h, stride);
 }
 
 template <int ST, int EDDY, bool KIN>
-static void launch_tile_c(const void* src, void* dst, int k, const Geom& g, const Rates& r,
-                          float c12, hipStream_t s) {
+static void launch_tile_c(const void* src, void* dst, int k, size_t keep, const Geom& g,
+                          const Rates& r, float c12, hipStream_t s) {
   if (tile_small(g))
-    launch_tile_r<ST, EDDY, KIN, 16, 16, 1>(src, dst, k, g, r, c12, s);
+    launch_tile_r<ST, EDDY, KIN, 16, 16, 1>(src, dst, k, keep, g, r, c12, s);
   else
-    launch_tile_r<ST, EDDY, KIN, 32, Tile<ST, EDDY, KIN>::kBigRows, 2>(src, dst, k, g, r, c12, s);
+    launch_tile_r<ST, EDDY, KIN, 32, Tile<ST, EDDY, KIN>::kBigRows, 2>(src, dst, k, keep, g, r,
+                                                                       c12, s);
 }
 
 template <int ST>
-static hipError_t launch_tile_s(int eddy, bool kin, const void* src, void* dst, int k,
+static hipError_t launch_tile_s(int eddy, bool kin, const void* src, void* dst, int k, size_t keep,
                                 const Geom& g, const Rates& r, float c12, hipStream_t s) {
   constexpr int SN = ST == kFP16S ? LBMHD_FP16 : ST;   // codec of the closures with neighbours
   if (kin && eddy == 0)
-    launch_tile_c<SN, 0, true>(src, dst, k, g, r, c12, s);
+    launch_tile_c<SN, 0, true>(src, dst, k, keep, g, r, c12, s);
   else if (kin && eddy == 1)
-    launch_tile_c<SN, 1, true>(src, dst, k, g, r, c12, s);
+    launch_tile_c<SN, 1, true>(src, dst, k, keep, g, r, c12, s);
   else if (kin)
-    launch_tile_c<SN, 2, true>(src, dst, k, g, r, c12, s);
+    launch_tile_c<SN, 2, true>(src, dst, k, keep, g, r, c12, s);
   else if (eddy == 2)
-    launch_tile_c<SN, 2, false>(src, dst, k, g, r, c12, s);
+    launch_tile_c<SN, 2, false>(src, dst, k, keep, g, r, c12, s);
   else if (eddy == 1)
-    launch_tile_c<ST, 1, false>(src, dst, k, g, r, c12, s);
+    launch_tile_c<ST, 1, false>(src, dst, k, keep, g, r, c12, s);
   else
-    launch_tile_c<ST, 0, false>(src, dst, k, g, r, c12, s);
+    launch_tile_c<ST, 0, false>(src, dst, k, keep, g, r, c12, s);
   return hipGetLastError();
 }
 
 hipError_t launch_tile(int storage, int eddy, bool kin, const void* src, void* dst, int k,
-                       const Geom& g, const Rates& r, double delta, hipStream_t s) {
-  if (k < 1 || k > tile_most(kin || eddy == 2, g)) return hipErrorInvalidValue;
+                       const Geom& g, const Rates& r, double delta, hipStream_t s, size_t keep) {
+  const bool nb = kin || eddy == 2;
+  if (k < 1 || k > tile_most(nb, g) || (keep && k != tile_keep(nb, g)))
+    return hipErrorInvalidValue;
   const float c12 = float(delta * delta / 12.0);
   if (storage == LBMHD_FP32)
-    return launch_tile_s<LBMHD_FP32>(eddy, kin, src, dst, k, g, r, c12, s);
-  return launch_tile_s<kFP16S>(eddy, kin, src, dst, k, g, r, c12, s);
+    return launch_tile_s<LBMHD_FP32>(eddy, kin, src, dst, k, keep, g, r, c12, s);
+  return launch_tile_s<kFP16S>(eddy, kin, src, dst, k, keep, g, r, c12, s);
+}
+
+int tile_keep(bool nb, const Geom& g) {
+  if (tile_small(g)) return nb ? kTileKeep<true, 1> : kTileKeep<false, 1>;
+  return nb ? kTileKeep<true, 2> : kTileKeep<false, 2>;
 }
 
 // The lattice's sites, weighted by the share of the row-walking kernels'
@@ -2081,6 +2108,19 @@ bool tile_short_pays(int storage, bool nb, int k, const Geom& g) {
   if (nb) return k > 1 || tile_size(g) < 2.2e6;
   if (k >= (storage == LBMHD_FP32 ? 4 : 3)) return true;
   return k > 1 && tile_size(g) < (storage == LBMHD_FP32 ? 1.04e6 : 4.0e6);
+}
+
+// Launches that keep states on the way, us per step against the launches that
+// keep one each.  Every second state: FP32 64^2 1.4 / 2.2, 512^2 4.5 / 5.7 (two
+// steps in tiles), 1024^2 17.4 / 19.2, 1448^2 37.4 / 37.6 (k_step2), 2048^2 72 / 66;
+// FP16 512^2 4.2 / 5.3, 1024^2 10.1 / 11.3, 2048^2 42.3 / 45.6 (k_step2), 2896^2 84
+// / 82 (eight steps a launch 20 / 20 at 1024^2 FP32, 60 / 46 at 2048^2 FP16).
+// Every state, neighbour terms: FP32 64^2 2.1 / 4.0 (one step in tiles), 512^2
+// 8.2 / 10.9, 724^2 16.9 / 18.6, 1024^2 35.6 / 31.8 (k_step_nb2); FP16 512^2 8.5 /
+// 9.9, 1024^2 22.4 / 23.3, 1448^2 46.2 / 47.4, 2048^2 89 / 79 (k_step_nb).
+bool tile_keep_pays(int storage, bool nb, const Geom& g) {
+  if (nb) return tile_size(g) < (storage == LBMHD_FP32 ? 8e5 : 2.2e6);
+  return tile_size(g) < (storage == LBMHD_FP32 ? 1.5e6 : 5e6);
 }
 
 // ------------------------------------------ several steps in place
