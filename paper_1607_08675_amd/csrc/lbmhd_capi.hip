@@ -780,15 +780,15 @@ int lbmhd_diag(lbmhd_t* h, lbmhd_diag_t* out) {
 }
 
 // The diagnostics of the state just reached, enqueued without waiting on the
-// host: results to dev (16 doubles).  With two lattices the pass runs on the
-// side stream after the bound stream's work so far, and the lattice it reads
-// is marked so that the next pass that writes it waits for it; an in-place
-// lattice (whose next pass rewrites it) is read on the bound stream.
-int enqueue_diag(lbmhd_t* h, double* dev) {
+// host: results to dev (16 doubles).  Aside (two lattices only) the pass runs on
+// the side stream after the bound stream's work so far, and the lattice it
+// reads is marked so that the next pass that writes it waits for it; otherwise
+// on the bound stream (an in-place lattice's next pass rewrites it).
+int enqueue_diag(lbmhd_t* h, double* dev, bool aside) {
   const void* st = nullptr;
   if (int rc = current(h, &st)) return rc;
   hipError_t e;
-  if (h->p.inplace) {
+  if (!aside) {
     e = lbk::launch_diag(h->p.storage, st, h->ws, dev, h->geo, h->stream);
     return e == hipSuccess ? LBMHD_OK : hip_fail(h, e, "diagnostics launch");
   }
@@ -824,11 +824,19 @@ int lbmhd_run(lbmhd_t* h, int64_t nsteps, int64_t every, double* dev, lbmhd_diag
   // closure without neighbour terms) takes that step and the diagnostics of
   // its result in one pass on the bound stream; so does every interval of a
   // lattice so small that the launch saved counts for more than the step
+  // (FP16 256^2, ten steps an interval: 48 us aside, 33 fused)
   const int ps = pass_steps(h), most = tile_most(h);
   const bool tiny = (long long)h->p.nx * h->p.ny < 300000;
-  const bool fuse = !h->p.inplace && h->p.storage == LBMHD_FP32 && !reads_neighbours(h) &&
-                    (most > 0 ? tiny || every % most == 1 : ps == 1 || every % ps == 1);
-  if (!h->p.inplace && !fuse && !h->side) {
+  const bool fuse = !h->p.inplace && !reads_neighbours(h) &&
+                    (h->p.storage == LBMHD_FP16 ? most > 0 && lbk::diag_by_row(h->geo)
+                     : most > 0                 ? tiny || every % most == 1
+                                                : ps == 1 || every % ps == 1);
+  // On a small lattice the events that order a second stream cost more than the
+  // pass: us per interval of ten steps, aside / on the bound stream, les = 2
+  // 64^2 50 / 33, 512^2 100 / 93, les = 1 FP32 640^2 92 / 86, 800^2 101 / 105.
+  const bool aside =
+      !h->p.inplace && !fuse && !(most > 0 && (long long)h->p.nx * h->p.ny < 500000);
+  if (aside && !h->side) {
     hipError_t e = hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&h->ev_state, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&h->ev_diag, hipEventDisableTiming);
@@ -843,9 +851,9 @@ int lbmhd_run(lbmhd_t* h, int64_t nsteps, int64_t every, double* dev, lbmhd_diag
       if (rc == LBMHD_OK) rc = before_write(h, 0);
       if (rc == LBMHD_OK) rc = before_write(h, 1);
       if (rc == LBMHD_OK) {
-        hipError_t e = lbk::launch_step_diag(eddy_of(h) == 1, h->lat[h->cur], h->lat[1 - h->cur],
-                                             h->ws, dev + k * lbk::kDiagSlots, h->geo, h->rates,
-                                             h->stream);
+        hipError_t e = lbk::launch_step_diag(h->p.storage, eddy_of(h) == 1, h->lat[h->cur],
+                                             h->lat[1 - h->cur], h->ws, dev + k * lbk::kDiagSlots,
+                                             h->geo, h->rates, h->stream);
         if (e != hipSuccess) {
           rc = hip_fail(h, e, "step and diagnostics launch");
         } else {
@@ -855,7 +863,7 @@ int lbmhd_run(lbmhd_t* h, int64_t nsteps, int64_t every, double* dev, lbmhd_diag
       }
     } else {
       rc = lbmhd_step(h, every);
-      if (rc == LBMHD_OK) rc = enqueue_diag(h, dev + k * lbk::kDiagSlots);
+      if (rc == LBMHD_OK) rc = enqueue_diag(h, dev + k * lbk::kDiagSlots, aside);
     }
     at[size_t(k)] = h->step;
   }

@@ -1485,16 +1485,19 @@ enum {
 // doubles of LDS): each wave takes every fourth quantity, four values a lane
 // from LDS and six exchanges in registers, one barrier in all (a tree of
 // eight barriers over all quantities: k_step_diag 10.2 us at 64^2 against 9.5,
-// k_diag_final 3.7 against 3.3).
-template <bool ROOT>
+// k_diag_final 3.7 against 3.3).  In a block of more WAVES the 256 threads with
+// on hand in their values as thread t.
+template <bool ROOT, int WAVES = 4>
 __device__ __forceinline__ void block_reduce(const double (&v)[kNRed], double* __restrict__ red,
-                                             double* __restrict__ out) {
+                                             double* __restrict__ out, int t, bool on = true) {
 #pragma clang fp contract(off)
-  const int t = int(threadIdx.x), lane = t & 63;
+  const int lane = int(threadIdx.x) & 63;
+  if (on) {
 #pragma unroll
-  for (int q = 0; q < kNRed; ++q) red[q * 256 + t] = v[q];
+    for (int q = 0; q < kNRed; ++q) red[q * 256 + t] = v[q];
+  }
   __syncthreads();
-  for (int q = t >> 6; q < kNRed; q += 4) {
+  for (int q = int(threadIdx.x) >> 6; q < kNRed; q += WAVES) {
     const double* r = red + q * 256 + lane;
     const double r0 = r[0], r1 = r[64], r2 = r[128], r3 = r[192];
     double a = q < kNSum ? (r0 + r1) + (r2 + r3) : fmax(fmax(r0, r1), fmax(r2, r3));
@@ -1596,7 +1599,8 @@ __device__ __forceinline__ void diag_partial(const double (&v)[kNRed], DiagRing&
                                              double* __restrict__ part) {
   static_assert(kDiagThreads == 256 && 3 * 5 * kDiagNC >= kNRed * kDiagThreads,
                 "ring too small to reduce in");
-  block_reduce<false>(v, &mac[0][0][0], part + (long long)blockIdx.x * kDiagSlots);
+  block_reduce<false>(v, &mac[0][0][0], part + (long long)blockIdx.x * kDiagSlots,
+                      int(threadIdx.x));
 }
 
 template <int ST>
@@ -1723,6 +1727,64 @@ __global__ __launch_bounds__(kDiagThreads) void k_step_diag(const float* __restr
   diag_partial(v, mac, part);
 }
 
+// Both where a strip is a single row (diag_rows): the three rows of the ring at
+// once, 256 threads each and six lanes of a last wave for the halo columns,
+// so that the chain is one gather, one collision and the moments' FP64 work
+// instead of three of each.  The row's sums are taken as above, so the partials
+// are the same bit for bit.  Columns past the lattice's right edge but the first
+// have nothing to do.
+constexpr int kDiagRowThreads = 3 * kDiagThreads + 64;
+template <int ST, bool STEP, bool LES>
+__global__ __launch_bounds__(kDiagRowThreads) void k_diag_row(
+    const typename Codec<ST>::T* __restrict__ src, typename Codec<ST>::T* __restrict__ dst,
+    double* __restrict__ part, Geom geo, Rates rt, int tiles_x) {
+  using C = Codec<ST>;
+  using T = typename C::T;
+  __shared__ DiagRing mac;
+  const int tid = int(threadIdx.x), k = tid - 3 * kDiagThreads;
+  const int xt = (int(blockIdx.x) % tiles_x) * kDiagThreads, y0 = int(blockIdx.x) / tiles_x;
+  const int slot = k < 0 ? tid / kDiagThreads : k >> 1;   // row y0 - 1 + slot
+  const int tx = tid % kDiagThreads;
+  int x = xt + tx;
+  bool has = x <= geo.nx;
+  int col = tx + 1;
+  if (k >= 0) {
+    has = k < 6;
+    x = (k & 1) == 0 ? (xt == 0 ? geo.nx - 1 : xt - 1) : xt + kDiagThreads;
+    col = (k & 1) == 0 ? 0 : kDiagNC - 1;
+  }
+  const bool own = k < 0 && slot == 1 && x < geo.nx;
+  if (has) {
+    x %= geo.nx;
+    unsigned row[3];
+    t2_rows(y0 - 1 + slot, geo, row);
+    T p[kNPop];
+    if constexpr (STEP) {
+      constexpr int SF = ST == LBMHD_FP32 ? LBMHD_FP32 : kFP16S;
+      float f[kNPop][1];
+      gather_row<SF, 1>(src, geo.plane, x, x == 0 ? geo.nx - 1 : x - 1,
+                        x == geo.nx - 1 ? 0 : x + 1, row, f);
+      collide_sites<1, LES, SF == kFP16S>(f, rt);
+      if (own) store_row<SF, 1, false>(dst, geo.plane, row[1] + unsigned(x), f);
+#pragma unroll
+      for (int q = 0; q < kNPop; ++q) p[q] = Codec<SF>::enc(f[q][0]);
+    } else {
+#pragma unroll
+      for (int q = 0; q < kNPop; ++q) p[q] = ld_plane<T>(src + q * geo.plane, row[1] + unsigned(x));
+    }
+    diag_moments<C>(p, mac, slot, col);
+  }
+  __syncthreads();
+  double v[kNRed];
+#pragma unroll
+  for (int q = 0; q < kNRed; ++q) v[q] = 0.0;
+  if (own) diag_accumulate(v, mac, 0, 1, 2, tx + 1);
+  __syncthreads();
+  block_reduce<false, kDiagRowThreads / 64>(v, &mac[0][0][0],
+                                            part + (long long)blockIdx.x * kDiagSlots, tx,
+                                            k < 0 && slot == 1);
+}
+
 // Pass 3: one block folds the partials.
 __global__ __launch_bounds__(256) void k_diag_final(const double* __restrict__ part, int nparts,
                                                     double* __restrict__ out) {
@@ -1736,7 +1798,7 @@ __global__ __launch_bounds__(256) void k_diag_final(const double* __restrict__ p
     for (int q = kNSum; q < kNRed; ++q) v[q] = fmax(v[q], part[(long long)b * kDiagSlots + q]);
   }
   __shared__ double red[kNRed * 256];
-  block_reduce<true>(v, red, out);
+  block_reduce<true>(v, red, out, int(threadIdx.x));
 }
 
 __global__ __launch_bounds__(256) void k_sum(const double* __restrict__ in, long long n,
@@ -2310,12 +2372,24 @@ int diag_partials(const Geom& g) {
   return int(std::min<long long>(kDiagBlocks, diag_units(g)));
 }
 
+// A block to a row (k_diag_row) while each has a CU of its own: us per interval
+// of one step and its diagnostics, walking / by the row, FP32 64^2 16.7 / 12.5,
+// 128^2 17.1 / 14.1, 256^2 18.7 / 17.5, 400^2 (800 blocks) 28.9 / 29.0, 512^2 30.7 / 32.9.
+bool diag_by_row(const Geom& g) { return diag_rows(g) == 1 && diag_units(g) <= 256; }
+
 hipError_t launch_diag(int storage, const void* lat, double* part, double* out_dev,
                        const Geom& g, hipStream_t s) {
   const int tiles_x = (g.nx + kDiagThreads - 1) / kDiagThreads;
   const long long units = diag_units(g);
   const int nparts = diag_partials(g), rows = diag_rows(g);
-  if (storage == LBMHD_FP32)
+  if (diag_by_row(g))
+    with_bools([&](auto fp32) {
+      constexpr int ST = fp32() ? LBMHD_FP32 : LBMHD_FP16;
+      hipLaunchKernelGGL((k_diag_row<ST, false, false>), dim3(nparts), dim3(kDiagRowThreads), 0, s,
+                         static_cast<const typename Codec<ST>::T*>(lat), nullptr, part, g, Rates{},
+                         tiles_x);
+    }, storage == LBMHD_FP32);
+  else if (storage == LBMHD_FP32)
     hipLaunchKernelGGL(k_diag<LBMHD_FP32>, dim3(nparts), dim3(kDiagThreads), 0, s,
                        static_cast<const float*>(lat), part, g, tiles_x, int(units), rows);
   else
@@ -2325,19 +2399,26 @@ hipError_t launch_diag(int storage, const void* lat, double* part, double* out_d
   return hipGetLastError();
 }
 
-hipError_t launch_step_diag(bool les, const void* src, void* dst, double* part, double* out_dev,
-                            const Geom& g, const Rates& r, hipStream_t s) {
+hipError_t launch_step_diag(int storage, bool les, const void* src, void* dst, double* part,
+                            double* out_dev, const Geom& g, const Rates& r, hipStream_t s) {
   const int tiles_x = (g.nx + kDiagThreads - 1) / kDiagThreads;
   const long long units = diag_units(g);
   const int nparts = diag_partials(g), rows = diag_rows(g);
-  auto* a = static_cast<const float*>(src);
-  auto* b = static_cast<float*>(dst);
-  if (les)
-    hipLaunchKernelGGL(k_step_diag<true>, dim3(nparts), dim3(kDiagThreads), 0, s, a, b, part, g, r,
-                       tiles_x, int(units), rows);
-  else
-    hipLaunchKernelGGL(k_step_diag<false>, dim3(nparts), dim3(kDiagThreads), 0, s, a, b, part, g,
-                       r, tiles_x, int(units), rows);
+  if (diag_by_row(g)) {
+    with_bools([&](auto fp32, auto l) {
+      constexpr int ST = fp32() ? LBMHD_FP32 : LBMHD_FP16;
+      using T = typename Codec<ST>::T;
+      hipLaunchKernelGGL((k_diag_row<ST, true, l()>), dim3(nparts), dim3(kDiagRowThreads), 0, s,
+                         static_cast<const T*>(src), static_cast<T*>(dst), part, g, r, tiles_x);
+    }, storage == LBMHD_FP32, les);
+  } else {
+    if (storage != LBMHD_FP32) return hipErrorInvalidValue;
+    with_bools([&](auto l) {
+      hipLaunchKernelGGL(k_step_diag<l()>, dim3(nparts), dim3(kDiagThreads), 0, s,
+                         static_cast<const float*>(src), static_cast<float*>(dst), part, g, r,
+                         tiles_x, int(units), rows);
+    }, les);
+  }
   hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(256), 0, s, part, nparts, out_dev);
   return hipGetLastError();
 }
