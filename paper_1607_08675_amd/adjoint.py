@@ -119,17 +119,19 @@ class Checkpointed:
                                     self.pairs)
         self.interval = k
         if k == 1 and self.pairs and nsteps > 1:
-            # the initial state, the even states 2 .. 2m (m = (nsteps - 1) // 2,
-            # one library call) and the final state, reached from state 2m by
-            # the one or two steps left; the lattice ends on the final state
+            # the initial state, the even states 2 .. 2m (m = (nsteps - 1) // 2)
+            # and the final state, all written where they are kept; the lattice
+            # ends on the final state
             m = (nsteps - 1) // 2
             self.store = store
             self.ckpts = [store[0]]
             lat.save_state(store[0])
-            lat.step_store_pairs(store[0], store[1:m + 1], m)
-            lat.load_state(store[m], lat.step_count + 2 * m)
-            lat.step(nsteps - 2 * m)
-            self.final = lat.save_state(store[m + 1])
+            pairs = nsteps // 2   # an even run's final state ends a pair
+            lat.step_store_pairs(store[0], store[1:pairs + 1], pairs)
+            if nsteps % 2:
+                lat.step_between(store[m], store[m + 1])
+            self.final = store[m + 1]
+            lat.load_state(self.final, lat.step_count + nsteps)
         elif k == 1:
             # every state kept, in one allocation, written by one library call;
             # the lattice ends on the final state
@@ -165,7 +167,15 @@ class Checkpointed:
         k = self.interval
         if k == 1 and self.pairs and self.nsteps > 1:
             m = (self.nsteps - 1) // 2
-            lat.adj_sweep_pairs(self.ckpts[0], self.store[1:m + 1], self.nsteps, lam, lam2, acc)
+            if (m + 1) % 2:
+                # an odd number of launches would begin with a copy of lam: the
+                # first goes alone, and the sweep from lam2 back into it
+                (lat.adj_step if self.nsteps % 2 else lat.adj_step2)(self.store[m], lam, lam2, acc)
+                lam, lam2 = lam2, lam
+                lat.adj_sweep_pairs(self.ckpts[0], self.store[1:m + 1], 2 * m, lam, lam2, acc)
+            else:
+                lat.adj_sweep_pairs(self.ckpts[0], self.store[1:m + 1], self.nsteps, lam, lam2,
+                                    acc)
         elif k == 1:
             lat.adj_sweep(self.ckpts[0], self.store[1:], self.nsteps, lam, lam2, acc)
         elif self.pairs:
