@@ -1013,14 +1013,16 @@ __global__ __launch_bounds__(kNb2Threads) __attribute__((amdgpu_waves_per_eu(4))
 }
 
 // ------------------------------------------ several steps of a tile in LDS
-// dst = (C S)^k src on small lattices, k >= 1 a run-time argument: a block
-// owns a tile of the output and a region of RX x RY sites around it, takes
-// the first update of every site of the region from HBM (periodic images
-// where the region passes the lattice's edge or is larger than the lattice),
-// and the other k - 1 from LDS, on a region that shrinks by one site on each
-// side per step.  A thread owns the S sites (rx, ry + j RY / S).  It holds
+// dst = (C S)^k src, k >= 1 a run-time argument or K: a block owns a tile of
+// the output and a region of RX x RY sites around it, takes the first update of
+// every site of the region from HBM (periodic images where the region passes
+// the lattice's edge or is larger than the lattice), and the other k - 1 from
+// LDS, on a region that shrinks by one site on each side per step.  A thread
+// owns the S sites (rx, ry + j RY / S).  It holds
 // the rest populations in registers; the 16 moving ones pass through one LDS
-// buffer (written, barrier, read at x - c, barrier).
+// buffer (written, barrier, read at x - c, barrier), in PH parts.  Bound by the
+// issue of vector instructions, about 80% of its ceiling with the lanes whose
+// sites are halo counted (1.4 to 1.8 a site and step).
 // The closures that read their neighbours' moments (NB) shrink by two sites
 // a step: each step's gathered moments go to a second LDS buffer, and the
 // update takes the sites whose eight neighbours were gathered.
@@ -1030,7 +1032,7 @@ __global__ __launch_bounds__(kNb2Threads) __attribute__((amdgpu_waves_per_eu(4))
 // measured 5-15% slower from 512^2 on).
 // KEEP > 0 stores the state after every KEEP steps (k a multiple of it), `stride`
 // elements apart from dst on, instead of the last one only.
-template <int ST, int EDDY, bool KIN, int RX, int RY, int S, int K, int KEEP = 0>
+template <int ST, int EDDY, bool KIN, int RX, int RY, int S, int K, int KEEP = 0, int PH = 1>
 __global__ __launch_bounds__(RX* RY / S) void k_tile(
     const typename Codec<ST>::T* __restrict__ src, typename Codec<ST>::T* __restrict__ dst,
     Geom geo, Rates rt, float c12, int steps, int tiles_x, int tile_w, int tile_h,
@@ -1041,7 +1043,8 @@ __global__ __launch_bounds__(RX* RY / S) void k_tile(
   constexpr bool NB = KIN || EDDY == 2;
   constexpr int NF = KIN ? 5 : 3;     // moments of NB: rho - 1, j (, B)
   constexpr int N = RX * RY, H = RY / S;
-  __shared__ T pl[16][N];             // moving planes (kTileRow)
+  constexpr int NP = 16 / PH;
+  __shared__ T pl[NP][N];             // moving planes (kTileRow), PH parts in turn
   __shared__ float mo[NB ? NF : 1][NB ? N : 1];
   const int rx = int(threadIdx.x) % RX, ry0 = int(threadIdx.x) / RX;
   const int halo = NB ? 2 * k - 1 : k - 1;
@@ -1108,6 +1111,7 @@ __global__ __launch_bounds__(RX* RY / S) void k_tile(
         if (s < k) {
 #pragma unroll
           for (int q = 0; q < kNPop; ++q) {
+            if (kTileRow[q] >= NP) continue;   // a later part
             const T e = C::enc(v[j][q][0]);
             if (kTileRow[q] >= 0)
               pl[kTileRow[q] < 0 ? 0 : kTileRow[q]][ry * RX + rx] = e;
@@ -1118,16 +1122,32 @@ __global__ __launch_bounds__(RX* RY / S) void k_tile(
       }
     }
     if (s == k) return;
-    __syncthreads();
 #pragma unroll
-    for (int j = 0; j < S; ++j) {
-      const int ry = ry0 + j * H;
-      if (rx > in && rx < RX - 1 - in && ry > in && ry < RY - 1 - in) {
+    for (int ph = 0; ph < PH; ++ph) {
+      if (ph > 0) {
+        __syncthreads();
 #pragma unroll
-        for (int q = 0; q < kNPop; ++q)
-          if (kTileRow[q] >= 0)
-            v[j][q][0] = C::dec(pl[kTileRow[q] < 0 ? 0 : kTileRow[q]]
-                                  [(ry - kPlaneCy[q]) * RX + rx - kPlaneCx[q]]);
+        for (int j = 0; j < S; ++j) {
+          const int ry = ry0 + j * H;
+          if (rx >= in && rx < RX - in && ry >= in && ry < RY - in) {
+#pragma unroll
+            for (int q = 0; q < kNPop; ++q)
+              if (kTileRow[q] / NP == ph && kTileRow[q] >= 0)
+                pl[kTileRow[q] < 0 ? 0 : kTileRow[q] % NP][ry * RX + rx] = C::enc(v[j][q][0]);
+          }
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < S; ++j) {
+        const int ry = ry0 + j * H;
+        if (rx > in && rx < RX - 1 - in && ry > in && ry < RY - 1 - in) {
+#pragma unroll
+          for (int q = 0; q < kNPop; ++q)
+            if (kTileRow[q] / NP == ph && kTileRow[q] >= 0)
+              v[j][q][0] = C::dec(pl[kTileRow[q] < 0 ? 0 : kTileRow[q] % NP]
+                                    [(ry - kPlaneCy[q]) * RX + rx - kPlaneCx[q]]);
+        }
       }
     }
     if constexpr (!NB) __syncthreads();   // NB: the moments' barrier follows every read
@@ -2040,10 +2060,11 @@ hipError_t launch_step2(int storage, bool les, const void* src, void* dst, void*
 // sites and up to five steps (tiles of 8 x 8; closures with neighbour terms
 // three steps, 6 x 6); from 200^2 on 32 x 32 (32 x 28 with FP32 neighbour
 // terms), two sites a thread: eight waves, two on each SIMD, and two blocks
-// per CU in 64-75 KB of LDS each.  Regions whose waves do not divide evenly
-// over the SIMDs (40 x 32, 32 x 36, 48 x 24) ran at 75k MLUPS at 4096^2 FP32
-// against 119k, one block per CU (64 x 32) at 89k, four sites a thread at 109k,
-// and blocks that stay for several tiles and gather the next one ahead at 85k.
+// per CU in 64-75 KB of LDS each; on large lattices 64 x 32 (launch_tile_wide).
+// Regions whose waves do not divide evenly over the SIMDs (40 x 32, 32 x 36,
+// 48 x 24) ran at 75k MLUPS at 4096^2 FP32 against 119k, four sites a thread of
+// 32 x 32 at 109k, and blocks that stay for several tiles and gather the next
+// one ahead at 85k.
 template <int ST, int EDDY, bool KIN>
 struct Tile {
   static constexpr bool kNb = KIN || EDDY == 2;
@@ -2070,35 +2091,72 @@ static int tile_most(bool nb, const Geom& g) {
 template <bool NB, int S>
 constexpr int kTileKeep = !NB ? 4 : (S == 1 ? 3 : 2);
 
+template <int ST, int EDDY, bool KIN, int RX, int RY, int S, int K, int KEEP = 0, int PH = 1>
+static void launch_tile_k(const void* src, void* dst, int k, size_t keep, const Geom& g,
+                          const Rates& r, float c12, hipStream_t s) {
+  using T = typename Codec<ST>::T;
+  const int halo = Tile<ST, EDDY, KIN>::kNb ? 2 * k - 1 : k - 1;
+  const int w = RX - 2 * halo, h = RY - 2 * halo;
+  const int tiles_x = (g.nx + w - 1) / w, tiles_y = (g.ny + h - 1) / h;
+  hipLaunchKernelGGL((k_tile<ST, EDDY, KIN, RX, RY, S, K, KEEP, PH>),
+                     dim3((tiles_x * tiles_y + 7) / 8 * 8), dim3(RX * RY / S), 0, s,
+                     static_cast<const T*>(src), static_cast<T*>(dst), g, r, c12, k, tiles_x, w, h,
+                     (long long)(keep / sizeof(T)));
+}
+
 template <int ST, int EDDY, bool KIN, int RX, int RY, int S>
 static void launch_tile_r(const void* src, void* dst, int k, size_t keep, const Geom& g,
                           const Rates& r, float c12, hipStream_t s) {
-  using T = typename Codec<ST>::T;
   constexpr bool kNb = Tile<ST, EDDY, KIN>::kNb;
-  const int halo = kNb ? 2 * k - 1 : k - 1;
-  const int w = RX - 2 * halo, h = RY - 2 * halo;
-  const int tiles_x = (g.nx + w - 1) / w, tiles_y = (g.ny + h - 1) / h;
-  const dim3 grid((tiles_x * tiles_y + 7) / 8 * 8), block(RX * RY / S);
-  auto* a = static_cast<const T*>(src);
-  auto* b = static_cast<T*>(dst);
   // the usual count of each kind is compiled for itself: unrolled, no value is
   // moved between registers from step to step (FP16 10-17% faster)
   constexpr int kFull = !kNb ? 5 : (ST == LBMHD_FP32 || S == 1 ? 3 : 2);
-  const long long stride = (long long)(keep / sizeof(T));
   if (keep)
-    hipLaunchKernelGGL((k_tile<ST, EDDY, KIN, RX, RY, S, kTileKeep<kNb, S>, kNb ? 1 : 2>), grid,
-                       block, 0, s, a, b, g, r, c12, k, tiles_x, w, h, stride);
+    launch_tile_k<ST, EDDY, KIN, RX, RY, S, kTileKeep<kNb, S>, kNb ? 1 : 2>(src, dst, k, keep, g,
+                                                                            r, c12, s);
   else if (k == kFull)
-    hipLaunchKernelGGL((k_tile<ST, EDDY, KIN, RX, RY, S, kFull>), grid, block, 0, s, a, b, g, r,
-                       c12, k, tiles_x, w, h, stride);
+    launch_tile_k<ST, EDDY, KIN, RX, RY, S, kFull>(src, dst, k, keep, g, r, c12, s);
   else
-    hipLaunchKernelGGL((k_tile<ST, EDDY, KIN, RX, RY, S, 0>), grid, block, 0, s, a, b, g, r, c12,
-                       k, tiles_x, w, h, stride);
+    launch_tile_k<ST, EDDY, KIN, RX, RY, S, 0>(src, dst, k, keep, g, r, c12, s);
+}
+
+// 64 x 32 sites, four a thread, for launches of four and five steps of large
+// lattices (no neighbour terms): a wave is a row of 64 columns, of which fewer
+// are halo (1.4 lanes issue for each site that counts, 1.6 with 32 x 32).
+// FP32 passes the planes in two parts through 64 KB of LDS, so that two blocks
+// share a CU here too (all at once, one block: 89k MLUPS at 4096^2 against 119k).
+// us per step of five, 32 x 32 / 64 x 32: FP32 1200^2 13.1 / 13.2, 1448^2 20.1 /
+// 18.7, 2048^2 39.1 / 36.2, 4096^2 155 / 130, 8192^2 606 / 504; FP16 2048^2 31.6 /
+// 31.2, 2500^2 48.1 / 46.6, 4096^2 129 / 116, 8192^2 535 / 461.  Keeping every
+// second state FP32 1024^2 17.6 / 16.1, 1200^2 26.3 / 24.2, 724^2 8.7 / 8.7.
+// Not faster: six steps (FP32 4096^2 132), four parts or six sites a thread
+// (more than 128 registers a lane: 220).
+static bool tile_wide(int storage, int k, bool keep, const Geom& g) {
+  const double sites = double(g.nx) * g.ny;
+  if (keep) return storage == LBMHD_FP32 && sites >= 8e5;
+  return (k == 4 || k == 5) && sites >= (storage == LBMHD_FP32 ? 1.6e6 : 5e6);
+}
+
+template <int ST, int EDDY>
+static void launch_tile_wide(const void* src, void* dst, int k, size_t keep, const Geom& g,
+                             const Rates& r, float c12, hipStream_t s) {
+  constexpr int PH = ST == LBMHD_FP32 ? 2 : 1;
+  if (keep) {
+    if constexpr (ST == LBMHD_FP32)
+      launch_tile_k<ST, EDDY, false, 64, 32, 4, 4, 2, PH>(src, dst, k, keep, g, r, c12, s);
+  } else if (k == 5) {
+    launch_tile_k<ST, EDDY, false, 64, 32, 4, 5, 0, PH>(src, dst, k, keep, g, r, c12, s);
+  } else {
+    launch_tile_k<ST, EDDY, false, 64, 32, 4, 4, 0, PH>(src, dst, k, keep, g, r, c12, s);
+  }
 }
 
 template <int ST, int EDDY, bool KIN>
 static void launch_tile_c(const void* src, void* dst, int k, size_t keep, const Geom& g,
                           const Rates& r, float c12, hipStream_t s) {
+  if constexpr (!Tile<ST, EDDY, KIN>::kNb)
+    if (tile_wide(ST == LBMHD_FP32 ? LBMHD_FP32 : LBMHD_FP16, k, keep > 0, g))
+      return launch_tile_wide<ST, EDDY>(src, dst, k, keep, g, r, c12, s);
   if (tile_small(g))
     launch_tile_r<ST, EDDY, KIN, 16, 16, 1>(src, dst, k, keep, g, r, c12, s);
   else
@@ -2149,9 +2207,9 @@ static double tile_size(const Geom& g) {
 }
 
 // Which launches go to tiles, us per step in tiles / by rows.  Five steps
-// always: FP32 1024^2 10.2 / 11.7 (k_step_t3), 2048^2 38 / 45, 4096^2 147 / 167,
-// 8192 x 4096 298 / 373; FP16 1024^2 9.2 / 12.9 (k_step), 4096^2 124 / 151
-// (k_step2), 8192 x 4096 247 / 289.  Neighbour terms, FP32: three steps 724^2
+// always: FP32 1024^2 10.2 / 11.7 (k_step_t3), 2048^2 36 / 45, 4096^2 130 / 167,
+// 8192 x 4096 252 / 373; FP16 1024^2 9.2 / 12.9 (k_step), 4096^2 116 / 151
+// (k_step2), 8192 x 4096 230 / 289.  Neighbour terms, FP32: three steps 724^2
 // 11.4 / 20.2 (k_step_nb2), 1300^2 34 / 40, 1448^2 45.1 / 44.5, 2048^2 89 / 73;
 // FP16: two steps 1024^2 17.9 / 35 (k_step_nb; three 19.3), 4096^2 237 / 268
 // (three 278).
@@ -2161,7 +2219,7 @@ int tile_steps(int storage, bool nb, const Geom& g) {
   return tile_size(g) < 1.6e6 ? 3 : 0;
 }
 
-// Fewer steps.  FP32: four 4096^2 171 / 234 (a triple and a single step), three
+// Fewer steps.  FP32: four 4096^2 154 / 234 (a triple and a single step), three
 // 1448^2 29.1 / 27.0 (k_step_t3), 4096^2 218 / 167, two 724^2 8.5 / 11.3 (k_step2),
 // 1024^2 14.3 / 14.2; FP16: three 4096^2 132 / 175, two 1448^2 16.6 / 25.3,
 // 2048^2 44.6 / 45.5, 4096^2 180 / 152; one with neighbour terms 1448^2
@@ -2174,7 +2232,7 @@ bool tile_short_pays(int storage, bool nb, int k, const Geom& g) {
 
 // Launches that keep states on the way, us per step against the launches that
 // keep one each.  Every second state: FP32 64^2 1.4 / 2.2, 512^2 4.5 / 5.7 (two
-// steps in tiles), 1024^2 17.4 / 19.2, 1448^2 37.4 / 37.6 (k_step2), 2048^2 72 / 66;
+// steps in tiles), 1024^2 16.1 / 19.2, 1200^2 24.2 / 29.9 (k_step2), 1448^2 38.5 / 37.0;
 // FP16 512^2 4.2 / 5.3, 1024^2 10.1 / 11.3, 2048^2 42.3 / 45.6 (k_step2), 2896^2 84
 // / 82 (eight steps a launch 20 / 20 at 1024^2 FP32, 60 / 46 at 2048^2 FP16).
 // Every state, neighbour terms: FP32 64^2 2.1 / 4.0 (one step in tiles), 512^2

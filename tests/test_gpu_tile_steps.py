@@ -1,11 +1,11 @@
-"""Several steps of a small lattice per launch (GPU), the automatic mode's tile kernel: equal
+"""Several steps of a lattice per launch (GPU), the automatic mode's tile kernel: equal
 to single steps bit for bit.
 
 A launch takes up to nine steps (three with neighbour terms) of a tile in LDS from a region of
-16 x 16, 32 x 32 or 32 x 28 sites.  The sizes take both regions and both sides of the line
+16 x 16, 32 x 32, 32 x 28 or 64 x 32 sites.  The sizes take both regions and both sides of the line
 between them, one tile and several with ragged ends, lattices smaller than the region (whose
 sites are periodic images of each other) and the step counts every split (one launch, even and
-uneven launches, a lone last step), then mid-size lattices where only whole launches are taken
+uneven launches, a lone last step), then larger lattices where only whole launches are taken
 and the remainder goes by rows.  The reference is the same library with steps_per_pass = 1.
 """
 import pytest
@@ -48,7 +48,8 @@ def test_tiles_equal_single_steps(nx, ny, les, storage):
 
 @pytest.mark.parametrize("nx,ny,les,storage", [
     (1000, 1100, 1, "fp32"), (2100, 1900, 1, "fp32"), (1400, 1300, 0, "fp16"),
-    (2100, 2000, 1, "fp16"), (900, 1000, 2, "fp32"), (2050, 1100, 2, "fp16"),
+    (2100, 2000, 1, "fp16"), (1300, 1301, 0, "fp32"), (2300, 2200, 0, "fp16"),
+    (2300, 2201, 1, "fp16"), (170000, 20, 1, "fp32"), (900, 1000, 2, "fp32"), (2050, 1100, 2, "fp16"),
     (1100, 1200, 4, "fp16")])
 def test_tiles_equal_single_steps_mid_sizes(nx, ny, les, storage):
     one, tile = lattices(nx, ny, les, storage)
