@@ -133,7 +133,9 @@ typedef struct {
                              storage and pairs with FP16 when the lattice is
                              large enough for that to pay (at least 512 tiles
                              of 8 rows by 256 FP32 or 512 FP16 columns, e.g.
-                             1024^2 FP32, 2048^2 FP16); 3 always takes
+                             1024^2 FP32, 2048^2 FP16), and before them what
+                             launches of several steps in tiles do faster
+                             (lbmhd_step); 3 always takes
                              triples with FP32 (pairs with FP16); 2 always
                              takes pairs.  Closures that read the neighbours'
                              moments (les = 2, 3, 4, 6): 0 takes pairs with
@@ -259,7 +261,9 @@ int lbmhd_step_between(lbmhd_t* h, const void* src, void* dst);
  * multiple of 256 and >= `lattice` bytes).  The same update as lbmhd_step,
  * launched from the library in one call: where lbmhd_step takes several
  * steps per pass, consecutive steps go in triples (FP32) or pairs here (with
- * FP16 storage only when steps_per_pass is 2 or more), a pass that reads
+ * FP16 storage only when steps_per_pass is 2 or more; with steps_per_pass = 0
+ * the closures that read the neighbours' moments in twos or threes in tiles on
+ * small and middling lattices), a pass that reads
  * state t - 1 once and writes all the states it computes (four lattice
  * transfers for three steps, three for two, instead of two per step).  The handle's current state and step count are untouched.  The
  * store range overlaps neither src nor the bound buffers.  Used to keep the
@@ -272,8 +276,8 @@ int lbmhd_step_store(lbmhd_t* h, const void* src, void* store, size_t stride, in
  * stride bytes (device; stride a multiple of 256 and >= `lattice` bytes), the
  * odd states are never written.  Each pair, with automatic steps_per_pass on
  * small and middling lattices each two pairs, is one pass over the lattice, and
- * the result equals 2 npairs single steps bit for bit.  The handle's current state and step count are
- * untouched; the store range overlaps neither src nor the bound buffers.
+ * the result equals 2 npairs single steps bit for bit.  The handle's current
+ * state and step count are untouched; the store range overlaps neither src nor the bound buffers.
  * Used to recompute a checkpoint segment for lbmhd_adj_sweep_pairs, which
  * needs only these states.  Asynchronous.  Errors as lbmhd_step_store. */
 int lbmhd_step_store_pairs(lbmhd_t* h, const void* src, void* store, size_t stride,
@@ -311,9 +315,11 @@ int lbmhd_diag(lbmhd_t* h, lbmhd_diag_t* out);
  * pass, which only reads that state; a pass that would overwrite a state still
  * being read waits for it on the bound stream.  Where lbmhd_step would end an
  * interval with a single step (FP32 storage, les = 0 or 1: e.g. intervals of
- * 3k + 1 steps taken in triples), that step and the diagnostics of its result
- * are one pass on the bound stream instead.  An in-place lattice takes its
- * diagnostics on the bound stream.  The reductions' block partials use the
+ * 3k + 1 steps taken in triples; with steps_per_pass = 0 any interval of a
+ * small lattice, FP16 storage up to 256 rows of 256 columns), that step and the
+ * diagnostics of its result are one pass on the bound stream instead.  An
+ * in-place lattice, and with steps_per_pass = 0 one below half a million
+ * sites, takes its diagnostics on the bound stream.  The reductions' block partials use the
  * bound workspace.
  *   dev   -- device memory, 8-byte aligned, of at least nout * 16 doubles,
  *            overlapping no bound buffer; diagnostics k is left in doubles

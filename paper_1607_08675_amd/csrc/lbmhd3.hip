@@ -725,21 +725,24 @@ size_t ws_doubles3(long long n) {
   return 7 * size_t(n) + size_t(lbk3::kReduceBlocks) * lbk3::kRed + 16;
 }
 // How the step kernel takes its sites and stores, by the bytes of the two
-// lattices.  Where they stay in the 256 MB last-level cache from step to step,
-// plain stores: they end there in whole lines, which the next step reads (us a
-// step, non-temporal / plain: 256 x 64 x 40 FP32 45 / 35, 90 x 60 x 70 29 / 24,
-// 96^3 FP16 47 / 41; 128^3 FP32 141 / 146, and 48 x 40 x 36 6.8 / 7.8, which the
-// L2s hold).  Sites in linear order where a row is no multiple of a block and
-// its rows end on cache lines (192^3 FP16 moment-space 290 / 263, 64 x 256 x 256
-// 196 / 158), and with FP16, bound by its arithmetic, wherever plain stores
-// are taken (96^3 57 / 39, 80 x 90 x 100 56 / 34); elsewhere its unaligned
+// lattices in whole cache lines.  Where they stay in the 256 MB last-level cache
+// from step to step, plain stores: they end there in whole lines, which the next
+// step reads (us a step, non-temporal / plain: FP32 256 x 64 x 40 45 / 35, 90 x 60 x
+// 70 29 / 24, 50 x 100 x 125 (288 MB of lines) 56 / 48, 50 x 100 x 135 (311 MB) 62 /
+// 65, 42 x 107 x 150 (370 MB) 65 / 76, 128^3 141 / 146; FP16 96^3 47 / 41, 42 x 130 x
+// 170 (254 MB) 60 / 46, 20 x 200 x 250 (576 MB) 151 / 164; FP32 48 x 40 x 36, which the
+// L2s hold, 6.8 / 7.8).  Sites in linear order where a row is no multiple of a
+// block and its rows end on cache lines (192^3 FP16 moment-space 290 / 263, 64 x
+// 256 x 256 196 / 158), and with FP16, bound by its arithmetic, wherever plain
+// stores are taken (96^3 57 / 39, 80 x 90 x 100 56 / 34); elsewhere its unaligned
 // stores cost more than the idle lanes (130^3 FP32 206 / 282).
 struct Order3 {
   bool lin, nt;
 };
 Order3 step3_order(const lbk3::Geom3& g, int esize) {
-  const double bytes = 2.0 * lbk3::kNPop * esize * g.nx * g.ny * g.nz;
-  const bool plain = bytes >= 50e6 && bytes <= (esize == 4 ? 320e6 : 200e6);
+  const double row = double((g.nx * esize + 127) / 128 * 128);
+  const double bytes = 2.0 * lbk3::kNPop * row * g.ny * g.nz;
+  const bool plain = bytes >= 50e6 && bytes <= 290e6;
   const bool lin = g.nx % lbk3::kThreads != 0 && bytes >= 50e6 &&
                    (g.nx * esize % 128 == 0 || (esize == 2 && plain));
   return Order3{lin, !plain};

@@ -105,7 +105,8 @@ hipError_t launch_two_steps(const lbmhd_t* h, const void* src, void* dst, void* 
   return lbk::launch_step2(h->p.storage, eddy == 1, src, dst, mid, h->geo, h->rates, h->stream);
 }
 
-// Steps that one kernel pass of lbmhd_step covers: 3 (FP32 only), 2 or 1.
+// Steps that one pass of the row-walking kernels covers: 3 (FP32 only), 2 or 1
+// (tile_most: the launches in tiles that the automatic mode takes before them).
 // Automatic: where the multi-step kernels fill the chip, triples for FP32
 // (measured faster than pairs from 1024^2 to 8192^2) and pairs for FP16; the
 // closures that read the neighbours' moments take pairs with FP32 storage (at
