@@ -7,15 +7,14 @@ stream-collide update on a 4096 x 4096 periodic Orszag-Tang vortex
 HBM, K timed steps with the FP64 diagnostics reduction run every 100 steps
 inside the timed region (one lbmhd_run call: each diagnostics pass overlaps
 the next kernel pass, and the host waits once, at the end, for all results).
-Steps go three per pass over the lattice (the
-intermediate states stay on chip; the results equal single steps bit for
-bit), so the dominant kernel moves 152 B per site per launch for three
-updates; the single-step kernel is timed beside it.  The same JSON line also reports the FP16-storage
-step on 8192 x 8192 decaying turbulence (nu = eta = 1e-6), the adjoint
+Steps go five per launch, in tiles of the lattice held on chip (the results
+equal single steps bit for bit), so the dominant kernel moves 152 B per site
+per launch for five updates; the single-step kernel is timed beside it.  The
+same JSON line also reports the FP16-storage step on 8192 x 8192 decaying turbulence (nu = eta = 1e-6), the adjoint
 (gradient of the final total energy after 2000 steps of a perturbed 1024 x 1024
 Orszag-Tang run, checkpoint interval from the free HBM), the adjoint-driven fit of C_S
-(2048^2 FP16 LES against a box-filtered 8192^2 FP32 run), the HBM roofline of
-the dominant kernel, and the FP64 CPU oracle timed on the host on the headline
+(2048^2 FP16 LES against a box-filtered 8192^2 FP32 run), the roofline of the
+dominant kernel (HBM and vector issue), and the FP64 CPU oracle timed on the host on the headline
 workload.
 
 Usage: python bench.py [--gpus 1] [--steps K] [--warmup W]
@@ -40,6 +39,9 @@ HBM_PEAK_GBS = 8000.0           # MI355X HBM3E, published
 FP32_BYTES_PER_SITE = 19 * 4 * 2
 FP16_BYTES_PER_SITE = 19 * 2 * 2
 ADJ_BYTES_PER_SITE = 19 * 4 * 2 + 3 * 19 * 4  # recompute step + (lam in, state gather, lam out)
+# steps of a launch of lbmhd_step in its automatic mode: in tiles without neighbour terms on
+# two lattices, by rows on one
+TILE_STEPS, INPLACE_STEPS = 5, 3
 COUNTERS_FILE = os.path.join(ROOT, "profiles", "counters_kernels.json")
 # VALU issue: 256 CUs x 4 SIMDs x 16 lanes, one lane-operation per lane and cycle, 2.4 GHz
 # (an FMA counted once; the 78.6 TFLOP/s FP32 figure counts it twice)
@@ -88,13 +90,14 @@ def valu_frac(key, ms_per_launch):
 
 def valu_roofline(key, ms_per_launch):
     """Roofline object of a kernel bound by its VALU issue rate: achieved lane
-    operations per second (counted instructions x 64 lanes, transcendentals
-    at four issue slots) against VALU_PEAK_TOPS."""
+    operations per second (counted instructions x 64 lanes) against
+    VALU_PEAK_TOPS, one instruction in flight per SIMD (a few overlap, so the
+    fraction can pass 1 by a percent or two)."""
     c = counters()
     if not c or key not in c["kernels"]:
         return None
     k = c["kernels"][key]
-    ops = (k["valu_insts"] + 3 * k["trans_insts"]) * 64
+    ops = k["valu_insts"] * 64
     achieved = ops / (ms_per_launch * 1e-3) / 1e12
     return {"kernel": k["kernel"], "bound": "alu", "achieved": round(achieved, 2),
             "peak": round(VALU_PEAK_TOPS, 2), "unit": "TOP/s (VALU lane operations)",
@@ -130,8 +133,8 @@ def warm_up(lat, steps):
 
 def burst_ms_per_step(torch, lat, steps):
     """Average time per step of `steps` back-to-back steps, from HIP events on
-    the lattice's stream (a kernel launch covers lat.steps_per_pass of them
-    when `steps` is even)."""
+    the lattice's stream (a whole number of kernel launches where `steps` is a
+    multiple of the steps a launch covers)."""
     s = lat.stream
     e0 = torch.cuda.Event(enable_timing=True)
     e1 = torch.cuda.Event(enable_timing=True)
@@ -166,8 +169,8 @@ def fp32_leg(torch, args):
     ms = timed_steps(torch, lat, args.steps, 100)
     wall = time.perf_counter() - t0
     d = lat.diag()
-    spp = lat.steps_per_pass
-    per_launch = burst_ms_per_step(torch, lat, 198) * spp   # 198 steps: 66 triples or 99 pairs
+    spp = TILE_STEPS
+    per_launch = burst_ms_per_step(torch, lat, 200) * spp
     # checkpoint of the final state: one plain copy kernel of lattice_bytes,
     # the reference size for calibrating HBM byte counters
     lat.save_state()
@@ -182,8 +185,7 @@ def fp32_leg(torch, args):
 
 def inplace_leg(torch, args):
     """The headline workload (4096^2 Orszag-Tang, FP32, LES) on one lattice
-    updated in place (AA pattern): an even number of back-to-back launches,
-    so the timing covers both step kinds equally and no layout pass."""
+    updated in place, three steps per pass by rows."""
     from lbmhd_inputs import orszag_tang
     from paper_1607_08675_amd.lattice import Lattice, LBMHDConfig
     n = 4096
@@ -193,13 +195,13 @@ def inplace_leg(torch, args):
     lat.init_fields(*orszag_tang(n, n))
     lat.step(2 * (args.warmup // 2))
     torch.cuda.synchronize()
-    per_launch = burst_ms_per_step(torch, lat, 200)
+    per_step = burst_ms_per_step(torch, lat, 66 * INPLACE_STEPS)
     d = lat.diag()
-    log(f"in-place 4096^2 FP32: {per_launch:.4f} ms/launch, nonfinite={d['nonfinite']}")
+    log(f"in-place 4096^2 FP32: {per_step:.4f} ms/step, nonfinite={d['nonfinite']}")
     mem = lat.lattice_bytes
     del lat
     torch.cuda.empty_cache()
-    return dict(per_launch=per_launch, sites=n * n, nonfinite=d["nonfinite"], lattice_bytes=mem)
+    return dict(per_step=per_step, sites=n * n, nonfinite=d["nonfinite"], lattice_bytes=mem)
 
 
 def threed_leg(torch, args):
@@ -281,8 +283,8 @@ def fp16_leg(torch, args):
         torch.cuda.synchronize()
         log(f"{st} 8192^2: timing {args.fp16_steps} steps")
         ms = timed_steps(torch, lat, args.fp16_steps, 100)
-        spp = lat.steps_per_pass
-        per_launch = burst_ms_per_step(torch, lat, 96) * spp   # 96: 48 pairs or 32 triples
+        spp = TILE_STEPS
+        per_launch = burst_ms_per_step(torch, lat, 100) * spp
         d = lat.diag()
         log(f"{st}: {ms / args.fp16_steps:.4f} ms/step, burst {per_launch:.4f} ms/launch of "
             f"{spp} steps, nonfinite={d['nonfinite']}")
@@ -347,8 +349,8 @@ def adjoint_leg(torch, args):
     out["grad_check"]["500"] = gradient_check(torch, cfg, fields, 500, run.backward(), (1e-3,))
     del run
     torch.cuda.empty_cache()
-    # the forward step as the forward run takes it (steps three per pass)
-    out["fwd_ms"] = burst_ms_per_step(torch, lat, 198)
+    # the forward step as the forward run takes it (steps five per pass)
+    out["fwd_ms"] = burst_ms_per_step(torch, lat, 200)
     # one reverse step alone
     st = lat.save_state()
     lam, lam2, acc = lat.new_adj_buffer(), lat.new_adj_buffer(), lat.new_adj_acc()
@@ -615,17 +617,16 @@ def main():
         "hbm_bytes_per_site_update": FP32_BYTES_PER_SITE / spp,
         "one_step_per_pass_bound_mlups": round(HBM_PEAK_GBS * 1e9 / FP32_BYTES_PER_SITE / 1e6, 1),
         "roofline": {
-            "kernel": {3: "k_step_t3<fp32,les>", 2: "k_step2<fp32,les>"}.get(spp, "k_step<fp32,les>"),
+            "kernel": "k_tile<fp32,les>",
             "bound": "hbm",
             "achieved": round(achieved, 1),
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBS, 4),
             "traffic": traffic,
-            "valu_frac": valu_frac("step_t3_fp32_4096", r32["per_launch"]),
-            "binding": "neither HBM nor VALU saturated (VALU ceiling 0.86x the HBM ceiling): "
-                       "9.5 waves per CU, each pass a chain of loads, three collisions and two "
-                       "barriers",
+            "valu_frac": valu_frac("tile_fp32_4096", r32["per_launch"]),
+            "binding": "vector issue (valu_frac, halo lanes included) before HBM: five steps "
+                       "per pass over HBM in tiles of 56 x 24 sites",
             "bytes_per_site": FP32_BYTES_PER_SITE,
             "steps_per_launch": spp,
             "ms_per_launch": round(r32["per_launch"], 5),
@@ -658,6 +659,11 @@ def main():
                           "oracle fixes about the reachable accuracy)",
         },
     }
+    head = valu_roofline("tile_fp32_4096", r32["per_launch"])
+    if head:   # its vector-issue ceiling is above the HBM one
+        line["roofline"].update({k: head[k] for k in ("bound", "achieved", "peak", "unit", "frac",
+                                                       "hbm_frac")})
+        line["roofline"]["hbm_achieved_gbs"] = round(achieved, 1)
     if r3:
         t32, t16 = r3["fp32"], r3["fp16"]
         m3 = r3["sites"] / (t32["per_launch"] * 1e-3) / 1e6
@@ -687,12 +693,14 @@ def main():
                 "frac": round(am / HBM_PEAK_GBS, 4), "nonfinite": tm["nonfinite"],
             }
     if rin:
-        mi = rin["sites"] / (rin["per_launch"] * 1e-3) / 1e6
-        ai = FP32_BYTES_PER_SITE * rin["sites"] / (rin["per_launch"] * 1e-3) / 1e9
+        ms_launch = rin["per_step"] * INPLACE_STEPS
+        mi = rin["sites"] / (rin["per_step"] * 1e-3) / 1e6
+        ai = FP32_BYTES_PER_SITE * rin["sites"] / (ms_launch * 1e-3) / 1e9
         line["inplace"] = {
             "workload": "Orszag-Tang 4096x4096, FP32, LES C_S=0.1, nu=eta=1e-5, one lattice "
-                        "updated in place (AA pattern)",
-            "mlups": round(mi, 1), "ms_per_step": round(rin["per_launch"], 5),
+                        "updated in place (three steps per pass by rows)",
+            "mlups": round(mi, 1), "ms_per_step": round(rin["per_step"], 5),
+            "steps_per_launch": INPLACE_STEPS, "ms_per_launch": round(ms_launch, 5),
             "achieved_gbs": round(ai, 1), "frac": round(ai / HBM_PEAK_GBS, 4),
             "bytes_per_site": FP32_BYTES_PER_SITE, "nonfinite": rin["nonfinite"],
             "state_bytes": rin["lattice_bytes"], "state_bytes_two_lattices": 2 * rin["lattice_bytes"],
@@ -735,7 +743,7 @@ def main():
                 "bytes_per_site": FP32_BYTES_PER_SITE, "steps_per_launch": f32["steps_per_pass"],
                 "nonfinite": f32["nonfinite"],
             },
-            "roofline": valu_roofline("step2_fp16_8192", f16["per_launch"]),
+            "roofline": valu_roofline("tile_fp16_8192", f16["per_launch"]),
             "speedup_vs_fp32_same_workload": round(m16 / m32, 3),
             "speedup_vs_fp32_headline": round(m16 / value, 3),
             "rel_l2_vs_fp32": {"step": args.fp16_compare_steps,
