@@ -1821,18 +1821,32 @@ __global__ __launch_bounds__(256) void k_diag_final(const double* __restrict__ p
   block_reduce<true>(v, red, out, int(threadIdx.x));
 }
 
-__global__ __launch_bounds__(256) void k_sum(const double* __restrict__ in, long long n,
-                                             double* __restrict__ out) {
-  __shared__ double sh[256];
-  double a = 0.0;
-  for (long long i = threadIdx.x; i < n; i += blockDim.x) a += in[i];
-  sh[threadIdx.x] = a;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
+// One block; the rounding errors of the additions are summed beside them
+// (Knuth's two-sum), so that the result does not depend on how the terms were
+// grouped into partials but for the last bit at most.
+constexpr int kSumThreads = 1024;
+__global__ __launch_bounds__(kSumThreads) void k_sum(const double* __restrict__ in, long long n,
+                                                     double* __restrict__ out) {
+#pragma clang fp contract(off) reassociate(off)
+  __shared__ double sh[kSumThreads], se[kSumThreads];
+  double a = 0.0, e = 0.0;
+  auto add = [&](double x) {
+    const double t = a + x, z = t - a;
+    e += (a - (t - z)) + (x - z);
+    a = t;
+  };
+  for (long long i = threadIdx.x; i < n; i += kSumThreads) add(in[i]);
+  for (int w = kSumThreads / 2; w > 0; w >>= 1) {
+    sh[threadIdx.x] = a;
+    se[threadIdx.x] = e;
+    __syncthreads();
+    if ((int)threadIdx.x < w) {
+      add(sh[threadIdx.x + w]);
+      e += se[threadIdx.x + w];
+    }
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[0] = sh[0];
+  if (threadIdx.x == 0) out[0] = isfinite(e) ? a + e : a;
 }
 
 inline unsigned blocks_for(long long n, int bs) { return unsigned((n + bs - 1) / bs); }
@@ -2504,12 +2518,12 @@ hipError_t launch_mismatch(int storage, const void* lat, const double* ux_t, con
   else
     hipLaunchKernelGGL(k_mismatch<LBMHD_FP16>, dim3(nparts), dim3(256), 0, s,
                        static_cast<const _Float16*>(lat), ux_t, uy_t, bx_t, by_t, part, g);
-  hipLaunchKernelGGL(k_sum, dim3(1), dim3(256), 0, s, part, (long long)nparts, out_dev);
+  hipLaunchKernelGGL(k_sum, dim3(1), dim3(kSumThreads), 0, s, part, (long long)nparts, out_dev);
   return hipGetLastError();
 }
 
 hipError_t launch_sum(const double* in, long long n, double* out_dev, hipStream_t s) {
-  hipLaunchKernelGGL(k_sum, dim3(1), dim3(256), 0, s, in, n, out_dev);
+  hipLaunchKernelGGL(k_sum, dim3(1), dim3(kSumThreads), 0, s, in, n, out_dev);
   return hipGetLastError();
 }
 
