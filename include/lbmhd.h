@@ -122,9 +122,10 @@ typedef struct {
                              a reversed lattice to the natural layout.  With
                              FP32 storage, steps_per_pass = 0 and three million
                              sites or more, two and three steps go in one pass
-                             on the natural layout, with copies of the rows
-                             and columns around its tiles and strips in the
-                             workspace (8% of the lattice at 4096^2). */
+                             on the natural layout where the caller gives room
+                             for copies of the rows and columns around its
+                             tiles and strips (lbmhd_bind_halos; 8% of the
+                             lattice at 4096^2, 22% at 2048^2). */
   int32_t steps_per_pass; /* How many steps lbmhd_step takes per pass over
                              the lattice when two lattices are bound, the
                              intermediate states staying on chip.  Closures
@@ -191,8 +192,7 @@ int lbmhd_destroy(lbmhd_t* h);
 /* Byte sizes the caller must allocate in device memory:
  *   lattice    -- one encoded population lattice (two are bound, one in place);
  *   workspace  -- scratch used by diagnostics, energy and reductions (block
- *                 partials and results, the same at any lattice size; in
- *                 place also the copies named above);
+ *                 partials and results, the same at any lattice size);
  *   adj_lattice -- one FP32 adjoint lattice (lambda), for the adjoint calls;
  *   adj_acc    -- the FP64 accumulator array of lbmhd_adj_step.
  * Any output pointer may be NULL. */
@@ -221,6 +221,20 @@ int lbmhd_layout(const lbmhd_t* h, int64_t* pitch, int64_t* plane, int64_t* adj_
  * Does not initialise the state.  Errors: LBMHD_ERR_INVALID_ARG. */
 int lbmhd_bind(lbmhd_t* h, void* lat_a, size_t lat_a_bytes, void* lat_b, size_t lat_b_bytes,
                void* workspace, size_t workspace_bytes, void* stream);
+
+/* Bytes of device memory with which lbmhd_step takes several steps per pass on
+ * an in-place lattice (see inplace above), 0 where this handle does not.  Host
+ * only.  Errors: LBMHD_ERR_INVALID_ARG for NULL arguments. */
+int lbmhd_halo_bytes(const lbmhd_t* h, size_t* out);
+
+/* Give a bound handle that memory: buf of at least lbmhd_halo_bytes bytes,
+ * 256-byte aligned, overlapping no bound buffer.  lbmhd_step writes it, so it
+ * serves no other handle whose steps may run at the same time (the
+ * workspace it does not use).  Without it, after lbmhd_bind or with buf =
+ * NULL, the lattice takes the alternating steps, to the same result bit for
+ * bit.  Ignored where lbmhd_halo_bytes is 0.  Errors: LBMHD_ERR_NOT_BOUND,
+ * LBMHD_ERR_INVALID_ARG (the handle then has no such memory). */
+int lbmhd_bind_halos(lbmhd_t* h, void* buf, size_t bytes);
 
 /* Set every site to the equilibria f^eq(rho, u, B) and g^eq(u, B) of Sec. 3
  * (the D2Q9 and D2Q5 relaxation distributions) computed in FP64, then encode

@@ -24,7 +24,8 @@ struct lbmhd {
   size_t lattice_bytes = 0, workspace_bytes = 0, adj_lattice_bytes = 0, adj_acc_bytes = 0;
   void* lat[2] = {nullptr, nullptr};
   double* ws = nullptr;
-  size_t halo_bytes = 0;   // in place: the halo copies at the workspace's end
+  size_t halo_bytes = 0;   // in place: room for the halo copies of several steps per pass
+  void* halo = nullptr;    // that room where the caller gave it
   hipStream_t stream = nullptr;
   bool bound = false;
   int cur = 0;  // index of the lattice holding the current state
@@ -424,7 +425,7 @@ int lbmhd_create(const lbmhd_params* p, lbmhd_t** out) {
   h->adj_lattice_bytes = size_t(lbk::kNPop) * size_t(ga.plane) * 4;
   if (p->inplace && p->steps_per_pass == 0 && p->storage == LBMHD_FP32)
     h->halo_bytes = lbk::inplace_halo_bytes(g);
-  h->workspace_bytes = round_up(workspace_doubles() * sizeof(double), kAlign) + h->halo_bytes;
+  h->workspace_bytes = round_up(workspace_doubles() * sizeof(double), kAlign);
   h->adj_acc_bytes = round_up(2 * size_t(lbk::adj_step_blocks(g)) * sizeof(double), kAlign);
   *out = h;
   return LBMHD_OK;
@@ -483,11 +484,32 @@ int lbmhd_bind(lbmhd_t* h, void* lat_a, size_t lat_a_bytes, void* lat_b, size_t 
   h->lat[0] = lat_a;
   h->lat[1] = lat_b;
   h->ws = static_cast<double*>(workspace);
+  h->halo = nullptr;
   h->stream = static_cast<hipStream_t>(stream);
   h->cur = 0;
   h->reversed = false;
   h->step = 0;
   h->bound = true;
+  return LBMHD_OK;
+}
+
+int lbmhd_halo_bytes(const lbmhd_t* h, size_t* out) {
+  if (!h || !out) return LBMHD_ERR_INVALID_ARG;
+  *out = h->halo_bytes;
+  return LBMHD_OK;
+}
+
+int lbmhd_bind_halos(lbmhd_t* h, void* buf, size_t bytes) {
+  if (int rc = need_bound(h)) return rc;
+  h->halo = nullptr;
+  if (!buf || h->halo_bytes == 0) return LBMHD_OK;
+  if (bytes < h->halo_bytes)
+    return fail(h, LBMHD_ERR_INVALID_ARG, "buffer smaller than lbmhd_halo_bytes() requires");
+  if (!aligned(buf)) return fail(h, LBMHD_ERR_INVALID_ARG, "buffers must be 256-byte aligned");
+  if (overlap(buf, h->halo_bytes, h->lat[0], h->lattice_bytes) ||
+      overlap(buf, h->halo_bytes, h->ws, h->workspace_bytes))
+    return fail(h, LBMHD_ERR_INVALID_ARG, "bound buffers overlap");
+  h->halo = buf;
   return LBMHD_OK;
 }
 
@@ -538,11 +560,10 @@ int inplace_steps(lbmhd_t* h, int64_t n) {
     if (int rc = inplace_one(h)) return rc;
     --n;
   }
-  void* halo = reinterpret_cast<char*>(h->ws) + (h->workspace_bytes - h->halo_bytes);
   while (n > 1) {
     const int k = n != 2 && n != 4 ? 3 : 2;
-    hipError_t e = lbk::launch_inplace_steps(eddy_of(h) == 1, k, h->lat[0], halo, h->geo, h->rates,
-                                             h->stream);
+    hipError_t e = lbk::launch_inplace_steps(eddy_of(h) == 1, k, h->lat[0], h->halo, h->geo,
+                                             h->rates, h->stream);
     if (e != hipSuccess) return hip_fail(h, e, "step launch");
     h->step += k;
     n -= k;
@@ -553,7 +574,7 @@ int inplace_steps(lbmhd_t* h, int64_t n) {
 int lbmhd_step(lbmhd_t* h, int64_t nsteps) {
   if (int rc = need_bound(h)) return rc;
   if (nsteps < 0) return fail(h, LBMHD_ERR_INVALID_ARG, "negative step count");
-  if (h->halo_bytes > 0) return inplace_steps(h, nsteps);
+  if (h->halo) return inplace_steps(h, nsteps);
   const bool les = (h->p.les & 1) && (h->p.cs > 0.0 || h->p.cs_b > 0.0);
   int64_t t = 0;
   const int ps = pass_steps(h);
@@ -642,6 +663,8 @@ int lbmhd_step_store(lbmhd_t* h, const void* src, void* store, size_t stride, in
   for (const void* b : {(const void*)h->lat[0], (const void*)h->lat[1], (const void*)h->ws})
     if (b && overlap(store, span, b, b == h->ws ? h->workspace_bytes : h->lattice_bytes))
       return fail(h, LBMHD_ERR_INVALID_ARG, "store overlaps a bound buffer");
+  if (h->halo && overlap(store, span, h->halo, h->halo_bytes))
+    return fail(h, LBMHD_ERR_INVALID_ARG, "store overlaps a bound buffer");
   if (int rc = natural(h, src)) return rc;
   const char* prev = static_cast<const char*>(src);
   char* out = static_cast<char*>(store);
@@ -704,6 +727,8 @@ int lbmhd_step_store_pairs(lbmhd_t* h, const void* src, void* store, size_t stri
   for (const void* b : {(const void*)h->lat[0], (const void*)h->lat[1], (const void*)h->ws})
     if (b && overlap(store, span, b, b == h->ws ? h->workspace_bytes : h->lattice_bytes))
       return fail(h, LBMHD_ERR_INVALID_ARG, "store overlaps a bound buffer");
+  if (h->halo && overlap(store, span, h->halo, h->halo_bytes))
+    return fail(h, LBMHD_ERR_INVALID_ARG, "store overlaps a bound buffer");
   if (int rc = natural(h, src)) return rc;
   const char* prev = static_cast<const char*>(src);
   char* out = static_cast<char*>(store);
@@ -821,6 +846,8 @@ int lbmhd_run(lbmhd_t* h, int64_t nsteps, int64_t every, double* dev, lbmhd_diag
       return fail(h, LBMHD_ERR_INVALID_ARG, "diagnostics buffer overlaps a bound lattice");
   if (overlap(dev, dev_bytes, h->ws, h->workspace_bytes))
     return fail(h, LBMHD_ERR_INVALID_ARG, "diagnostics buffer overlaps the workspace");
+  if (h->halo && overlap(dev, dev_bytes, h->halo, h->halo_bytes))
+    return fail(h, LBMHD_ERR_INVALID_ARG, "diagnostics buffer overlaps the bound halos");
   // an interval that lbmhd_step ends with a single step (FP32 storage, a
   // closure without neighbour terms) takes that step and the diagnostics of
   // its result in one pass on the bound stream; so does every interval of a

@@ -103,6 +103,16 @@ class Lattice:
                              0 if self._b is None else self.lattice_bytes, _ptr(self._ws),
                              self.workspace_bytes,
                              ctypes.c_void_p(self.stream.cuda_stream)), "lbmhd_bind", h)
+        self._halos = None
+        halo = ctypes.c_size_t()
+        C.check(L.lbmhd_halo_bytes(h, ctypes.byref(halo)), "lbmhd_halo_bytes", h)
+        if halo.value:
+            try:
+                self._halos = torch.empty(halo.value, dtype=torch.uint8, device=self.device)
+            except torch.OutOfMemoryError:
+                return   # the lattice steps without them, more slowly
+            C.check(L.lbmhd_bind_halos(h, _ptr(self._halos), halo.value), "lbmhd_bind_halos", h)
+            self.workspace_bytes += halo.value   # all scratch held beside the lattices
 
     def __del__(self):
         h = getattr(self, "_h", None)
