@@ -114,7 +114,7 @@ hipError_t launch_unswap_aa(int storage, void* lat, const Geom& g, hipStream_t s
 hipError_t launch_inplace_steps(bool les, int k, void* lat, void* halo, const Geom& g,
                                 const Rates& r, hipStream_t s);
 // Whether launch_inplace_steps beats the AA steps on this lattice, and the
-// bytes of its halo copies (0 where it does not).
+// bytes of its halo copies (0 where it does not or they outgrow a quarter of it).
 bool inplace_rows_pay(const Geom& g);
 size_t inplace_halo_bytes(const Geom& g);
 // Forward step that needs the neighbours' rho, j, B (lattice gradients):

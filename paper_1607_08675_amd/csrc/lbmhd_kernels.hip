@@ -2282,10 +2282,14 @@ static size_t halo_row_elems(const Geom& g) {
   return size_t((g.ny + rows - 1) / rows) * kNPop * 6 * g.pitch;
 }
 
+// At most a quarter of the lattice: six rows a strip are 3/16 of the strips of 32
+// rows but three lattices on two rows, where half the memory, which the mode is
+// for, would be lost.
 size_t inplace_halo_bytes(const Geom& g) {
   if (!inplace_rows_pay(g)) return 0;
   const size_t cols = size_t((g.nx + kT2Threads - 1) / kT2Threads) * kNPop * g.ny * 8;
-  return (halo_row_elems(g) + cols) * sizeof(float) / 256 * 256 + 256;
+  const size_t bytes = (halo_row_elems(g) + cols) * sizeof(float) / 256 * 256 + 256;
+  return bytes <= kNPop * size_t(g.plane) * sizeof(float) / 4 ? bytes : 0;
 }
 
 template <bool LES>

@@ -53,3 +53,19 @@ def test_two_handles_share_one_workspace():
         got = stored_words(L)
         torch.cuda.synchronize()
         assert torch.equal(stored_words(r), got)
+
+
+# strips of 28 rows, a last strip of one row, two strips of uneven heights; six rows, which the
+# copies would outgrow
+@pytest.mark.parametrize("nx,ny,rows", [(110000, 28, True), (15600, 193, True),
+                                        (50000, 97, True), (500000, 6, False)])
+def test_low_wide_lattices_in_place(nx, ny, rows):
+    from paper_1607_08675_amd.lattice import Lattice, LBMHDConfig
+    f = random_fields(nx, ny, seed=nx + ny, rho_amp=0.004, u_amp=0.02, b_amp=0.02)
+    two = Lattice(LBMHDConfig(**{**KW, "nx": nx, "ny": ny}, steps_per_pass=1)).init_fields(*f)
+    one = Lattice(LBMHDConfig(**{**KW, "nx": nx, "ny": ny}, inplace=True)).init_fields(*f)
+    assert (one._halos is not None) == rows
+    for n in (5, 4, 1, 3):
+        two.step(n)
+        one.step(n)
+    assert torch.equal(stored_words(two), stored_words(one))

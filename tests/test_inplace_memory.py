@@ -56,3 +56,13 @@ def test_binding_the_room_for_copies(capi):  # noqa: F811
         assert L.lbmhd_bind(h, LAT, lat, None, 0, WS, ws, None) == 0
         assert L.lbmhd_bind_halos(h, HALO, 0) == 0
         assert L.lbmhd_destroy(h) == 0
+
+
+@pytest.mark.parametrize("nx,ny,rows", [
+    (4096, 4096, True), (2048, 1500, True), (16384, 190, True), (257, 11800, True),
+    (110000, 28, True), (15600, 193, True), (120000, 33, True), (1600000, 2, False),
+    (500000, 6, False), (200000, 16, False)])
+def test_copies_stay_below_a_quarter_of_the_lattice(capi, nx, ny, rows):  # noqa: F811
+    h, lat, _, halo = handle(capi, nx=nx, ny=ny, inplace=1)
+    assert (halo > 0) == rows and 4 * halo <= lat
+    assert capi.lib().lbmhd_destroy(h) == 0
