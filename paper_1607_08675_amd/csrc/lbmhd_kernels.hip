@@ -1877,9 +1877,12 @@ void with_bools(F&& f, bool b, More... more) {
 // FP32 31 / 22, 2048 x 1024 FP16 34 / 22, k_step_t3 1280 x 1024 17.7 / 14.3, k_step2
 // 1024^2 18.2 / 14.1, k_step_nb2 23.7 / 21.8; beyond it (1448^2 FP32, 318 MB)
 // k_step_t3 26.8 / 27.8 and k_step_nb2 44.6 / 46.4, and in the L2s (512^2 FP16,
-// 20 MB) k_step 6.2 / 6.8.
-static bool stores_bypass(const Geom& g, size_t esize) {
-  const double bytes = 2.0 * kNPop * double(esize) * g.nx * g.ny;
+// 20 MB) k_step 6.2 / 6.8.  Counted in the 128-byte lines that the rows take, which
+// is what the cache holds of narrow lattices (16 x 100000 FP16, 61 MB of sites in
+// 486 MB of lines: 98 / 131; 72 x 40000 65 / 76).
+bool stores_bypass(const Geom& g, size_t esize) {
+  const double row = double((size_t(g.nx) * esize + 127) / 128 * 128);
+  const double bytes = 2.0 * kNPop * row * g.ny;
   return bytes < 30e6 || bytes > 240e6;
 }
 

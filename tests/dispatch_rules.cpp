@@ -1,0 +1,15 @@
+// The library's rules on lattice sizes behind C names, for tests on the host.
+#include "lbmhd_impl.h"
+
+static lbk::Geom geom(int nx, int ny, int esize) {
+  lbk::Geom g;
+  g.nx = nx;
+  g.ny = ny;
+  g.pitch = (nx * esize + 255) / 256 * 256 / esize;
+  g.plane = (long long)g.pitch * ny + 768 / esize;
+  return g;
+}
+
+extern "C" int rule_stores_bypass(int nx, int ny, int esize) {
+  return lbk::stores_bypass(geom(nx, ny, esize), size_t(esize));
+}

@@ -1,0 +1,39 @@
+"""The rules that choose kernels by the lattice's size (host only, nothing is launched).
+
+tests/dispatch_rules.cpp is built against the library and gives its rules C names.
+"""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from conftest import ROOT
+
+FP32, FP16 = 0, 1
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    from paper_1607_08675_amd import _capi, build
+    if not os.path.exists(_capi.LIB_PATH):
+        build.build()
+    if not shutil.which("g++") or not os.path.exists("/opt/rocm/include/hip/hip_runtime.h"):
+        pytest.skip("g++ or the HIP headers missing")
+    out = str(tmp_path_factory.mktemp("rules") / "rules.so")
+    pkg = os.path.dirname(_capi.LIB_PATH)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__",
+                    "-I", "/opt/rocm/include", "-I", os.path.join(ROOT, "include"),
+                    "-I", os.path.join(pkg, "csrc"),
+                    os.path.join(ROOT, "tests", "dispatch_rules.cpp"), _capi.LIB_PATH,
+                    "-Wl,-rpath," + pkg, "-o", out], check=True)
+    return ctypes.CDLL(out)
+
+
+@pytest.mark.parametrize("nx,ny,esize,bypass", [
+    (1024, 1024, 4, 0), (1448, 1448, 4, 1), (512, 512, 2, 1), (1021, 767, 4, 0),
+    # narrow rows: few sites, many lines
+    (16, 100000, 2, 1), (2, 100000, 4, 1), (33, 70000, 2, 1), (72, 40000, 2, 1)])
+def test_stores_by_the_lines_that_the_rows_take(rules, nx, ny, esize, bypass):
+    assert rules.rule_stores_bypass(nx, ny, esize) == bypass
