@@ -86,14 +86,15 @@ int tile_keep(const lbmhd_t* h) {
   return lbk::tile_keep(nb, h->geo);
 }
 
-// One step src -> dst with the handle's closure.
-hipError_t launch_one_step(const lbmhd_t* h, const void* src, void* dst) {
+// One step src -> dst with the handle's closure (kept: dst is one of many states
+// written in a row).
+hipError_t launch_one_step(const lbmhd_t* h, const void* src, void* dst, bool kept = false) {
   const int eddy = eddy_of(h);
   if (reads_neighbours(h) && tile_short(h, 1)) return launch_tile_steps(h, src, dst, 1);
   if (reads_neighbours(h))
     return lbk::launch_step_nb(h->p.storage, eddy, (h->p.les & 2) != 0, src, dst, h->geo,
                                h->rates, h->p.delta, h->stream);
-  return lbk::launch_step(h->p.storage, eddy == 1, src, dst, h->geo, h->rates, h->stream);
+  return lbk::launch_step(h->p.storage, eddy == 1, src, dst, h->geo, h->rates, h->stream, kept);
 }
 
 // Two steps src -> dst in one pass (mid: also the state between them).
@@ -702,7 +703,7 @@ int lbmhd_step_store(lbmhd_t* h, const void* src, void* store, size_t stride, in
     }
   }
   for (; t < n; ++t) {
-    hipError_t e = launch_one_step(h, prev, out);
+    hipError_t e = launch_one_step(h, prev, out, true);
     if (e != hipSuccess) return hip_fail(h, e, "step launch");
     prev = out;
     out += stride;

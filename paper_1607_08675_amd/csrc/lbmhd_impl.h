@@ -88,9 +88,9 @@ constexpr int kDiagBlocks = 4096; // partials in the workspace (one per reducing
 
 // Forward step: dst = C(S(src)).
 hipError_t launch_step(int storage, bool les, const void* src, void* dst, const Geom& g,
-                       const Rates& r, hipStream_t s);
+                       const Rates& r, hipStream_t s, bool kept = false);
 // Whether the row-walking step kernels store past the caches (non-temporal).
-bool stores_bypass(const Geom& g, size_t esize);
+bool stores_bypass(const Geom& g, size_t esize, bool kept = false);
 // Two forward steps in one pass: dst = C(S(C(S(src)))), equal to two
 // launch_step calls; with mid != nullptr the intermediate state C(S(src)) is
 // stored there as well.  src, dst and mid must not overlap.

@@ -1880,15 +1880,20 @@ void with_bools(F&& f, bool b, More... more) {
 // 20 MB) k_step 6.2 / 6.8.  Counted in the 128-byte lines that the rows take, which
 // is what the cache holds of narrow lattices (16 x 100000 FP16, 61 MB of sites in
 // 486 MB of lines: 98 / 131; 72 x 40000 65 / 76).
-bool stores_bypass(const Geom& g, size_t esize) {
+// A state that is kept (dst one of many, lbmhd_step_store) leaves the cache to
+// those after it, so from 80 MB on it goes past: us per state, non-temporal / plain,
+// FP32 1024^2 (three states a pass) 21.4 / 26.6, 1000^2 (one) 29.4 / 34.8, 800^2 (97
+// MB) 20.7 / 20.2, 724^2 16.3 / 15.7, 640^2 (62 MB) 13.7 / 11.6; FP16 1500^2 35.3 /
+// 38.7, 1100^2 (92 MB) 21.0 / 22.4, 1024^2 (80 MB) 16.8 / 14.4.
+bool stores_bypass(const Geom& g, size_t esize, bool kept) {
   const double row = double((size_t(g.nx) * esize + 127) / 128 * 128);
   const double bytes = 2.0 * kNPop * row * g.ny;
-  return bytes < 30e6 || bytes > 240e6;
+  return bytes < 30e6 || bytes > (kept ? 80e6 : 240e6);
 }
 
 template <int ST, int V>
 void launch_step_v(bool les, const void* src, void* dst, const Geom& g, const Rates& r,
-                   hipStream_t s) {
+                   hipStream_t s, bool kept) {
   using T = typename Codec<ST>::T;
   const int tiles_x = (g.nx / V + kStepThreads - 1) / kStepThreads;
   const dim3 grid(unsigned(tiles_x) * unsigned(g.ny)), block(kStepThreads);
@@ -1896,7 +1901,7 @@ void launch_step_v(bool les, const void* src, void* dst, const Geom& g, const Ra
   auto* b = static_cast<T*>(dst);
   with_bools([&](auto l, auto nt) {
     hipLaunchKernelGGL((k_step<ST, V, l(), nt()>), grid, block, 0, s, a, b, g, r, tiles_x);
-  }, les, stores_bypass(g, sizeof(T)));
+  }, les, stores_bypass(g, sizeof(T), kept));
 }
 
 // Strips of the two-step kernel, measured on MI355X: FP32 runs best with about
@@ -1925,7 +1930,7 @@ void launch_step2_v(bool les, const void* src, void* dst, void* mid, const Geom&
   with_bools([&](auto l, auto md, auto nt) {
     hipLaunchKernelGGL((k_step2<ST, V, l(), md(), false, nt()>), grid, block, 0, s, a, b, m, g, r,
                        tiles_x, h, xcd, none);
-  }, les, m != nullptr, stores_bypass(g, sizeof(T)));
+  }, les, m != nullptr, stores_bypass(g, sizeof(T), m != nullptr));
 }
 
 template <int ST, int EDDY, bool KIN>
@@ -1977,7 +1982,7 @@ void launch_step_nb2_t(const void* src, void* dst, void* mid, const Geom& g, con
   with_bools([&](auto md, auto nt) {
     hipLaunchKernelGGL((k_step_nb2<ST, EDDY, KIN, md(), nt()>), grid, block, 0, s, a, b, m, g, r,
                        c12, tiles_x, h, xcd);
-  }, m != nullptr, stores_bypass(g, sizeof(T)));
+  }, m != nullptr, stores_bypass(g, sizeof(T), m != nullptr));
 }
 
 template <int ST>
@@ -2018,13 +2023,13 @@ hipError_t launch_step_nb(int storage, int eddy, bool kin, const void* src, void
 }
 
 hipError_t launch_step(int storage, bool les, const void* src, void* dst, const Geom& g,
-                       const Rates& r, hipStream_t s) {
+                       const Rates& r, hipStream_t s, bool kept) {
   if (storage == LBMHD_FP32)
-    launch_step_v<LBMHD_FP32, 1>(les, src, dst, g, r, s);
+    launch_step_v<LBMHD_FP32, 1>(les, src, dst, g, r, s, kept);
   else if (g.nx % 2 == 0)
-    launch_step_v<kFP16S, 2>(les, src, dst, g, r, s);
+    launch_step_v<kFP16S, 2>(les, src, dst, g, r, s, kept);
   else
-    launch_step_v<kFP16S, 1>(les, src, dst, g, r, s);
+    launch_step_v<kFP16S, 1>(les, src, dst, g, r, s, kept);
   return hipGetLastError();
 }
 
@@ -2058,7 +2063,7 @@ hipError_t launch_step_t3(bool les, const void* src, void* dst, void* mid1, void
   with_bools([&](auto l, auto md, auto nt) {
     hipLaunchKernelGGL((k_step_t3<l(), md(), false, nt()>), grid, block, 0, s, a, b, m1, m2, g, r,
                        tiles_x, h, xcd, none);
-  }, les, m1 != nullptr, stores_bypass(g, 4));
+  }, les, m1 != nullptr, stores_bypass(g, 4, m1 != nullptr));
   return hipGetLastError();
 }
 

@@ -10,6 +10,6 @@ static lbk::Geom geom(int nx, int ny, int esize) {
   return g;
 }
 
-extern "C" int rule_stores_bypass(int nx, int ny, int esize) {
-  return lbk::stores_bypass(geom(nx, ny, esize), size_t(esize));
+extern "C" int rule_stores_bypass(int nx, int ny, int esize, int kept) {
+  return lbk::stores_bypass(geom(nx, ny, esize), size_t(esize), kept != 0);
 }

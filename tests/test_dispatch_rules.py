@@ -36,4 +36,11 @@ def rules(tmp_path_factory):
     # narrow rows: few sites, many lines
     (16, 100000, 2, 1), (2, 100000, 4, 1), (33, 70000, 2, 1), (72, 40000, 2, 1)])
 def test_stores_by_the_lines_that_the_rows_take(rules, nx, ny, esize, bypass):
-    assert rules.rule_stores_bypass(nx, ny, esize) == bypass
+    assert rules.rule_stores_bypass(nx, ny, esize, 0) == bypass
+
+
+@pytest.mark.parametrize("nx,ny,esize,bypass", [
+    (1024, 1024, 4, 1), (1000, 1000, 4, 1), (1500, 1500, 2, 1), (1100, 1100, 2, 1),
+    (640, 640, 4, 0), (1024, 1024, 2, 0), (512, 512, 4, 0), (100, 100, 4, 1)])
+def test_kept_states_go_past_the_cache_that_they_outgrow(rules, nx, ny, esize, bypass):
+    assert rules.rule_stores_bypass(nx, ny, esize, 1) == bypass
