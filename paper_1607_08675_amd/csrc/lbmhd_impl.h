@@ -69,16 +69,23 @@ inline Strips strips_of(int rows, int ny, int idle = 8) {
 // About `want` blocks, never more while strips of `lo` rows allow it: a few
 // blocks over an even round leave some CUs a round of their own.  Strips
 // taller than `hi` become `big` rows (many rounds; there idle strips cost more
-// than the order by XCDs gives, 2% at 5990 x 3900).  ms per step, rows rounded down and plain order /
+// than the order by XCDs gives, 2% at 5990 x 3900).  ms per step, rows rounded
+// down and plain order /
 // this rule: k_step_t3 1448^2 0.0326 / 0.0272, 2500^2 0.089 / 0.070,
 // 5000 x 3000 0.186 / 0.156; k_step_nb2 0.064 / 0.044, 0.166 / 0.110,
 // 0.345 / 0.242; k_adj_step2 0.086 / 0.065, 0.251 / 0.175, 0.530 / 0.409;
 // 2048^2 and 4096^2, which split evenly, as before.
-inline Strips split_rows(long long tiles_x, int ny, int want, int lo, int hi, int big) {
+// One strip of up to two thirds of `want` tiles, a block on most CUs and two on
+// some, becomes `few` (us per step, one strip / four: k_step_t3 70000 x 33 38.9 /
+// 32.4, 80000 x 100 108 / 95, k_step_nb2 184 / 145 and 186 / 157 at 100 rows,
+// k_adj_step2 281 / 216; 100000 columns, 391 tiles, 109 / 111, 188 / 195, 295 / 302).
+inline Strips split_rows(long long tiles_x, int ny, int want, int lo, int hi, int big,
+                         int few = 4) {
   long long n = want / tiles_x;
   n = n >= 8 ? n / 8 * 8 : (n > 1 ? n : 1);
-  const long long rows = (ny + n - 1) / n;
+  long long rows = (ny + n - 1) / n;
   if (rows > hi) return strips_of(big, ny, 0);
+  if (tiles_x > want / 2 && tiles_x <= want * 2 / 3) rows = (ny + few - 1) / few;
   return strips_of(int(rows < lo ? lo : rows), ny);
 }
 

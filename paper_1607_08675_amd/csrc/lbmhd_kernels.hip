@@ -2269,7 +2269,7 @@ bool tile_keep_pays(int storage, bool nb, const Geom& g) {
 // Strips of 32 to 128 rows and tiles of 256 columns: the copies are
 // 6 / rows + 8 / 256 of the lattice (8% at 4096^2).
 static Strips halo_strips(const Geom& g) {
-  return split_rows((g.nx + kT2Threads - 1) / kT2Threads, g.ny, 512, 32, 128, 128);
+  return split_rows((g.nx + kT2Threads - 1) / kT2Threads, g.ny, 512, 32, 128, 128, 1);
 }
 
 // Against the AA steps, us per step: 2048 x 1024 46.3 / 46.3 by rows, 2048^2

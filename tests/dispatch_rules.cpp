@@ -13,3 +13,8 @@ static lbk::Geom geom(int nx, int ny, int esize) {
 extern "C" int rule_stores_bypass(int nx, int ny, int esize, int kept) {
   return lbk::stores_bypass(geom(nx, ny, esize), size_t(esize), kept != 0);
 }
+
+// Rows of a strip for `tiles` tiles of columns.
+extern "C" int rule_strip_rows(int tiles, int ny, int want, int lo, int hi, int big) {
+  return lbk::split_rows(tiles, ny, want, lo, hi, big).rows;
+}

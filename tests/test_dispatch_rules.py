@@ -44,3 +44,12 @@ def test_stores_by_the_lines_that_the_rows_take(rules, nx, ny, esize, bypass):
     (640, 640, 4, 0), (1024, 1024, 2, 0), (512, 512, 4, 0), (100, 100, 4, 1)])
 def test_kept_states_go_past_the_cache_that_they_outgrow(rules, nx, ny, esize, bypass):
     assert rules.rule_stores_bypass(nx, ny, esize, 1) == bypass
+
+
+@pytest.mark.parametrize("tiles,ny,rows", [
+    (274, 33, 9), (274, 100, 25), (341, 40, 10), (274, 24, 8), (274, 2, 8),   # four strips
+    (274, 250, 32),                               # taller than 128 rows: many rounds
+    (342, 40, 40), (391, 33, 33), (469, 100, 100),   # one strip nearly fills a round
+    (256, 40, 20), (196, 100, 50), (169, 40, 14), (16, 4096, 128), (8, 2048, 32)])
+def test_one_strip_does_not_leave_half_the_card(rules, tiles, ny, rows):
+    assert rules.rule_strip_rows(tiles, ny, 512, 8, 128, 32) == rows
