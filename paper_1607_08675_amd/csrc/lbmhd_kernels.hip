@@ -838,8 +838,16 @@ __global__ __launch_bounds__(kNb2Threads) __attribute__((amdgpu_waves_per_eu(4))
     tile = int(blockIdx.x) % tiles_x;
     strip = int(blockIdx.x) / tiles_x;
   }
+  // Kinetic closure with FP32 states: the next pass's first gather is issued
+  // right after this pass's first barrier and flies during stages 2 to 4
+  // (66.5k against 62.4k MLUPS at 4096^2, 62.8k against 57.9k with les = 3,
+  // same results); the cross-helicity closure's registers spill with it
+  // (29.7k against 54.6k).
+  constexpr bool kPf = ST == LBMHD_FP32 && EDDY != 2;
   const int x0 = tile * W, y0 = strip * rows;
-  if (y0 >= ny) return;
+  // a strip past the lattice; those without kPf return below, as fast as without
+  // the test (FP16, kinetic closure, 64^2: 15.8 us per step, 17.0 from here)
+  if (kPf && y0 >= ny) return;
   const int wt = min(W, nx - x0), h = min(rows, ny - y0);
   // the thread's column: its own (threads 0 .. W - 1) or a halo column
   // (lanes 0 .. 5 of the fifth wave: x0 - 3 .. x0 - 1, x0 + wt .. x0 + wt + 2)
@@ -873,12 +881,6 @@ __global__ __launch_bounds__(kNb2Threads) __attribute__((amdgpu_waves_per_eu(4))
   for (int k = 0; k < 6; ++k) x1c[k] = 0.0f;
 #pragma unroll
   for (int k = 0; k < 2; ++k) x1u1[k] = x1u2[k] = 0.0f;
-  // Kinetic closure with FP32 states: the next pass's first gather is issued
-  // right after this pass's first barrier and flies during stages 2 to 4
-  // (66.5k against 62.4k MLUPS at 4096^2, 62.8k against 57.9k with les = 3,
-  // same results); the cross-helicity closure's registers spill with it
-  // (29.7k against 54.6k).
-  constexpr bool kPf = ST == LBMHD_FP32 && EDDY != 2;
   float pf[kNPop][1];
   // rows y0 - 3 .. y0 + h + 2: more than one period on a lattice two rows high
   auto gather_at = [&](int r, float (&v)[kNPop][1]) {
@@ -888,6 +890,7 @@ __global__ __launch_bounds__(kNb2Threads) __attribute__((amdgpu_waves_per_eu(4))
     t2_rows(a, geo, row);
     gather_row<ST, 1>(src, P, xc, xl, xr, row, v);
   };
+  if (!kPf && h <= 0) return;
   if (kPf && has) gather_at(y0 - 3, pf);
   for (int t = 0; t < h + 6; ++t) {
     const int s0 = t % 3;                         // ring slot of this pass
