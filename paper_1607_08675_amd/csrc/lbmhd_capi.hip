@@ -922,7 +922,7 @@ int lbmhd_run(lbmhd_t* h, int64_t nsteps, int64_t every, double* dev, lbmhd_diag
 int lbmhd_diag_noalloc(lbmhd_t* h, lbmhd_diag_t* out) {
   if (int rc = need_bound(h)) return rc;
   if (!out) return fail(h, LBMHD_ERR_INVALID_ARG, "null output");
-  if (size_t(lbk::diag_partials(h->geo)) > kScratchParts)
+  if (size_t(lbk::diag_partials(h->p.storage, h->geo)) > kScratchParts)
     return fail(h, LBMHD_ERR_UNSUPPORTED, "more reduction partials than the static scratch holds");
   double* s = nullptr;
   if (int rc = scratch_address(h, &s)) return rc;

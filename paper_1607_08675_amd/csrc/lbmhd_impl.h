@@ -181,7 +181,9 @@ bool diag_by_row(const Geom& g);
 hipError_t launch_step_diag(int storage, bool les, const void* src, void* dst, double* part,
                             double* out_dev, const Geom& g, const Rates& r, hipStream_t s);
 // Number of block partials launch_diag writes for this lattice (<= kDiagBlocks).
-int diag_partials(const Geom& g);
+int diag_partials(int storage, const Geom& g);
+// Rows of a strip of both passes.
+int diag_rows(int storage, const Geom& g);
 
 // Box-averaged macroscopic fields (w x w blocks).
 hipError_t launch_macro_box(int storage, const void* lat, int w, double* rho, double* ux,

@@ -1750,7 +1750,7 @@ __global__ __launch_bounds__(kDiagThreads) void k_step_diag(const float* __restr
   diag_partial(v, mac, part);
 }
 
-// Both where a strip is a single row (diag_rows): the three rows of the ring at
+// Both where each row has a block (diag_by_row): the three rows of the ring at
 // once, 256 threads each and six lanes of a last wave for the halo columns,
 // so that the chain is one gather, one collision and the moments' FP64 work
 // instead of three of each.  The row's sums are taken as above, so the partials
@@ -2437,38 +2437,44 @@ hipError_t launch_copy(const void* src, void* dst, size_t bytes, hipStream_t s) 
   return hipGetLastError();
 }
 
-// Strip height of the diagnostics passes.  A block takes its rows one after
-// another (about 1.9 us a row, the latency of the loads and of the FP64
-// chain), so a strip is only as tall as leaves about 1024 of them.  64-row
-// strips on every lattice against this rule: k_step_diag 121 and 10.6 us at
-// 64^2 (one block and 64), 132 and 11.9 us at 256^2, k_diag 82 and 31 us at
-// 1024^2 (4 rows).  On the largest lattices 64 rows are 8-11% faster than 16
-// (two halo rows a strip).
-static int diag_rows(const Geom& g) {
-  const long long tiles_x = (g.nx + kDiagThreads - 1) / kDiagThreads;
-  return int(std::max<long long>(1, std::min<long long>(kDiagRows, tiles_x * g.ny / 1024)));
+// Strips of the diagnostics passes.  A block takes its rows one after another
+// (about 1.9 us a row, the latency of the loads and of the FP64 chain), so a
+// strip is as short as leaves whole strips for 512 blocks with FP32 storage and
+// 1024 with FP16, which has half the bytes in flight a row; never a few blocks
+// over that, which would run a round of their own.  us of lbmhd_diag, 64-row
+// strips / 1024 strips rounded up / this rule: FP32 512^2 106 / 45 / 40, 1024^2 105 /
+// 57 / 49, 2500^2 135 / 149 / 122, 100000 x 8 45 / 55 / 45; FP16 1024^2 119 / 49 /
+// 49, 2500^2 142 / 120 / 99, 100000 x 8 47 / 50 / 46.  On the largest lattices 64
+// rows are 8-11% faster than 16 (two halo rows a strip).
+int diag_rows(int storage, const Geom& g) {
+  const int tiles_x = (g.nx + kDiagThreads - 1) / kDiagThreads;
+  const int strips = std::max(1, (storage == LBMHD_FP32 ? 512 : 1024) / tiles_x);
+  return std::min(kDiagRows, (g.ny + strips - 1) / strips);
 }
 
-static long long diag_units(const Geom& g) {
+static long long diag_units(int storage, const Geom& g) {
   const long long tiles_x = (g.nx + kDiagThreads - 1) / kDiagThreads;
-  const int rows = diag_rows(g);
+  const int rows = diag_rows(storage, g);
   return tiles_x * ((g.ny + rows - 1) / rows);
 }
 
-int diag_partials(const Geom& g) {
-  return int(std::min<long long>(kDiagBlocks, diag_units(g)));
+int diag_partials(int storage, const Geom& g) {
+  return int(std::min<long long>(kDiagBlocks, diag_units(storage, g)));
 }
 
-// A block to a row (k_diag_row) while each has a CU of its own: us per interval
-// of one step and its diagnostics, walking / by the row, FP32 64^2 16.7 / 12.5,
-// 128^2 17.1 / 14.1, 256^2 18.7 / 17.5, 400^2 (800 blocks) 28.9 / 29.0, 512^2 30.7 / 32.9.
-bool diag_by_row(const Geom& g) { return diag_rows(g) == 1 && diag_units(g) <= 256; }
+// A block to a row (k_diag_row; the strips above are then one row) while each has
+// a CU of its own: us per interval of one step and its diagnostics, walking / by
+// the row, FP32 64^2 16.7 / 12.5, 128^2 17.1 / 14.1, 256^2 18.7 / 17.5, 400^2 (800
+// blocks) 28.9 / 29.0, 512^2 30.7 / 32.9.
+bool diag_by_row(const Geom& g) {
+  return (long long)((g.nx + kDiagThreads - 1) / kDiagThreads) * g.ny <= 256;
+}
 
 hipError_t launch_diag(int storage, const void* lat, double* part, double* out_dev,
                        const Geom& g, hipStream_t s) {
   const int tiles_x = (g.nx + kDiagThreads - 1) / kDiagThreads;
-  const long long units = diag_units(g);
-  const int nparts = diag_partials(g), rows = diag_rows(g);
+  const long long units = diag_units(storage, g);
+  const int nparts = diag_partials(storage, g), rows = diag_rows(storage, g);
   if (diag_by_row(g))
     with_bools([&](auto fp32) {
       constexpr int ST = fp32() ? LBMHD_FP32 : LBMHD_FP16;
@@ -2489,8 +2495,8 @@ hipError_t launch_diag(int storage, const void* lat, double* part, double* out_d
 hipError_t launch_step_diag(int storage, bool les, const void* src, void* dst, double* part,
                             double* out_dev, const Geom& g, const Rates& r, hipStream_t s) {
   const int tiles_x = (g.nx + kDiagThreads - 1) / kDiagThreads;
-  const long long units = diag_units(g);
-  const int nparts = diag_partials(g), rows = diag_rows(g);
+  const long long units = diag_units(storage, g);
+  const int nparts = diag_partials(storage, g), rows = diag_rows(storage, g);
   if (diag_by_row(g)) {
     with_bools([&](auto fp32, auto l) {
       constexpr int ST = fp32() ? LBMHD_FP32 : LBMHD_FP16;

@@ -18,3 +18,10 @@ extern "C" int rule_stores_bypass(int nx, int ny, int esize, int kept) {
 extern "C" int rule_strip_rows(int tiles, int ny, int want, int lo, int hi, int big) {
   return lbk::split_rows(tiles, ny, want, lo, hi, big).rows;
 }
+
+// Strips of the diagnostics passes: their rows, or with `blocks` their count.
+extern "C" int rule_diag(int nx, int ny, int storage, int blocks) {
+  const lbk::Geom g = geom(nx, ny, storage == LBMHD_FP32 ? 4 : 2);
+  return blocks ? lbk::diag_partials(storage, g) : lbk::diag_rows(storage, g);
+}
+extern "C" int rule_diag_by_row(int nx, int ny) { return lbk::diag_by_row(geom(nx, ny, 4)); }

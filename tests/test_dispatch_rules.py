@@ -53,3 +53,15 @@ def test_kept_states_go_past_the_cache_that_they_outgrow(rules, nx, ny, esize, b
     (256, 40, 20), (196, 100, 50), (169, 40, 14), (16, 4096, 128), (8, 2048, 32)])
 def test_one_strip_does_not_leave_half_the_card(rules, tiles, ny, rows):
     assert rules.rule_strip_rows(tiles, ny, 512, 8, 128, 32) == rows
+
+
+@pytest.mark.parametrize("storage,most", [(FP32, 512), (FP16, 1024)])
+@pytest.mark.parametrize("nx,ny", [(2, 2), (64, 64), (256, 256), (600, 600), (1024, 1024),
+                                   (2500, 2500), (3000, 1999), (100000, 8), (120000, 33),
+                                   (20000, 16), (200, 16000), (5000, 2900), (8192, 8192)])
+def test_diagnostics_strips_fill_whole_rounds(rules, nx, ny, storage, most):
+    tiles, rows = -(-nx // 256), rules.rule_diag(nx, ny, storage, 0)
+    blocks = rules.rule_diag(nx, ny, storage, 1)
+    assert 1 <= rows <= 64 and blocks == tiles * -(-ny // rows)
+    assert blocks <= most or rows == 64
+    assert not rules.rule_diag_by_row(nx, ny) or rows == 1
