@@ -155,6 +155,9 @@ bool tile_keep_pays(int storage, bool nb, const Geom& g);
 // The steps of one launch where tiles are the faster way (nb: closures with
 // neighbour terms), or 0 where the row-walking kernels are.
 int tile_steps(int storage, bool nb, const Geom& g);
+// Whether launch_tile takes regions of 64 x 32 sites (closures without neighbour
+// terms; keep: a launch that keeps states).
+bool tile_wide(int storage, int k, bool keep, const Geom& g);
 // Where tile_steps is not 0: whether tiles are also faster for only k steps.
 bool tile_short_pays(int storage, bool nb, int k, const Geom& g);
 // Equilibrium initialisation from FP64 fields.

@@ -2098,6 +2098,13 @@ struct Tile {
 
 static bool tile_small(const Geom& g) { return (long long)g.nx * g.ny <= 40000; }
 
+// Lanes that issue for each site that counts, in regions of rx x ry sites of
+// which a rim of `halo` is halo.
+static double tile_lanes(const Geom& g, int rx, int ry, int halo) {
+  const int w = rx - 2 * halo, h = ry - 2 * halo;
+  return double((g.nx + w - 1) / w) * rx * ((g.ny + h - 1) / h) * ry / (double(g.nx) * g.ny);
+}
+
 // Steps per launch: without neighbour terms up to nine in the larger region
 // while the smaller tiles still leave a CU each (256^2: five steps 14.5 us, 121
 // blocks; nine steps 21.3 us, 256 blocks).
@@ -2155,11 +2162,15 @@ static void launch_tile_r(const void* src, void* dst, int k, size_t keep, const 
 // 31.2, 2500^2 48.1 / 46.6, 4096^2 129 / 116, 8192^2 535 / 461.  Keeping every
 // second state FP32 1024^2 17.6 / 16.1, 1200^2 26.3 / 24.2, 724^2 8.7 / 8.7.
 // Not faster: six steps (FP32 4096^2 132), four parts or six sites a thread
-// (more than 128 registers a lane: 220).
-static bool tile_wide(int storage, int k, bool keep, const Geom& g) {
+// (more than 128 registers a lane: 220); lattices whose width leaves the wide tiles
+// emptier, five steps 32 x 32 / 64 x 32: FP32 60 x 33333 21.6 / 25.9, 72 x 27777 22.4 /
+// 25.1, 120 x 50000 55 / 61, FP16 60 x 100000 54 / 76, 72 x 83333 50 / 68.
+bool tile_wide(int storage, int k, bool keep, const Geom& g) {
   const double sites = double(g.nx) * g.ny;
-  if (keep) return storage == LBMHD_FP32 && sites >= 8e5;
-  return (k == 4 || k == 5) && sites >= (storage == LBMHD_FP32 ? 1.6e6 : 5e6);
+  if (keep ? storage != LBMHD_FP32 || sites < 8e5
+           : (k != 4 && k != 5) || sites < (storage == LBMHD_FP32 ? 1.6e6 : 5e6))
+    return false;
+  return 1.02 * tile_lanes(g, 64, 32, k - 1) <= tile_lanes(g, 32, 32, k - 1);
 }
 
 template <int ST, int EDDY>

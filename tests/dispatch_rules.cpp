@@ -25,3 +25,7 @@ extern "C" int rule_diag(int nx, int ny, int storage, int blocks) {
   return blocks ? lbk::diag_partials(storage, g) : lbk::diag_rows(storage, g);
 }
 extern "C" int rule_diag_by_row(int nx, int ny) { return lbk::diag_by_row(geom(nx, ny, 4)); }
+
+extern "C" int rule_tile_wide(int nx, int ny, int storage, int k, int keep) {
+  return lbk::tile_wide(storage, k, keep != 0, geom(nx, ny, storage == LBMHD_FP32 ? 4 : 2));
+}

@@ -65,3 +65,20 @@ def test_diagnostics_strips_fill_whole_rounds(rules, nx, ny, storage, most):
     assert 1 <= rows <= 64 and blocks == tiles * -(-ny // rows)
     assert blocks <= most or rows == 64
     assert not rules.rule_diag_by_row(nx, ny) or rows == 1
+
+
+@pytest.mark.parametrize("nx,ny,storage,wide", [
+    (4096, 4096, FP32, 1), (1448, 1448, FP32, 1), (8192, 8192, FP16, 1), (1000, 1000, FP32, 0),
+    (56, 40000, FP32, 1), (112, 20000, FP32, 1), (168, 50000, FP16, 1), (100, 40000, FP32, 1),
+    # one column of 56 and a few columns more
+    (60, 40000, FP32, 0), (72, 40000, FP32, 0), (120, 50000, FP32, 0), (60, 100000, FP16, 0),
+    (72, 100000, FP16, 0)])
+def test_wide_tiles_where_they_issue_fewer_lanes(rules, nx, ny, storage, wide):
+    assert rules.rule_tile_wide(nx, ny, storage, 5, 0) == wide
+    assert rules.rule_tile_wide(nx, ny, storage, 3, 0) == 0
+
+
+def test_wide_tiles_of_kept_states(rules):
+    assert [rules.rule_tile_wide(nx, ny, FP32, 4, 1)
+            for nx, ny in ((1024, 1024), (58, 20000), (64, 20000), (700, 700))] == [1, 1, 0, 0]
+    assert not rules.rule_tile_wide(4096, 4096, FP16, 4, 1)
