@@ -20,6 +20,8 @@
 // order (a remap giving each XCD a contiguous band of tiles measured slower).
 #include <math.h>
 
+#include <algorithm>
+#include <cmath>
 #include <tuple>
 #include <type_traits>
 
@@ -2242,17 +2244,56 @@ static double tile_size(const Geom& g) {
   return double(g.nx) * g.ny * (g.nx / cols);
 }
 
-// Which launches go to tiles, us per step in tiles / by rows.  Five steps
-// always: FP32 1024^2 10.2 / 11.7 (k_step_t3), 2048^2 36 / 45, 4096^2 130 / 167,
+// The region of a launch of k steps and its halo.
+struct Region {
+  int rx, ry, halo;
+};
+static Region tile_region(int storage, bool nb, int k, bool keep, const Geom& g) {
+  const int halo = nb ? 2 * k - 1 : k - 1;
+  if (!nb && tile_wide(storage, k, keep, g)) return Region{64, 32, halo};
+  if (tile_small(g)) return Region{16, 16, halo};
+  return Region{32, nb && storage == LBMHD_FP32 ? 28 : 32, halo};
+}
+
+// The share of the tiles of a launch of k steps that the lattice fills, relative
+// to what it fills of the row-walking kernels' columns.
+static double tile_fill(int storage, bool nb, int k, bool keep, const Geom& g) {
+  const Region r = tile_region(storage, nb, k, keep, g);
+  const int w = r.rx - 2 * r.halo, h = r.ry - 2 * r.halo;
+  const double cols = double((g.nx + 255) / 256) * 256;
+  return double(r.rx) * r.ry / (double(w) * h * tile_lanes(g, r.rx, r.ry, r.halo)) *
+         (cols / g.nx);
+}
+
+// Whether that is enough: low, wide lattices leave most of their tiles' rows
+// empty, which matters the more, the more of the launch is bound by its lanes and
+// not by its latency.  us per step by rows / in tiles: five steps FP32 25000 x 4
+// (share 0.17) 4.9 / 5.6, 16666 x 6 (0.25) 4.9 / 3.9, 50000 x 6 (0.25) 7.6 / 9.8, 30000 x 10
+// (0.42) 8.7 / 6.2, 83332 x 12 (0.5) 13.9 / 15.2, 31250 x 32 (0.67) 13.0 / 13.3, 107142 x 28
+// (0.58) 36.2 / 36.9, 93750 x 32 (0.67) 39 / 33; FP16 37500 x 8 (0.33) 7.2 / 7.8, 93750 x 32
+// (0.67) 28.5 / 31.9, 53570 x 56 (0.78) 30.7 / 27.9; neighbour terms FP32 three steps
+// 25000 x 4 (0.22) 11.2 / 8.7, 50000 x 6 (0.33) 14.5 / 16.4, 41666 x 24 (0.67) 23.3 / 28.0,
+// 20832 x 48 (0.89) 23.4 / 22.2; FP16 two steps 62500 x 16 (0.62) 24.3 / 23.1, 53570 x 56
+// (0.72) 62.2 / 56.6, 107142 x 28 (0.54) 54.9 / 74.1.
+static bool tile_filled(int storage, bool nb, int k, bool keep, const Geom& g) {
+  const bool fp32 = storage == LBMHD_FP32;
+  const double grow = nb ? 0.22 : (fp32 ? 0.19 : 0.27), top = nb ? (fp32 ? 0.8 : 0.7) : (fp32 ? 0.65 : 0.7);
+  return tile_fill(storage, nb, k, keep, g) >=
+         std::min(top, grow * std::sqrt(double(g.nx) * g.ny / 1e5));
+}
+
+// Which launches go to tiles where these are filled, us per step in tiles / by
+// rows.  Five steps: FP32 1024^2 10.2 / 11.7 (k_step_t3), 2048^2 36 / 45, 4096^2 130 / 167,
 // 8192 x 4096 252 / 373; FP16 1024^2 9.2 / 12.9 (k_step), 4096^2 116 / 151
 // (k_step2), 8192 x 4096 230 / 289.  Neighbour terms, FP32: three steps 724^2
 // 11.4 / 20.2 (k_step_nb2), 1300^2 34 / 40, 1448^2 45.1 / 44.5, 2048^2 89 / 73;
 // FP16: two steps 1024^2 17.9 / 35 (k_step_nb; three 19.3), 4096^2 237 / 268
 // (three 278).
 int tile_steps(int storage, bool nb, const Geom& g) {
-  if (!nb) return tile_most(nb, g);
-  if (storage == LBMHD_FP16) return tile_size(g) < 4e5 ? 3 : 2;
-  return tile_size(g) < 1.6e6 ? 3 : 0;
+  int k = tile_most(nb, g);
+  if (nb && storage == LBMHD_FP16) k = tile_size(g) < 4e5 ? 3 : 2;
+  if (nb && storage == LBMHD_FP32 && tile_size(g) >= 1.6e6) return 0;
+  return tile_filled(storage, nb, k, false, g) ? k : 0;
 }
 
 // Fewer steps.  FP32: four 4096^2 154 / 234 (a triple and a single step), three
@@ -2261,9 +2302,12 @@ int tile_steps(int storage, bool nb, const Geom& g) {
 // 2048^2 44.6 / 45.5, 4096^2 180 / 152; one with neighbour terms 1448^2
 // 79 / 95 FP32 and 36 / 60 FP16, 2048^2 170 / 132 and 94 / 78.
 bool tile_short_pays(int storage, bool nb, int k, const Geom& g) {
-  if (nb) return k > 1 || tile_size(g) < 2.2e6;
+  if (!tile_filled(storage, nb, k, false, g)) return false;
+  const double fill = std::min(1.0, tile_fill(storage, nb, k, false, g));
+  if (nb) return k > 1 || tile_size(g) < 2.2e6 * fill;
   if (k >= (storage == LBMHD_FP32 ? 4 : 3)) return true;
-  return k > 1 && tile_size(g) < (storage == LBMHD_FP32 ? 1.04e6 : 4.0e6);
+  return k > 1 && (tile_small(g) || fill >= 0.65) &&
+         tile_size(g) < (storage == LBMHD_FP32 ? 1.04e6 : 4.0e6) * fill;
 }
 
 // Launches that keep states on the way, us per step against the launches that
@@ -2275,8 +2319,11 @@ bool tile_short_pays(int storage, bool nb, int k, const Geom& g) {
 // 8.2 / 10.9, 724^2 16.9 / 18.6, 1024^2 35.6 / 31.8 (k_step_nb2); FP16 512^2 8.5 /
 // 9.9, 1024^2 22.4 / 23.3, 1448^2 46.2 / 47.4, 2048^2 89 / 79 (k_step_nb).
 bool tile_keep_pays(int storage, bool nb, const Geom& g) {
-  if (nb) return tile_size(g) < (storage == LBMHD_FP32 ? 8e5 : 2.2e6);
-  return tile_size(g) < (storage == LBMHD_FP32 ? 1.5e6 : 5e6);
+  const int k = tile_keep(nb, g);
+  if (!tile_filled(storage, nb, k, true, g)) return false;
+  const double size = tile_size(g) / std::min(1.0, tile_fill(storage, nb, k, true, g));
+  if (nb) return size < (storage == LBMHD_FP32 ? 8e5 : 2.2e6);
+  return size < (storage == LBMHD_FP32 ? 1.5e6 : 5e6);
 }
 
 // ------------------------------------------ several steps in place

@@ -29,3 +29,15 @@ extern "C" int rule_diag_by_row(int nx, int ny) { return lbk::diag_by_row(geom(n
 extern "C" int rule_tile_wide(int nx, int ny, int storage, int k, int keep) {
   return lbk::tile_wide(storage, k, keep != 0, geom(nx, ny, storage == LBMHD_FP32 ? 4 : 2));
 }
+
+// Steps of a tile launch (0: by rows), whether k steps alone go to tiles, and
+// whether kept states do.
+extern "C" int rule_tile_steps(int nx, int ny, int storage, int nb) {
+  return lbk::tile_steps(storage, nb != 0, geom(nx, ny, storage == LBMHD_FP32 ? 4 : 2));
+}
+extern "C" int rule_tile_short(int nx, int ny, int storage, int nb, int k) {
+  return lbk::tile_short_pays(storage, nb != 0, k, geom(nx, ny, storage == LBMHD_FP32 ? 4 : 2));
+}
+extern "C" int rule_tile_keep(int nx, int ny, int storage, int nb) {
+  return lbk::tile_keep_pays(storage, nb != 0, geom(nx, ny, storage == LBMHD_FP32 ? 4 : 2));
+}

@@ -82,3 +82,37 @@ def test_wide_tiles_of_kept_states(rules):
     assert [rules.rule_tile_wide(nx, ny, FP32, 4, 1)
             for nx, ny in ((1024, 1024), (58, 20000), (64, 20000), (700, 700))] == [1, 1, 0, 0]
     assert not rules.rule_tile_wide(4096, 4096, FP16, 4, 1)
+
+
+# low, wide lattices that leave most of the tiles' rows empty go by rows again
+LOW = [(100000, 2), (1000000, 4), (400000, 12), (75000, 4), (50000, 6), (107142, 28)]
+
+
+@pytest.mark.parametrize("storage", [FP32, FP16])
+@pytest.mark.parametrize("nx,ny", LOW)
+def test_low_lattices_go_by_rows(rules, nx, ny, storage):
+    for nb in (0, 1):
+        assert rules.rule_tile_steps(nx, ny, storage, nb) == 0
+        assert not rules.rule_tile_keep(nx, ny, storage, nb)
+
+
+@pytest.mark.parametrize("nx,ny,local,nb32,nb16", [
+    (2, 2, 5, 3, 3), (64, 64, 5, 3, 3), (4096, 8, 5, 3, 3), (256, 256, 9, 3, 3),
+    (1000, 100, 5, 3, 3), (6000, 50, 5, 3, 3), (1021, 767, 5, 3, 2), (1024, 1024, 5, 3, 2),
+    (2, 100000, 5, 3, 3), (60, 40000, 5, 3, 2), (4096, 4096, 5, 0, 2), (8192, 8192, 5, 0, 2),
+    (41666, 24, 5, 0, 2), (30000, 100, 5, 0, 2)])
+def test_other_lattices_keep_their_tiles(rules, nx, ny, local, nb32, nb16):
+    assert rules.rule_tile_steps(nx, ny, FP32, 0) == local
+    assert rules.rule_tile_steps(nx, ny, FP16, 0) == local
+    assert rules.rule_tile_steps(nx, ny, FP32, 1) == nb32
+    assert rules.rule_tile_steps(nx, ny, FP16, 1) == nb16
+
+
+@pytest.mark.parametrize("nx,ny,storage,nb,k,tiles", [
+    (1000, 1000, FP32, 0, 2, 1), (1024, 1024, FP32, 0, 3, 0), (1448, 1448, FP16, 0, 2, 1),
+    (1448, 1448, FP32, 1, 1, 1), (2048, 2048, FP32, 1, 1, 0), (64, 64, FP32, 0, 2, 1),
+    # tiles whose second row of tiles is nearly empty
+    (31250, 32, FP32, 0, 2, 0), (31250, 32, FP16, 0, 2, 0), (93750, 32, FP16, 0, 3, 0),
+    (43100, 40, FP16, 1, 1, 0), (35714, 28, FP32, 1, 1, 0)])
+def test_short_launches(rules, nx, ny, storage, nb, k, tiles):
+    assert rules.rule_tile_short(nx, ny, storage, nb, k) == tiles
