@@ -61,7 +61,7 @@ bool reads_neighbours(const lbmhd_t* h) { return (h->p.les & 2) || eddy_of(h) ==
 // name).
 int tile_most(const lbmhd_t* h) {
   if (h->p.inplace || h->p.steps_per_pass != 0) return 0;
-  return lbk::tile_steps(h->p.storage, reads_neighbours(h), h->geo);
+  return lbk::tile_steps(h->p.storage, eddy_of(h), (h->p.les & 2) != 0, h->geo);
 }
 
 // Whether a launch of only k steps goes to the tile kernel as well.

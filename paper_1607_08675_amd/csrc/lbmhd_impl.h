@@ -152,13 +152,14 @@ hipError_t launch_tile(int storage, int eddy, bool kin, const void* src, void* d
 // that keep one each.
 int tile_keep(bool nb, const Geom& g);
 bool tile_keep_pays(int storage, bool nb, const Geom& g);
-// The steps of one launch where tiles are the faster way (nb: closures with
-// neighbour terms), or 0 where the row-walking kernels are.
-int tile_steps(int storage, bool nb, const Geom& g);
+// The steps of one launch where tiles are the faster way (eddy, kin as
+// launch_tile), or 0 where the row-walking kernels are.
+int tile_steps(int storage, int eddy, bool kin, const Geom& g);
 // Whether launch_tile takes regions of 64 x 32 sites (closures without neighbour
 // terms; keep: a launch that keeps states).
 bool tile_wide(int storage, int k, bool keep, const Geom& g);
-// Where tile_steps is not 0: whether tiles are also faster for only k steps.
+// Where tile_steps is not 0: whether tiles are also faster for only k steps (nb:
+// closures with neighbour terms).
 bool tile_short_pays(int storage, bool nb, int k, const Geom& g);
 // Equilibrium initialisation from FP64 fields.
 hipError_t launch_init(int storage, const double* rho, const double* ux, const double* uy,

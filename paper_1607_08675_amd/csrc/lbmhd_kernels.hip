@@ -2274,10 +2274,12 @@ static double tile_fill(int storage, bool nb, int k, bool keep, const Geom& g) {
 // (0.67) 28.5 / 31.9, 53570 x 56 (0.78) 30.7 / 27.9; neighbour terms FP32 three steps
 // 25000 x 4 (0.22) 11.2 / 8.7, 50000 x 6 (0.33) 14.5 / 16.4, 41666 x 24 (0.67) 23.3 / 28.0,
 // 20832 x 48 (0.89) 23.4 / 22.2; FP16 two steps 62500 x 16 (0.62) 24.3 / 23.1, 53570 x 56
-// (0.72) 62.2 / 56.6, 107142 x 28 (0.54) 54.9 / 74.1.
+// (0.72) 62.2 / 56.6 (cross-helicity 62.6 / 66.4), 107142 x 28 (0.54) 54.9 / 74.1;
+// kept pairs FP16 53570 x 56 (0.72) 33.2 / 38.0.
 static bool tile_filled(int storage, bool nb, int k, bool keep, const Geom& g) {
   const bool fp32 = storage == LBMHD_FP32;
-  const double grow = nb ? 0.22 : (fp32 ? 0.19 : 0.27), top = nb ? (fp32 ? 0.8 : 0.7) : (fp32 ? 0.65 : 0.7);
+  const double grow = nb ? 0.22 : (fp32 ? 0.19 : 0.27);
+  const double top = nb || keep ? (fp32 ? 0.8 : 0.75) : (fp32 ? 0.65 : 0.7);
   return tile_fill(storage, nb, k, keep, g) >=
          std::min(top, grow * std::sqrt(double(g.nx) * g.ny / 1e5));
 }
@@ -2288,11 +2290,17 @@ static bool tile_filled(int storage, bool nb, int k, bool keep, const Geom& g) {
 // (k_step2), 8192 x 4096 230 / 289.  Neighbour terms, FP32: three steps 724^2
 // 11.4 / 20.2 (k_step_nb2), 1300^2 34 / 40, 1448^2 45.1 / 44.5, 2048^2 89 / 73;
 // FP16: two steps 1024^2 17.9 / 35 (k_step_nb; three 19.3), 4096^2 237 / 268
-// (three 278).
-int tile_steps(int storage, bool nb, const Geom& g) {
+// (three 278), 6000^2 510 / 561, 8192^2 1087 / 1070; cross-helicity alone 3000^2
+// 147.5 / 156.4, 3500^2 198.6 / 194.7, 4096^2 271 / 266, 8192^2 1111 / 1050, with the
+// kinetic closure 1224 / 1437.
+int tile_steps(int storage, int eddy, bool kin, const Geom& g) {
+  const bool nb = kin || eddy == 2;
   int k = tile_most(nb, g);
-  if (nb && storage == LBMHD_FP16) k = tile_size(g) < 4e5 ? 3 : 2;
   if (nb && storage == LBMHD_FP32 && tile_size(g) >= 1.6e6) return 0;
+  if (nb && storage == LBMHD_FP16) {
+    if (!(kin && eddy == 2) && tile_size(g) >= (kin ? 5e7 : 1.05e7)) return 0;
+    k = tile_size(g) < 4e5 ? 3 : 2;
+  }
   return tile_filled(storage, nb, k, false, g) ? k : 0;
 }
 

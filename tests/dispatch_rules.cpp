@@ -32,8 +32,8 @@ extern "C" int rule_tile_wide(int nx, int ny, int storage, int k, int keep) {
 
 // Steps of a tile launch (0: by rows), whether k steps alone go to tiles, and
 // whether kept states do.
-extern "C" int rule_tile_steps(int nx, int ny, int storage, int nb) {
-  return lbk::tile_steps(storage, nb != 0, geom(nx, ny, storage == LBMHD_FP32 ? 4 : 2));
+extern "C" int rule_tile_steps(int nx, int ny, int storage, int les) {
+  return lbk::tile_steps(storage, les & 4 ? 2 : les & 1, (les & 2) != 0, geom(nx, ny, storage == LBMHD_FP32 ? 4 : 2));
 }
 extern "C" int rule_tile_short(int nx, int ny, int storage, int nb, int k) {
   return lbk::tile_short_pays(storage, nb != 0, k, geom(nx, ny, storage == LBMHD_FP32 ? 4 : 2));

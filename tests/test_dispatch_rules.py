@@ -91,8 +91,9 @@ LOW = [(100000, 2), (1000000, 4), (400000, 12), (75000, 4), (50000, 6), (107142,
 @pytest.mark.parametrize("storage", [FP32, FP16])
 @pytest.mark.parametrize("nx,ny", LOW)
 def test_low_lattices_go_by_rows(rules, nx, ny, storage):
+    for les in (0, 1, 2, 3, 4, 6):
+        assert rules.rule_tile_steps(nx, ny, storage, les) == 0
     for nb in (0, 1):
-        assert rules.rule_tile_steps(nx, ny, storage, nb) == 0
         assert not rules.rule_tile_keep(nx, ny, storage, nb)
 
 
@@ -102,10 +103,19 @@ def test_low_lattices_go_by_rows(rules, nx, ny, storage):
     (2, 100000, 5, 3, 3), (60, 40000, 5, 3, 2), (4096, 4096, 5, 0, 2), (8192, 8192, 5, 0, 2),
     (41666, 24, 5, 0, 2), (30000, 100, 5, 0, 2)])
 def test_other_lattices_keep_their_tiles(rules, nx, ny, local, nb32, nb16):
-    assert rules.rule_tile_steps(nx, ny, FP32, 0) == local
-    assert rules.rule_tile_steps(nx, ny, FP16, 0) == local
-    assert rules.rule_tile_steps(nx, ny, FP32, 1) == nb32
-    assert rules.rule_tile_steps(nx, ny, FP16, 1) == nb16
+    for les in (0, 1):
+        assert rules.rule_tile_steps(nx, ny, FP32, les) == local
+        assert rules.rule_tile_steps(nx, ny, FP16, les) == local
+    for les in (2, 3, 4, 6):
+        assert rules.rule_tile_steps(nx, ny, FP32, les) == nb32
+    assert rules.rule_tile_steps(nx, ny, FP16, 6) == nb16
+
+
+@pytest.mark.parametrize("n,les,k", [
+    (3000, 4, 2), (3500, 4, 0), (8192, 4, 0), (4096, 2, 2), (6000, 3, 2), (8192, 2, 0),
+    (8192, 3, 0), (8192, 6, 2), (8192, 1, 5)])
+def test_fp16_closures_leave_the_tiles_on_large_lattices(rules, n, les, k):
+    assert rules.rule_tile_steps(n, n, FP16, les) == k
 
 
 @pytest.mark.parametrize("nx,ny,storage,nb,k,tiles", [
@@ -116,3 +126,11 @@ def test_other_lattices_keep_their_tiles(rules, nx, ny, local, nb32, nb16):
     (43100, 40, FP16, 1, 1, 0), (35714, 28, FP32, 1, 1, 0)])
 def test_short_launches(rules, nx, ny, storage, nb, k, tiles):
     assert rules.rule_tile_short(nx, ny, storage, nb, k) == tiles
+
+
+@pytest.mark.parametrize("nx,ny,storage,nb,keeps", [
+    (1024, 1024, FP32, 0, 1), (1200, 1200, FP32, 0, 1), (2048, 2048, FP16, 0, 1),
+    (512, 512, FP32, 1, 1), (1024, 1024, FP32, 1, 0), (1448, 1448, FP16, 1, 1),
+    (64, 64, FP32, 1, 1), (53570, 56, FP16, 0, 0), (43100, 40, FP16, 1, 0), (100000, 8, FP16, 1, 0)])
+def test_kept_states_by_size(rules, nx, ny, storage, nb, keeps):
+    assert rules.rule_tile_keep(nx, ny, storage, nb) == keeps
