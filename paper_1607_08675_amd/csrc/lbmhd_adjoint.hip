@@ -1402,12 +1402,24 @@ static bool adj_slots_hold(const Geom& g, int w, int h) {
 }
 
 // Two reverse steps by tiles of 28 x 12 sites, us per step by rows / by tiles
-// (les = 1, states from HBM): FP32 128^2 20.7 / 4.5, 512^2 22.9 / 10.8, 1024^2
-// 35 / 29, 1800^2 98 / 94, 2048^2 115 / 121; FP16 1024^2 34 / 26, 2048^2 107 /
-// 105, 2500^2 169 / 160, 4096^2 414 / 424.
-static bool adj_tile_pays(int storage, const Geom& g) {
+// (les = 1, states from HBM): FP32 128^2 20.7 / 4.5, 512^2 21.0 / 9.1, 1024^2 34.8 /
+// 29.0, 1448^2 67.6 / 60.8, 1800^2 98.5 / 94.5, 2048^2 114 / 121; FP16 1024^2 32.7 /
+// 25.8, 2048^2 107 / 106, 2500^2 169 / 160, 4096^2 414 / 424.  From 1.3 million sites
+// on both are bound by what they issue: the rows by whole rounds of 512 blocks
+// (`walk`, in sites), which some lattices fill badly, the tiles by their lanes
+// (1.54 a site on large lattices).  FP32 10000 x 300 (the rounds filled to 0.6) 116 /
+// 91, 400 x 8000 (0.76) 105 / 94, 1600^2 (0.85) 79.6 / 79.8, 2000 x 1500 (0.95) 86 / 92, 8000
+// x 400 (0.98) 89 / 98, 4096 x 512 (1) 61 / 65, 107142 x 28 (0.82, 1.96 lanes a site) 94 /
+// 115; FP16 2000 x 1500 82.2 / 81.1, 107142 x 28 92 / 98.
+bool adj_tile_pays(int storage, const Geom& g) {
   const double sites = double(g.nx) * g.ny;
-  return sites < (storage == LBMHD_FP32 ? 3.5e6 : 8e6) && adj_slots_hold(g, 28, 12);
+  if (sites >= (storage == LBMHD_FP32 ? 3.5e6 : 8e6) || !adj_slots_hold(g, 28, 12)) return false;
+  if (sites < 1.3e6) return true;
+  const int rows = adj_step2_strips(g).rows, tiles_x = (g.nx + kT3Cols - 1) / kT3Cols;
+  const int rounds = (tiles_x * ((g.ny + rows - 1) / rows) + 511) / 512;
+  const double walk = 512.0 * rounds * rows * kT3Cols;
+  const double tiles = adj_tiles(g, 28, 12) * (32 * 16 / 1.54);
+  return walk >= tiles * (storage == LBMHD_FP16 ? 0.98 : (sites < 2.4e6 ? 1.05 : 1.12));
 }
 // ... and of 12 x 12 sites, more and shorter blocks: 64^2 3.3 us per step
 // against 3.8, 128^2 3.3 against 3.9, 200^2 4.2 against 4.4.

@@ -219,6 +219,9 @@ int adj_step_blocks(const Geom& g);
 hipError_t launch_adj_step2(int storage, bool les_fwd, bool les, const void* state,
                             const float* lam_next, float* lam_prev, double* acc, const Geom& g,
                             const Geom& ga, const Rates& r, double delta2, hipStream_t s);
+// Whether launch_adj_step2 takes tiles of 28 x 12 sites (below 40000 sites smaller
+// ones may come first) and not strips of rows.
+bool adj_tile_pays(int storage, const Geom& g);
 // Whether a sweep over every state takes its steps in pairs: from 512 blocks of
 // 8-row strips on (below, acc gains each step's block sums in the slots and
 // order of single steps).

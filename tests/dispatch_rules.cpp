@@ -41,3 +41,8 @@ extern "C" int rule_tile_short(int nx, int ny, int storage, int nb, int k) {
 extern "C" int rule_tile_keep(int nx, int ny, int storage, int nb) {
   return lbk::tile_keep_pays(storage, nb != 0, geom(nx, ny, storage == LBMHD_FP32 ? 4 : 2));
 }
+
+// Whether the paired reverse step goes by tiles.
+extern "C" int rule_adj_tile(int nx, int ny, int storage) {
+  return lbk::adj_tile_pays(storage, geom(nx, ny, storage == LBMHD_FP32 ? 4 : 2));
+}

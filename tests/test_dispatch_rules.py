@@ -134,3 +134,15 @@ def test_short_launches(rules, nx, ny, storage, nb, k, tiles):
     (64, 64, FP32, 1, 1), (53570, 56, FP16, 0, 0), (43100, 40, FP16, 1, 0), (100000, 8, FP16, 1, 0)])
 def test_kept_states_by_size(rules, nx, ny, storage, nb, keeps):
     assert rules.rule_tile_keep(nx, ny, storage, nb) == keeps
+
+
+@pytest.mark.parametrize("nx,ny,fp32,fp16", [
+    (64, 64, 1, 1), (1024, 1024, 1, 1), (6000, 50, 1, 1), (1448, 1448, 1, 1), (1800, 1800, 1, 1),
+    (10000, 300, 1, 1), (400, 8000, 1, 1), (60, 40000, 1, 1), (2048, 2048, 0, 1),
+    (4096, 4096, 0, 0), (20000, 16, 0, 0),   # the last: more tiles than slots
+    # the rows fill their rounds
+    (8000, 400, 0, 1), (16000, 200, 0, 1), (2000, 1500, 0, 1), (4096, 512, 0, 1),
+    (107142, 28, 0, 0)])
+def test_reverse_tiles_where_rows_fill_their_rounds_badly(rules, nx, ny, fp32, fp16):
+    assert rules.rule_adj_tile(nx, ny, FP32) == fp32
+    assert rules.rule_adj_tile(nx, ny, FP16) == fp16
