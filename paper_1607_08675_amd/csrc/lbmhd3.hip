@@ -678,6 +678,18 @@ __global__ __launch_bounds__(256) void k_final3(const double* __restrict__ part,
 }
 
 }  // namespace
+
+// Planes of z that a block of the diagnostics pass takes: whole chunks that leave
+// at most 768 blocks, three per CU (its registers admit no more), one round while
+// there are no more columns than that.  us of lbmhd3_diag, 1 / 768 of the planes
+// rounded up (792, 800 and 840 blocks) / this: FP32 130^3 135 / 128, 200^3 392 / 349,
+// 160^3 173 / 169; FP16 116 / 99, 347 / 277, 137 / 130; 256^3 and 96^3, 768 blocks
+// either way, 558 and 62.
+int diag3_chunk(long long tiles, int nz) {
+  const int chunks = int(std::max<long long>(1, 768 / tiles));
+  return (nz + chunks - 1) / chunks;
+}
+
 }  // namespace lbk3
 
 struct lbmhd3 {
@@ -925,13 +937,10 @@ int lbmhd3_diag(lbmhd3_t* h, lbmhd3_diag_t* out) {
   if (!out) return fail3(h, LBMHD_ERR_INVALID_ARG, "null output");
   double* part = h->ws;
   double* res = part + size_t(lbk3::kReduceBlocks) * lbk3::kRed;
-  // planes per block: as many as leave at most 768 blocks, three per CU (its
-  // registers admit no more): one round
   const lbk3::Geom3& g = h->geo;
   const int tiles_x = (g.nx + lbk3::kDiagX - 1) / lbk3::kDiagX;
   const long long tiles = (long long)tiles_x * ((g.ny + lbk3::kDiagY - 1) / lbk3::kDiagY);
-  const long long want = (tiles * g.nz + 767) / 768;
-  const int chunk = int(std::min<long long>(want, g.nz));
+  const int chunk = lbk3::diag3_chunk(tiles, g.nz);
   const long long units = tiles * ((g.nz + chunk - 1) / chunk);
   const int nb = int(std::min<long long>(lbk3::kReduceBlocks, units));
   const dim3 grid(nb), block(lbk3::kDiagThreads3);

@@ -1,6 +1,10 @@
 // The library's rules on lattice sizes behind C names, for tests on the host.
 #include "lbmhd_impl.h"
 
+namespace lbk3 {
+int diag3_chunk(long long tiles, int nz);
+}
+
 static lbk::Geom geom(int nx, int ny, int esize) {
   lbk::Geom g;
   g.nx = nx;
@@ -46,3 +50,6 @@ extern "C" int rule_tile_keep(int nx, int ny, int storage, int nb) {
 extern "C" int rule_adj_tile(int nx, int ny, int storage) {
   return lbk::adj_tile_pays(storage, geom(nx, ny, storage == LBMHD_FP32 ? 4 : 2));
 }
+
+// Planes of a block of the 3D diagnostics.
+extern "C" int rule_diag3_chunk(int tiles, int nz) { return lbk3::diag3_chunk(tiles, nz); }

@@ -146,3 +146,15 @@ def test_kept_states_by_size(rules, nx, ny, storage, nb, keeps):
 def test_reverse_tiles_where_rows_fill_their_rounds_badly(rules, nx, ny, fp32, fp16):
     assert rules.rule_adj_tile(nx, ny, FP32) == fp32
     assert rules.rule_adj_tile(nx, ny, FP16) == fp16
+
+
+@pytest.mark.parametrize("nx,ny,nz", [(2, 2, 2), (96, 96, 96), (130, 130, 130), (160, 160, 160),
+                                      (192, 192, 192), (200, 200, 200), (256, 256, 256),
+                                      (64, 4, 4000), (3072, 64, 7), (4000, 300, 5)])
+def test_3d_diagnostics_take_one_round(rules, nx, ny, nz):
+    tiles = -(-nx // 64) * -(-ny // 4)
+    chunk = rules.rule_diag3_chunk(tiles, nz)
+    assert 1 <= chunk <= nz
+    blocks = tiles * -(-nz // chunk)
+    assert blocks <= 768 or (tiles > 768 and chunk == nz)
+    assert chunk == 1 or tiles * -(-nz // (chunk - 1)) > 768 or blocks == tiles   # no fewer planes would do
