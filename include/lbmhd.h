@@ -252,7 +252,8 @@ int lbmhd_init_fields(lbmhd_t* h, const double* rho, const double* ux, const dou
  * takes five (up to nine on small lattices; three or two for closures that
  * read the neighbours' moments, below about 1.6 million sites with FP32
  * storage) in tiles of the lattice held on chip, and a remainder that tiles
- * do not speed up with those kernels.  Asynchronous. */
+ * do not speed up, or all steps of a lattice too low and wide to fill its tiles
+ * (e.g. 100000 x 2), with those kernels.  Asynchronous. */
 int lbmhd_step(lbmhd_t* h, int64_t nsteps);
 
 /* Steps that one pass over the lattice covers when lbmhd_step advances a

@@ -731,8 +731,8 @@ long long sites3(const lbmhd3_t* h) {
   return (long long)h->geo.nx * h->geo.ny * h->geo.nz;
 }
 unsigned blocks3(long long n) { return unsigned((n + 255) / 256); }
-// workspace: reduction partials, 16 results; its size stays that of seven fields
-// of n doubles more, which callers may count on
+// workspace: reduction partials, 16 results, and seven fields of n doubles that
+// no kernel uses (the size that lbmhd3_sizes has reported all along)
 size_t ws_doubles3(long long n) {
   return 7 * size_t(n) + size_t(lbk3::kReduceBlocks) * lbk3::kRed + 16;
 }

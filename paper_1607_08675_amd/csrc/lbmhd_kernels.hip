@@ -1026,8 +1026,9 @@ __global__ __launch_bounds__(kNb2Threads) __attribute__((amdgpu_waves_per_eu(4))
 // owns the S sites (rx, ry + j RY / S).  It holds
 // the rest populations in registers; the 16 moving ones pass through one LDS
 // buffer (written, barrier, read at x - c, barrier), in PH parts.  Bound by the
-// issue of vector instructions, about 80% of its ceiling with the lanes whose
-// sites are halo counted (1.4 to 1.8 a site and step).
+// issue of vector instructions, with the lanes whose sites are halo counted (1.4
+// to 1.8 a site and step): 0.6-0.7 of their nominal issue time with FP32 storage
+// (4096^2, 1024^2), 0.92-1.01 with FP16 (8192^2).
 // The closures that read their neighbours' moments (NB) shrink by two sites
 // a step: each step's gathered moments go to a second LDS buffer, and the
 // update takes the sites whose eight neighbours were gathered.
@@ -1827,8 +1828,8 @@ __global__ __launch_bounds__(256) void k_diag_final(const double* __restrict__ p
 }
 
 // One block; the rounding errors of the additions are summed beside them
-// (Knuth's two-sum), so that the result does not depend on how the terms were
-// grouped into partials but for the last bit at most.
+// (Knuth's two-sum), so that this sum adds no rounding of its own beyond the last
+// bit.  (The terms, a block's FP64 sums over all its steps, carry theirs.)
 constexpr int kSumThreads = 1024;
 __global__ __launch_bounds__(kSumThreads) void k_sum(const double* __restrict__ in, long long n,
                                                      double* __restrict__ out) {
