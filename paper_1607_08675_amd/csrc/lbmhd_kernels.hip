@@ -847,9 +847,11 @@ __global__ __launch_bounds__(kNb2Threads) __attribute__((amdgpu_waves_per_eu(4))
   // (29.7k against 54.6k).
   constexpr bool kPf = ST == LBMHD_FP32 && EDDY != 2;
   const int x0 = tile * W, y0 = strip * rows;
-  // a strip past the lattice; those without kPf return below, as fast as without
-  // the test (FP16, kinetic closure, 64^2: 15.8 us per step, 17.0 from here)
-  if (kPf && y0 >= ny) return;
+  // a strip past the lattice; the FP16 kinetic pass returns below, as fast as
+  // without the test (64^2 15.8 us per step, 17.0 from here; FP32 cross-helicity
+  // 4096^2 315.5 from here, 317.5 from below)
+  constexpr bool kLate = ST != LBMHD_FP32 && EDDY == 0;
+  if (!kLate && y0 >= ny) return;
   const int wt = min(W, nx - x0), h = min(rows, ny - y0);
   // the thread's column: its own (threads 0 .. W - 1) or a halo column
   // (lanes 0 .. 5 of the fifth wave: x0 - 3 .. x0 - 1, x0 + wt .. x0 + wt + 2)
@@ -892,7 +894,7 @@ __global__ __launch_bounds__(kNb2Threads) __attribute__((amdgpu_waves_per_eu(4))
     t2_rows(a, geo, row);
     gather_row<ST, 1>(src, P, xc, xl, xr, row, v);
   };
-  if (!kPf && h <= 0) return;
+  if (kLate && h <= 0) return;
   if (kPf && has) gather_at(y0 - 3, pf);
   for (int t = 0; t < h + 6; ++t) {
     const int s0 = t % 3;                         // ring slot of this pass
