@@ -198,10 +198,11 @@ def inplace_leg(torch, args):
     per_step = burst_ms_per_step(torch, lat, 66 * INPLACE_STEPS)
     d = lat.diag()
     log(f"in-place 4096^2 FP32: {per_step:.4f} ms/step, nonfinite={d['nonfinite']}")
-    mem = lat.lattice_bytes
+    mem, scratch = lat.lattice_bytes, lat.workspace_bytes
     del lat
     torch.cuda.empty_cache()
-    return dict(per_step=per_step, sites=n * n, nonfinite=d["nonfinite"], lattice_bytes=mem)
+    return dict(per_step=per_step, sites=n * n, nonfinite=d["nonfinite"], lattice_bytes=mem,
+                scratch_bytes=scratch)
 
 
 def threed_leg(torch, args):
@@ -704,6 +705,8 @@ def main():
             "achieved_gbs": round(ai, 1), "frac": round(ai / HBM_PEAK_GBS, 4),
             "bytes_per_site": FP32_BYTES_PER_SITE, "nonfinite": rin["nonfinite"],
             "state_bytes": rin["lattice_bytes"], "state_bytes_two_lattices": 2 * rin["lattice_bytes"],
+            # the workspace and the copies of rows and columns around tiles and strips
+            "scratch_bytes": rin["scratch_bytes"],
         }
     for key, res, what in (
             ("kinetic_closure", rkin, "kinetic LES closure (filtered equilibria, Delta = 1)"),

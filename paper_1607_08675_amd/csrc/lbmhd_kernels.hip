@@ -1029,8 +1029,8 @@ __global__ __launch_bounds__(kNb2Threads) __attribute__((amdgpu_waves_per_eu(4))
 // the rest populations in registers; the 16 moving ones pass through one LDS
 // buffer (written, barrier, read at x - c, barrier), in PH parts.  Bound by the
 // issue of vector instructions, with the lanes whose sites are halo counted (1.4
-// to 1.8 a site and step): 0.6-0.7 of their nominal issue time with FP32 storage
-// (4096^2, 1024^2), 0.92-1.01 with FP16 (8192^2).
+// to 1.8 a site and step): at 0.60-0.70 of their nominal issue rate with FP32
+// storage (1024^2, 4096^2), 0.87-1.02 with FP16 (8192^2), by the clocks.
 // The closures that read their neighbours' moments (NB) shrink by two sites
 // a step: each step's gathered moments go to a second LDS buffer, and the
 // update takes the sites whose eight neighbours were gathered.
