@@ -69,3 +69,23 @@ def test_low_wide_lattices_in_place(nx, ny, rows):
         two.step(n)
         one.step(n)
     assert torch.equal(stored_words(two), stored_words(one))
+
+
+def test_a_lattice_steps_where_the_copies_find_no_memory(monkeypatch):
+    from paper_1607_08675_amd import lattice as lb
+    empty = torch.empty
+
+    def full(*size, **kw):
+        if size == (room,):
+            raise torch.OutOfMemoryError("planted")
+        return empty(*size, **kw)
+
+    room = lattice(5, inplace=True)._halos.numel()
+    monkeypatch.setattr(lb.torch, "empty", full)
+    two, one = lattice(5, steps_per_pass=1), lattice(5, inplace=True)
+    monkeypatch.undo()
+    assert one._halos is None
+    two.step(5)
+    one.step(5)
+    assert torch.equal(stored_words(two), stored_words(one))
+    assert two.diag() == one.diag()
